@@ -8,6 +8,7 @@
 
 #include "../../include/flashfps.h"
 #include "fps_launch.h"
+#include "fps_local.h"
 
 static_assert(ffps::kErrGaveUp == FFPS_ERR_TIMEOUT && ffps::kErrInconsistent == FFPS_ERR_INTERNAL,
               "the kernels write these codes into the status word");
@@ -20,7 +21,7 @@ constexpr size_t kAlign = 256;
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 struct Workspace {  // byte offsets into the caller's workspace
-    size_t status, exchange, cxyz, loc, bitmap, mind, cand, spos, total;
+    size_t status, exchange, cxyz, loc, bitmap, mind, cand, spos, local, local_bytes, total;
 };
 
 Workspace carve(int B, int N, int M) {
@@ -34,6 +35,9 @@ Workspace carve(int B, int N, int M) {
     w.mind = o;     o += align_up((size_t)B * N * sizeof(float));
     w.cand = o;     o += align_up((size_t)B * N * sizeof(int32_t));
     w.spos = o;     o += align_up((size_t)B * sizeof(int));
+    // the local-maximum kernel's area comes last; clouds of one workgroup do not need it
+    w.local = o;    w.local_bytes = N > wgm_capacity() ? local_workspace_bound(B, N) : 0;
+    o += align_up(w.local_bytes);
     w.total = o;
     return w;
 }
@@ -167,6 +171,26 @@ int run_exact(const float *xyz, int B, int N, int M, int start, const int *start
     if (v == FFPS_VARIANT_WG)
         return hip_rc(launch_fps_wg(xyz, B, N, M, start, start_dev, idx, idx_stride, md, md_stride,
                                     variant_picks(variant), (int *)(ws + w.status), s));
+    // AUTO without a cap on the picks of a round (which the kernel does not know): the local-maximum
+    // kernel wherever its area fits, see its file for the two compared.
+    if (v == FFPS_VARIANT_GRID && variant_kind(variant) == FFPS_VARIANT_AUTO && ((variant >> 8) & 0xff) == 0 && M > 1) {
+        const LocalPlan plan = plan_fps_local(B, N, dev.num_cu);
+        size_t bytes = 0;
+        if (plan.wg_per_cloud > 0) {
+            const LocalBuffers l = carve_local(ws + w.local, B, N, plan, &bytes);
+            if (bytes <= w.local_bytes) {
+                int *status = (int *)(ws + w.status);
+                int rc = hip_rc(launch_order(xyz, B, N, l, s));
+                if (rc == FFPS_OK)
+                    rc = hip_rc(launch_local(xyz, l, B, N, M, start, start_dev, plan, status,
+                                             (variant & FFPS_VARIANT_TEST_NO_WAIT) ? 0 : -1, s));
+                if (rc == FFPS_OK)
+                    rc = hip_rc(launch_finish(l, B, N, M, plan.units_per_cloud, start, start_dev, idx, idx_stride, md,
+                                              md_stride, status, s));
+                return rc;
+            }
+        }
+    }
     if (v == FFPS_VARIANT_GRID) {
         const GridPlan plan = plan_fps_grid(B, N, dev.num_cu);
         for (int b = 0; b < B; b += plan.clouds_per_launch) {
@@ -312,7 +336,9 @@ int ffps_exact_noalloc(const float *d_xyz, int B, int N, int M, int start_idx, i
     if (!ws) return FFPS_ERR_LAUNCH_FAILED;
     Workspace w;
     const size_t none = ~(size_t)0;
+    // the local-maximum kernel takes the exchange areas' place where its own area fits there
     w.status = 0; w.exchange = kAlign; w.total = kScratchBytes;
+    w.local = kAlign; w.local_bytes = kScratchBytes - kAlign;
     w.cxyz = w.loc = w.bitmap = w.mind = w.cand = w.spos = none;  // not part of this path
     hipStream_t s = (hipStream_t)stream;
     if ((rc = clear_status(ws, w, s))) return rc;

@@ -1,0 +1,497 @@
+// The two sorts around k_fps_local (fps_local.hip): the points along a space-filling curve
+// before it, the picks by (value descending, index ascending) after it.
+//
+// Points: 15-bit Hilbert codes of a 32^3 grid over the cloud (finer grids make no fewer rounds:
+// a unit of 98 points of the 200,000-point room covers about two cells), a radix sort of 8 and 7
+// bits.  Both passes are stable, so the order, and with it every round of the kernel, is the
+// same in each run.  Four launches: boxes of tiles; codes and counts of the low digit; low digit
+// (which also counts the high one, tile by tile of the result); high digit with the gather of
+// the coordinates.  A block adds up the counts of all tiles itself instead of a scan of its own.
+//
+// Picks: k_fps_local counts them in 8192 bins by value (32 bins to a factor of two), so a pick's
+// bin is known at once; bins are sorted in LDS.
+#include "fps_device.h"
+#include "fps_launch.h"
+#include "fps_local.h"
+
+namespace ffps {
+
+namespace {
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int kOT = 512;               // threads of the ordering kernels
+constexpr int kOW = kOT / kWave;
+constexpr int kLowBins = 256, kHighBins = 128;  // 15 code bits in two digits
+
+// First and last point of a tile.
+__device__ __forceinline__ void tile_range(int N, int tiles, int t, int &lo, int &hi) {
+    const int per = ((N + tiles - 1) / tiles + kOT - 1) / kOT * kOT;
+    lo = min(N, t * per);
+    hi = min(N, lo + per);
+}
+__device__ __forceinline__ int tile_points(int N, int tiles) { return ((N + tiles - 1) / tiles + kOT - 1) / kOT * kOT; }
+
+struct Ext { float lo[3], hi[3]; };
+
+__device__ __forceinline__ void block_box(Ext &e, float (*sh)[6], int tid) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            e.lo[k] = fminf(e.lo[k], __shfl_xor(e.lo[k], o));
+            e.hi[k] = fmaxf(e.hi[k], __shfl_xor(e.hi[k], o));
+        }
+    }
+    if ((tid & 63) == 0) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            sh[tid >> 6][k] = e.lo[k];
+            sh[tid >> 6][3 + k] = e.hi[k];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        for (int v = 0; v < kOW; ++v) {
+            e.lo[k] = fminf(e.lo[k], sh[v][k]);
+            e.hi[k] = fmaxf(e.hi[k], sh[v][3 + k]);
+        }
+    }
+}
+
+// Box of each tile; clears the words the later kernels count and poll in.
+__global__ __launch_bounds__(kOT) void k_order_box(const float *__restrict__ xyz, int N, int tiles, float *__restrict__ boxes,
+                                                   uint32_t *__restrict__ zero, long zero_words, uint32_t *__restrict__ zero2,
+                                                   long zero2_words) {
+    __shared__ float sh[kOW][6];
+    const int tid = threadIdx.x, t = blockIdx.x, b = blockIdx.y;
+    const long nthr = (long)gridDim.x * gridDim.y * kOT, me = ((long)b * gridDim.x + t) * kOT + tid;
+    for (long i = me; i < zero_words; i += nthr) zero[i] = 0u;
+    for (long i = me; i < zero2_words; i += nthr) zero2[i] = 0u;
+    int lo, hi;
+    tile_range(N, tiles, t, lo, hi);
+    const float *p = xyz + (size_t)b * N * 3;
+    Ext e;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) { e.lo[k] = __builtin_inff(); e.hi[k] = -__builtin_inff(); }
+    for (int i = lo + tid; i < hi; i += kOT) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const float v = p[3 * (size_t)i + k];
+            e.lo[k] = fminf(e.lo[k], v);
+            e.hi[k] = fmaxf(e.hi[k], v);
+        }
+    }
+    block_box(e, sh, tid);
+    if (tid < 6) boxes[((size_t)b * tiles + t) * 6 + tid] = tid < 3 ? e.lo[tid] : e.hi[tid - 3];
+}
+
+// 15-bit code of a cell of a 32^3 grid along the Hilbert curve (Skilling's transpose form).
+__device__ __forceinline__ uint32_t hilbert15(uint32_t x, uint32_t y, uint32_t z) {
+    uint32_t X[3] = {x, y, z};
+#pragma unroll
+    for (uint32_t q = 16; q > 1; q >>= 1) {
+        const uint32_t p = q - 1;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            if (X[i] & q) {
+                X[0] ^= p;
+            } else {
+                const uint32_t t = (X[0] ^ X[i]) & p;
+                X[0] ^= t;
+                X[i] ^= t;
+            }
+        }
+    }
+    X[1] ^= X[0];
+    X[2] ^= X[1];
+    uint32_t t = 0;
+#pragma unroll
+    for (uint32_t q = 16; q > 1; q >>= 1)
+        if (X[2] & q) t ^= q - 1;
+    uint32_t r = 0;
+#pragma unroll
+    for (int k = 4; k >= 0; --k) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) r = (r << 1) | (((X[i] ^ t) >> k) & 1u);
+    }
+    return r;
+}
+
+// Codes, and how often each low digit occurs in a tile.
+__global__ __launch_bounds__(kOT) void k_order_code(const float *__restrict__ xyz, int N, int tiles, const float *__restrict__ boxes,
+                                                    uint16_t *__restrict__ codes, uint32_t *__restrict__ hist) {
+    __shared__ float sh[kOW][6];
+    __shared__ uint32_t cnt[kLowBins];
+    const int tid = threadIdx.x, t = blockIdx.x, b = blockIdx.y;
+    if (tid < kLowBins) cnt[tid] = 0;
+    Ext e;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) { e.lo[k] = __builtin_inff(); e.hi[k] = -__builtin_inff(); }
+    for (int i = tid; i < tiles; i += kOT) {
+        const float *q = boxes + ((size_t)b * tiles + i) * 6;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            e.lo[k] = fminf(e.lo[k], q[k]);
+            e.hi[k] = fmaxf(e.hi[k], q[3 + k]);
+        }
+    }
+    block_box(e, sh, tid);
+    const float side = fmaxf(fmaxf(e.hi[0] - e.lo[0], e.hi[1] - e.lo[1]), e.hi[2] - e.lo[2]);
+    const float scale = side > 0.f ? 32.f / side : 0.f;
+    int lo, hi;
+    tile_range(N, tiles, t, lo, hi);
+    const float *p = xyz + (size_t)b * N * 3;
+    for (int i = lo + tid; i < hi; i += kOT) {
+        uint32_t c[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) c[k] = (uint32_t)fmaxf(0.f, fminf(31.f, (p[3 * (size_t)i + k] - e.lo[k]) * scale));
+        const uint32_t code = hilbert15(c[0], c[1], c[2]);
+        codes[(size_t)b * N + i] = (uint16_t)code;
+        atomicAdd(&cnt[code & (kLowBins - 1)], 1u);
+    }
+    __syncthreads();
+    if (tid < kLowBins) hist[((size_t)b * tiles + t) * kLowBins + tid] = cnt[tid];
+}
+
+// Lanes of the wave whose digit equals this lane's (among the lanes of `valid`).
+template <int BITS>
+__device__ __forceinline__ uint64_t same_digit(uint32_t d, uint64_t valid) {
+    uint64_t m = valid;
+#pragma unroll
+    for (int k = 0; k < BITS; ++k) {
+        const bool on = (d >> k) & 1u;
+        const uint64_t s = __builtin_amdgcn_ballot_w64(on);
+        m &= on ? s : ~s;
+    }
+    return m;
+}
+__device__ __forceinline__ int lanes_below(uint64_t m) {
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// One pass of a stable radix sort: a block moves the elements of its tile behind those of
+// earlier tiles and, within the tile, behind those of earlier waves.  `digit(i)` is the digit
+// of element i, `move(i, pos)` puts it in its place.
+template <int BITS, typename D, typename MV>
+__device__ __forceinline__ void stable_pass(const uint32_t *__restrict__ hist, int tiles, int t, int lo, int hi, int tid,
+                                            uint32_t (*cnt)[1 << BITS], uint32_t *part, D digit, MV move) {
+    constexpr int NB = 1 << BITS;
+    static_assert(NB <= kOT, "a thread per digit");
+    const int lane = tid & 63, wave = tid >> 6;
+    for (int i = tid; i < kOW * NB; i += kOT) (&cnt[0][0])[i] = 0;
+    // elements of each digit in earlier tiles, and in all of them
+    uint32_t before = 0, total = 0;
+    if (tid < NB) {
+#pragma unroll 8
+        for (int k = 0; k < tiles; ++k) {
+            const uint32_t h = hist[(size_t)k * NB + tid];
+            before += k < t ? h : 0u;
+            total += h;
+        }
+        part[tid] = total;
+    }
+    __syncthreads();
+    const int rows = (hi - lo + kOT - 1) / kOT, w0 = lo + wave * rows * kWave;
+    for (int r = 0; r < rows; ++r) {
+        const int i = w0 + r * kWave + lane;
+        if (i < hi) atomicAdd(&cnt[wave][digit(i)], 1u);
+    }
+    for (int o = 1; o < NB; o <<= 1) {
+        const uint32_t v = tid < NB && tid >= o ? part[tid - o] : 0u;
+        __syncthreads();
+        if (tid < NB) part[tid] += v;
+        __syncthreads();
+    }
+    if (tid < NB) {
+        uint32_t at = part[tid] - total + before;
+        for (int v = 0; v < kOW; ++v) {
+            const uint32_t c = cnt[v][tid];
+            cnt[v][tid] = at;
+            at += c;
+        }
+    }
+    __syncthreads();
+    for (int r = 0; r < rows; ++r) {
+        const int i = w0 + r * kWave + lane;
+        const bool ok = i < hi;
+        const uint32_t d = ok ? digit(i) : 0u;
+        const uint64_t m = same_digit<BITS>(d, __builtin_amdgcn_ballot_w64(ok));
+        if (ok) {
+            const uint32_t base = cnt[wave][d];
+            const int r_in = lanes_below(m);
+            move(i, base + r_in);
+            if (r_in == 0) cnt[wave][d] = base + (uint32_t)__builtin_popcountll(m);
+        }
+    }
+}
+
+__global__ __launch_bounds__(kOT) void k_order_low(int N, int tiles, const uint16_t *__restrict__ codes, const uint32_t *__restrict__ hist,
+                                                   u32x2 *__restrict__ pairs, uint32_t *__restrict__ hist2) {
+    __shared__ uint32_t cnt[kOW][kLowBins], part[kLowBins];
+    const int tid = threadIdx.x, t = blockIdx.x, b = blockIdx.y;
+    int lo, hi;
+    tile_range(N, tiles, t, lo, hi);
+    const int per = tile_points(N, tiles);
+    const uint16_t *c = codes + (size_t)b * N;
+    u32x2 *out = pairs + (size_t)b * N;
+    uint32_t *h2 = hist2 + (size_t)b * tiles * kHighBins;
+    stable_pass<8>(hist + (size_t)b * tiles * kLowBins, tiles, t, lo, hi, tid, cnt, part,
+                   [&](int i) { return (uint32_t)c[i] & (kLowBins - 1); },
+                   [&](int i, uint32_t pos) {
+                       const uint32_t h = (uint32_t)c[i] >> 8;
+                       out[pos] = u32x2{(uint32_t)i, h};
+                       atomicAdd(&h2[(pos / (uint32_t)per) * kHighBins + h], 1u);
+                   });
+}
+
+__global__ __launch_bounds__(kOT) void k_order_high(const float *__restrict__ xyz, int N, int tiles, const u32x2 *__restrict__ pairs,
+                                                    const uint32_t *__restrict__ hist2, u32x4 *__restrict__ pts) {
+    __shared__ uint32_t cnt[kOW][kHighBins], part[kHighBins];
+    const int tid = threadIdx.x, t = blockIdx.x, b = blockIdx.y;
+    int lo, hi;
+    tile_range(N, tiles, t, lo, hi);
+    const u32x2 *in = pairs + (size_t)b * N;
+    const float *p = xyz + (size_t)b * N * 3;
+    u32x4 *out = pts + (size_t)b * N;
+    stable_pass<7>(hist2 + (size_t)b * tiles * kHighBins, tiles, t, lo, hi, tid, cnt, part,
+                   [&](int i) { return in[i].y; },
+                   [&](int i, uint32_t pos) {
+                       const uint32_t k = in[i].x;
+                       out[pos] = u32x4{f2u(p[3 * (size_t)k]), f2u(p[3 * (size_t)k + 1]), f2u(p[3 * (size_t)k + 2]), k};
+                   });
+}
+
+// ---- the picks in their order ----------------------------------------------------
+constexpr int kFT = 1024;
+constexpr int kSortMax = 2048;  // picks of a bin that are sorted in LDS
+
+struct FinishArgs {
+    int N, M, U;                // points, samples, units of a cloud
+    const int *start_dev;
+    int start;
+    const u32x4 *picks;         // [B][N] per unit {value, index, round, -}
+    const int *npicks;          // [B][U]
+    const uint32_t *hist;       // [B][kLocalWords]: picks per bin
+    uint32_t *cursor;           // [B][kLocalBins], zero
+    u32x2 *runs;                // [B][kLocalBins] {first place, picks} of the bins in use
+    int *nruns;                 // [B]
+    uint64_t *keys;             // [B][N]
+    uint64_t *spare;            // [B][2 N]: the lists, which are done with by the time it is used
+    int32_t *idx;
+    long idx_stride;
+    float *md;
+    long md_stride;
+    int *status;
+};
+
+// Places of the bins (largest values first), then every pick into its bin.
+__global__ __launch_bounds__(kFT) void k_finish_bins(FinishArgs a) {
+    __shared__ uint32_t base[kLocalBins], cnt[kLocalBins], part[kFT];
+    const int tid = threadIdx.x, b = blockIdx.y;
+    const uint32_t *hist = a.hist + (size_t)b * kLocalWords;
+    constexpr int per = kLocalBins / kFT;
+    // thread t: bins kLocalBins - 1 - t * per downwards
+    uint32_t h[per], sum = 0, used = 0;
+#pragma unroll
+    for (int k = 0; k < per; ++k) {
+        h[k] = hist[local_bin_place(kLocalBins - 1 - (tid * per + k))];
+        sum += h[k];
+        used += h[k] ? 1u : 0u;
+    }
+    part[tid] = sum;
+    __syncthreads();
+    for (int o = 1; o < kFT; o <<= 1) {
+        const uint32_t v = tid >= o ? part[tid - o] : 0u;
+        __syncthreads();
+        part[tid] += v;
+        __syncthreads();
+    }
+    uint32_t at = part[tid] - sum;
+    const uint32_t first = at;
+#pragma unroll
+    for (int k = 0; k < per; ++k) {
+        const int bin = kLocalBins - 1 - (tid * per + k);
+        base[bin] = at;
+        cnt[bin] = 0;
+        at += h[k];
+    }
+    const uint32_t total = part[kFT - 1];
+    __syncthreads();
+    if (blockIdx.x == 0) {
+        // the bins that hold samples, for the next kernel; samples beyond the picks repeat point 0
+        uint32_t n = 0;
+        if (first < (uint32_t)(a.M - 1)) n = used;
+        part[tid] = n;
+        __syncthreads();
+        for (int o = 1; o < kFT; o <<= 1) {
+            const uint32_t v = tid >= o ? part[tid - o] : 0u;
+            __syncthreads();
+            part[tid] += v;
+            __syncthreads();
+        }
+        uint32_t r = part[tid] - n;
+        if (n) {
+            uint32_t p = first;
+#pragma unroll
+            for (int k = 0; k < per; ++k) {
+                if (h[k]) a.runs[(size_t)b * kLocalBins + r++] = u32x2{p, h[k]};
+                p += h[k];
+            }
+        }
+        if (tid == 0) {
+            a.nruns[b] = (int)part[kFT - 1];
+            a.idx[b * a.idx_stride] = a.start_dev ? a.start_dev[b] : a.start;
+            if (a.md) a.md[b * a.md_stride] = __builtin_inff();
+        }
+        for (uint32_t k = total + tid; k < (uint32_t)(a.M - 1); k += kFT) {
+            a.idx[b * a.idx_stride + 1 + k] = 0;
+            if (a.md) a.md[b * a.md_stride + 1 + k] = 0.f;
+        }
+    }
+    // units of this block
+    const int u0 = (int)((long)blockIdx.x * a.U / gridDim.x), u1 = (int)((long)(blockIdx.x + 1) * a.U / gridDim.x);
+    const int lane = tid & 63, wave = tid >> 6;
+    const u32x4 *picks = a.picks + (size_t)b * a.N;
+    for (int u = u0 + wave; u < u1; u += kFT / kWave) {
+        const u32x4 *l = picks + (int)((long)u * a.N / a.U);
+        const int n = a.npicks[(size_t)b * a.U + u];
+        for (int k = lane; k < n; k += kWave) atomicAdd(&cnt[(l[k].x >> kLocalBinShift) & (kLocalBins - 1)], 1u);
+    }
+    __syncthreads();
+    for (int i = tid; i < kLocalBins; i += kFT) {
+        const uint32_t c = cnt[i];
+        if (c) cnt[i] = base[i] + atomicAdd(&a.cursor[(size_t)b * kLocalBins + i], c);
+    }
+    __syncthreads();
+    uint32_t rounds = 0;
+    for (int u = u0 + wave; u < u1; u += kFT / kWave) {
+        const u32x4 *l = picks + (int)((long)u * a.N / a.U);
+        const int n = a.npicks[(size_t)b * a.U + u];
+        for (int k = lane; k < n; k += kWave) {
+            const u32x4 p = l[k];
+            const uint32_t bin = (p.x >> kLocalBinShift) & (kLocalBins - 1);
+            if (base[bin] < (uint32_t)(a.M - 1)) rounds = umax(rounds, p.z);
+            const uint32_t pos = atomicAdd(&cnt[bin], 1u);
+            a.keys[(size_t)b * a.N + pos] = ((uint64_t)p.x << 32) | (uint32_t)~p.y;
+        }
+    }
+    rounds = wave_max_u32(rounds);
+    if (lane == 0 && rounds) __hip_atomic_fetch_max(a.status + 1, (int)rounds, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Sorts each bin (descending keys) and writes the samples.
+__global__ __launch_bounds__(256) void k_finish_sort(FinishArgs a) {
+    __shared__ uint64_t s[kSortMax];
+    __shared__ uint32_t cnt[256];
+    const int tid = threadIdx.x, b = blockIdx.y, wave = tid >> 6;
+    const int n_runs = a.nruns[b];
+    auto put = [&](uint32_t place, uint64_t key) {
+        if (place < (uint32_t)(a.M - 1)) {
+            a.idx[b * a.idx_stride + 1 + place] = (int32_t)~(uint32_t)key;
+            if (a.md) a.md[b * a.md_stride + 1 + place] = u2f((uint32_t)(key >> 32));
+        }
+    };
+    for (int j = blockIdx.x; j < n_runs; j += gridDim.x) {
+        const u32x2 run = a.runs[(size_t)b * kLocalBins + j];
+        uint64_t *keys = a.keys + (size_t)b * a.N + run.x;
+        const int n = (int)run.y;
+        if (n <= kSortMax) {
+            int size = 2;
+            while (size < n) size <<= 1;
+            for (int i = tid; i < size; i += 256) s[i] = i < n ? keys[i] : 0ull;
+            __syncthreads();
+            for (int k = 2; k <= size; k <<= 1) {
+                for (int o = k >> 1; o > 0; o >>= 1) {
+                    for (int i = tid; i < size / 2; i += 256) {
+                        const int p = 2 * i - (i & (o - 1)), q = p + o;
+                        const uint64_t x = s[p], y = s[q];
+                        const bool up = (p & k) != 0;  // ascending half
+                        if ((x < y) != up) { s[p] = y; s[q] = x; }
+                    }
+                    __syncthreads();
+                }
+            }
+            for (int i = tid; i < n; i += 256) put(run.x + i, s[i]);
+            __syncthreads();
+        } else {
+            // many picks of nearly one value (lattices): a radix sort of the complements by this
+            // block alone, 8 bits at a time, four waves taking 64 keys each in turn
+            uint64_t *src = keys, *dst = a.spare + (size_t)b * 2 * a.N + run.x;
+            for (int shift = 0; shift < 64; shift += 8) {
+                cnt[tid] = 0;
+                __syncthreads();
+                for (int i = tid; i < n; i += 256) atomicAdd(&cnt[(uint32_t)(~src[i] >> shift) & 255u], 1u);
+                __syncthreads();
+                const uint32_t own = cnt[tid];
+                for (int o = 1; o < 256; o <<= 1) {
+                    const uint32_t v = tid >= o ? cnt[tid - o] : 0u;
+                    __syncthreads();
+                    cnt[tid] += v;
+                    __syncthreads();
+                }
+                const uint32_t at = cnt[tid] - own;
+                __syncthreads();
+                cnt[tid] = at;
+                const bool one_digit = __syncthreads_or(own == (uint32_t)n);
+                if (one_digit) continue;
+                for (int i0 = 0; i0 < n; i0 += 256) {
+                    const int i = i0 + tid;
+                    const bool ok = i < n;
+                    const uint64_t key = ok ? src[i] : 0ull;
+                    const uint32_t d = (uint32_t)(~key >> shift) & 255u;
+                    const uint64_t m = same_digit<8>(d, __builtin_amdgcn_ballot_w64(ok));
+                    for (int v = 0; v < 4; ++v) {
+                        if (wave == v && ok) {
+                            const uint32_t base = cnt[d];
+                            const int r_in = lanes_below(m);
+                            dst[base + r_in] = key;
+                            if (r_in == 0) cnt[d] = base + (uint32_t)__builtin_popcountll(m);
+                        }
+                        __syncthreads();
+                    }
+                }
+                uint64_t *t = src; src = dst; dst = t;
+                __syncthreads();
+            }
+            for (int i = tid; i < n; i += 256) put(run.x + i, src[i]);
+            __syncthreads();
+        }
+    }
+}
+
+}  // namespace
+
+int order_tiles(int N) {
+    const int t = (N + 2047) / 2048;
+    return t < 1 ? 1 : t > 256 ? 256 : t;
+}
+
+hipError_t launch_order(const float *xyz, int B, int N, const LocalBuffers &l, hipStream_t s) {
+    const int tiles = order_tiles(N);
+    const dim3 grid(tiles, B);
+    u32x2 *pairs = (u32x2 *)l.picks;  // the picks come later
+    k_order_box<<<grid, dim3(kOT), 0, s>>>(xyz, N, tiles, l.boxes, (uint32_t *)l.zeroed, (long)(l.zero_bytes / 4), l.hist2,
+                                           (long)B * tiles * kHighBins);
+    k_order_code<<<grid, dim3(kOT), 0, s>>>(xyz, N, tiles, l.boxes, l.codes, l.hist1);
+    k_order_low<<<grid, dim3(kOT), 0, s>>>(N, tiles, l.codes, l.hist1, pairs, l.hist2);
+    k_order_high<<<grid, dim3(kOT), 0, s>>>(xyz, N, tiles, pairs, l.hist2, (u32x4 *)l.pts);
+    return hipGetLastError();
+}
+
+hipError_t launch_finish(const LocalBuffers &l, int B, int N, int M, int units, int start, const int *start_dev, int32_t *idx, long idx_stride,
+                         float *md, long md_stride, int *status, hipStream_t s) {
+    FinishArgs a;
+    a.N = N; a.M = M; a.U = units; a.start = start; a.start_dev = start_dev;
+    a.picks = (const u32x4 *)l.picks; a.npicks = l.npicks; a.hist = l.hist; a.cursor = l.cursor;
+    a.runs = (u32x2 *)l.runs; a.nruns = l.nruns; a.keys = (uint64_t *)l.pts; a.spare = (uint64_t *)l.picks;
+    a.idx = idx; a.idx_stride = idx_stride; a.md = md; a.md_stride = md_stride; a.status = status;
+    const int gb = B >= 32 ? 1 : units < 256 ? 4 : 32;
+    k_finish_bins<<<dim3(gb, B), dim3(kFT), 0, s>>>(a);
+    k_finish_sort<<<dim3(B >= 8 ? 64 : 256, B), dim3(256), 0, s>>>(a);
+    return hipGetLastError();
+}
+
+}  // namespace ffps
