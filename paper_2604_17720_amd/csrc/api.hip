@@ -259,7 +259,7 @@ int run_prune(const float *xyz, int B, int N, int M, int start, int keep_num, in
         rc = run_exact(xyz, B, N, k, start, nullptr, variant, idx, idx_stride, nullptr, 0, ws, w, dev, s);
         if (rc) return rc;
     }
-    if (perm) return hip_rc(launch_fill_perm(B, N, k, R, seed, idx, idx_stride, bitmap, s));
+    if (perm) return hip_rc(launch_fill_perm(B, N, k, R, seed, idx, idx_stride, bitmap, (int *)(ws + w.cand), s));  // the list is done with
     return hip_rc(launch_fill(B, N, k, R, idx, idx_stride, bitmap, s));
 }
 

@@ -53,63 +53,82 @@ __global__ void k_map_candidates(const int32_t *__restrict__ loc, long loc_strid
         idx[b * idx_stride + j] = cand_at(loc[b * loc_stride + j], N, Nc, start, j0);
 }
 
-// One workgroup per cloud: bitmap of the k FPS picks, ranks of the free
-// indices by popcount + scan, then every free index decides on its own whether
+// bm[b] |= the k picks of cloud b (bitmap cleared beforehand)
+__global__ void k_mark_picks(int N, int k, const int32_t *__restrict__ idx_all, long idx_stride, uint32_t *__restrict__ bitmap_all) {
+    const int b = blockIdx.y;
+    uint32_t *bm = bitmap_all + (size_t)b * ((N + 31) / 32);
+    const int32_t *idx = idx_all + b * idx_stride;
+    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < k; j += gridDim.x * blockDim.x) {
+        const int v = idx[j];
+        atomicOr(&bm[v >> 5], 1u << (v & 31));
+    }
+}
+
+constexpr int kTileWords = 1024;  // bitmap words of a tile, one per thread: 32,768 points
+
+// Exclusive prefix over the block of one count per thread; `total` receives the sum.
+__device__ __forceinline__ int block_prefix(int cnt, int *part, int tid, int *total) {
+    part[tid] = cnt;
+    __syncthreads();
+    for (int off = 1; off < 1024; off <<= 1) {  // inclusive scan
+        const int v = tid >= off ? part[tid - off] : 0;
+        __syncthreads();
+        part[tid] += v;
+        __syncthreads();
+    }
+    if (total) *total = part[1023];
+    const int r = part[tid] - cnt;
+    __syncthreads();
+    return r;
+}
+
+// Fill of FPS-Prune, a tile of the bitmap per block: ranks of the free indices by popcount
+// (a block counts the words of the tiles before its own again: 25 KB for 200,000 points) and
+// scan, then every free index decides on its own whether
 // some j maps to its rank: fill[j] = free[floor(j*F/R)], F = N - k.  Since
 // F >= R the ranks floor(j*F/R) are distinct, and rank r is hit exactly by
 // j = ceil(r*R/F) when floor(j*F/R) == r.
+// Clouds of one tile are marked here as well, in the same launch.  One block did clouds of all
+// sizes before: 51 us for 200,000 points, with tiles 14 us in three launches.
 __global__ __launch_bounds__(1024) void k_fill(int N, int k, int R, int32_t *__restrict__ idx_all,
                                                long idx_stride, uint32_t *__restrict__ bitmap_all) {
     __shared__ int part[1024];
-    const int b = blockIdx.x;
+    const int b = blockIdx.y, tile = blockIdx.x;
     const int tid = threadIdx.x;
     const int words = (N + 31) / 32;
     uint32_t *bm = bitmap_all + (size_t)b * words;
     int32_t *idx = idx_all + b * idx_stride;
 
-    for (int i = tid; i < words; i += 1024) bm[i] = 0u;
-    __syncthreads();
-    for (int j = tid; j < k; j += 1024) {
-        int v = idx[j];
-        atomicOr(&bm[v >> 5], 1u << (v & 31));
-    }
-    __syncthreads();
-
-    const int per = (words + 1023) / 1024;
-    const int w0 = tid * per;
-    const int w1 = min(words, w0 + per);
-    int cnt = 0;
-    for (int wd = w0; wd < w1; ++wd) {
-        uint32_t valid = (wd == words - 1 && (N & 31)) ? ((1u << (N & 31)) - 1u) : 0xffffffffu;
-        cnt += __popc(~bm[wd] & valid);
-    }
-    part[tid] = cnt;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {  // inclusive scan
-        int v = tid >= off ? part[tid - off] : 0;
+    if (gridDim.x == 1) {
+        for (int i = tid; i < words; i += 1024) bm[i] = 0u;
         __syncthreads();
-        part[tid] += v;
+        for (int j = tid; j < k; j += 1024) {
+            int v = idx[j];
+            atomicOr(&bm[v >> 5], 1u << (v & 31));
+        }
         __syncthreads();
     }
+    int before = 0;
+    for (int wd = tid; wd < tile * kTileWords; wd += 1024) before += __popc(~bm[wd]);
+    if (tile > 0) (void)block_prefix(before, part, tid, &before);
+    const int wd = tile * kTileWords + tid;
+    uint32_t free_bits = 0u;
+    if (wd < words) free_bits = ~bm[wd] & ((wd == words - 1 && (N & 31)) ? ((1u << (N & 31)) - 1u) : 0xffffffffu);
     // Rank r is taken by fill slot j = ceil(r*R/F) iff floor(j*F/R) == r, i.e. iff
     // acc = j*F - r*R lies in [0, R).  One division finds j for the thread's first
     // rank; from rank to rank acc drops by R and, when it goes negative, j steps up.
-    long r = part[tid] - cnt;  // rank of this thread's first free index
+    const long r = before + block_prefix(__popc(free_bits), part, tid, nullptr);  // rank of the first free index
     const long F = (long)N - k;
     long j = (r * R + F - 1) / F;
     long acc = j * F - r * R;
-    for (int wd = w0; wd < w1; ++wd) {
-        uint32_t valid = (wd == words - 1 && (N & 31)) ? ((1u << (N & 31)) - 1u) : 0xffffffffu;
-        uint32_t free_bits = ~bm[wd] & valid;
-        while (free_bits) {
-            int bit = __ffs(free_bits) - 1;
-            free_bits &= free_bits - 1;
-            if (acc < R && j < R) idx[k + j] = wd * 32 + bit;
-            acc -= R;
-            if (acc < 0) {
-                ++j;
-                acc += F;
-            }
+    while (free_bits) {
+        const int bit = __ffs(free_bits) - 1;
+        free_bits &= free_bits - 1;
+        if (acc < R && j < R) idx[k + j] = wd * 32 + bit;
+        acc -= R;
+        if (acc < 0) {
+            ++j;
+            acc += F;
         }
     }
 }
@@ -213,95 +232,104 @@ __global__ void k_perm_mark(int N, int Nc, uint64_t seed, uint32_t *__restrict__
     }
 }
 
-// One workgroup per cloud: force `start` into the candidate set (in place of
-// the last drawn candidate), then list the set in ascending order with the
-// candidates' coordinates, and report the position of `start` in it.
+// The candidate set in ascending order with the candidates' coordinates, a tile of the bitmap per
+// block; `start` takes the place of the last drawn candidate when it was not drawn.  A wave takes
+// two words at a time, a lane per bit, so that list and coordinates are written side by side.
+// (One block with a stretch of words per thread took 429 us for 300,000 points.)
 __global__ __launch_bounds__(1024) void k_perm_compact(const float *__restrict__ xyz_all, int N, int Nc,
                                                        int start, uint64_t seed,
-                                                       uint32_t *__restrict__ bitmap_all,
+                                                       const uint32_t *__restrict__ bitmap_all,
                                                        int32_t *__restrict__ cand_all,
                                                        float *__restrict__ cxyz_all,
                                                        int *__restrict__ spos_all) {
     __shared__ int part[1024];
-    const int b = blockIdx.x;
-    const int tid = threadIdx.x;
+    __shared__ uint32_t bits_of[kTileWords];
+    __shared__ int rank_of[kTileWords];
+    const int b = blockIdx.y, tile = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int words = (N + 31) / 32;
-    uint32_t *bm = bitmap_all + (size_t)b * words;
+    const uint32_t *bm = bitmap_all + (size_t)b * words;
     const float *xyz = xyz_all + (size_t)b * N * 3;
     int32_t *cand = cand_all + (size_t)b * Nc;
     float *cxyz = cxyz_all + (size_t)b * Nc * 3;
-    if (tid == 0 && !((bm[start >> 5] >> (start & 31)) & 1u)) {
-        const uint32_t last = perm_at(make_perm(N, seed + (uint64_t)b), (uint32_t)(Nc - 1));
-        bm[last >> 5] &= ~(1u << (last & 31));
-        bm[start >> 5] |= 1u << (start & 31);
-    }
+    const bool drawn = (bm[start >> 5] >> (start & 31)) & 1u;
+    const int last = drawn ? -1 : (int)perm_at(make_perm(N, seed + (uint64_t)b), (uint32_t)(Nc - 1));
+    auto word = [&](int wd) {
+        uint32_t v = bm[wd];
+        if (!drawn) {
+            if (wd == last >> 5) v &= ~(1u << (last & 31));
+            if (wd == start >> 5) v |= 1u << (start & 31);
+        }
+        return v;
+    };
+    int before = 0;
+    for (int wd = tid; wd < tile * kTileWords; wd += 1024) before += __popc(word(wd));
+    if (tile > 0) (void)block_prefix(before, part, tid, &before);
+    const int wd0 = tile * kTileWords;
+    const uint32_t own = wd0 + tid < words ? word(wd0 + tid) : 0u;
+    const int r = before + block_prefix(__popc(own), part, tid, nullptr);
+    bits_of[tid] = own;
+    rank_of[tid] = r;
     __syncthreads();
-    const int per = (words + 1023) / 1024;
-    const int w0 = tid * per, w1 = min(words, w0 + per);
-    int cnt = 0;
-    for (int wd = w0; wd < w1; ++wd) cnt += __popc(bm[wd]);
-    part[tid] = cnt;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {  // inclusive scan
-        int v = tid >= off ? part[tid - off] : 0;
-        __syncthreads();
-        part[tid] += v;
-        __syncthreads();
-    }
-    int r = part[tid] - cnt;
-    for (int wd = w0; wd < w1; ++wd) {
-        uint32_t bits = bm[wd];
-        while (bits) {
-            const int i = wd * 32 + __ffs(bits) - 1;
-            bits &= bits - 1;
-            cand[r] = i;
-            cxyz[3 * (size_t)r + 0] = xyz[3 * (size_t)i + 0];
-            cxyz[3 * (size_t)r + 1] = xyz[3 * (size_t)i + 1];
-            cxyz[3 * (size_t)r + 2] = xyz[3 * (size_t)i + 2];
-            if (i == start) spos_all[b] = r;
-            ++r;
+    for (int p = wave; p < kTileWords / 2; p += 16) {
+        const int t = 2 * p + (lane >> 5);
+        const uint32_t v = bits_of[t];
+        if ((v >> (lane & 31)) & 1u) {
+            const int at = rank_of[t] + __popc(v & ((1u << (lane & 31)) - 1u));
+            const int i = (wd0 + t) * 32 + (lane & 31);
+            cand[at] = i;
+            cxyz[3 * (size_t)at + 0] = xyz[3 * (size_t)i + 0];
+            cxyz[3 * (size_t)at + 1] = xyz[3 * (size_t)i + 1];
+            cxyz[3 * (size_t)at + 2] = xyz[3 * (size_t)i + 2];
+            if (i == start) spos_all[b] = at;
         }
     }
 }
 
-// One workgroup per cloud: idx[k + r] = r-th index, in the order of a second
-// permutation of [0, N), that is not among idx[0..k); r < R.
+// The seeded fill: idx[k + r] = r-th index, in the order of a second permutation of [0, N), that
+// is not among the picks (marked in the bitmap); r < R.  A tile of 4096 places of the permutation
+// per block, twice: the first launch counts the free ones of each tile, the second places them.
+// (One block walking through all places took 1560 us for 300,000 points.)
+constexpr int kPermTile = 4096;
+template <bool COUNT>
 __global__ __launch_bounds__(1024) void k_fill_perm(int N, int k, int R, uint64_t seed,
                                                     int32_t *__restrict__ idx_all, long idx_stride,
-                                                    uint32_t *__restrict__ bitmap_all) {
+                                                    const uint32_t *__restrict__ bitmap_all, int *__restrict__ free_all) {
     __shared__ int part[1024];
-    const int b = blockIdx.x;
+    const int b = blockIdx.y, tile = blockIdx.x;
     const int tid = threadIdx.x;
-    const int words = (N + 31) / 32;
-    uint32_t *bm = bitmap_all + (size_t)b * words;
+    const uint32_t *bm = bitmap_all + (size_t)b * ((N + 31) / 32);
     int32_t *idx = idx_all + b * idx_stride;
-    for (int i = tid; i < words; i += 1024) bm[i] = 0u;
-    __syncthreads();
-    for (int j = tid; j < k; j += 1024) {
-        int v = idx[j];
-        atomicOr(&bm[v >> 5], 1u << (v & 31));
+    int *nfree = free_all + (size_t)b * gridDim.x;
+    int before = 0;
+    if constexpr (!COUNT) {
+        for (int t = tid; t < tile; t += 1024) before += nfree[t];
+        (void)block_prefix(before, part, tid, &before);
+        if (before >= R) return;
     }
-    __syncthreads();
     const Perm p = make_perm(N, (seed + (uint64_t)b) ^ kFillSeedXor);
-    const int per = (N + 1023) / 1024;
-    const int j0 = tid * per, j1 = min(N, j0 + per);
+    constexpr int per = kPermTile / 1024;
+    uint32_t at[per];
     int cnt = 0;
-    for (int j = j0; j < j1; ++j) {
-        const uint32_t t = perm_at(p, (uint32_t)j);
-        cnt += !((bm[t >> 5] >> (t & 31)) & 1u);
+    bool is_free[per];
+#pragma unroll
+    for (int e = 0; e < per; ++e) {
+        const int j = tile * kPermTile + tid * per + e;
+        is_free[e] = false;
+        if (j < N) {
+            at[e] = perm_at(p, (uint32_t)j);
+            is_free[e] = !((bm[at[e] >> 5] >> (at[e] & 31)) & 1u);
+        }
+        cnt += is_free[e] ? 1 : 0;
     }
-    part[tid] = cnt;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        int v = tid >= off ? part[tid - off] : 0;
-        __syncthreads();
-        part[tid] += v;
-        __syncthreads();
-    }
-    int r = part[tid] - cnt;
-    for (int j = j0; j < j1 && r < R; ++j) {
-        const uint32_t t = perm_at(p, (uint32_t)j);
-        if (!((bm[t >> 5] >> (t & 31)) & 1u)) idx[k + r++] = (int32_t)t;
+    int total = 0;
+    int r = before + block_prefix(cnt, part, tid, &total);
+    if constexpr (COUNT) {
+        if (tid == 0) nfree[tile] = total;
+    } else {
+#pragma unroll
+        for (int e = 0; e < per; ++e)
+            if (is_free[e] && r < R) idx[k + r++] = (int32_t)at[e];
     }
 }
 
@@ -391,10 +419,25 @@ hipError_t launch_map_candidates(const int32_t *loc, long loc_stride, int B, int
     return hipGetLastError();
 }
 
+// Clears the bitmap and marks the picks in it.
+static hipError_t mark_picks(int B, int N, int k, const int32_t *idx, long idx_stride, uint32_t *bitmap, hipStream_t s) {
+    const size_t words = (size_t)B * ((N + 31) / 32);
+    hipLaunchKernelGGL(k_fill_zero, dim3(blocks_for(words)), dim3(kT), 0, s, bitmap, words);
+    hipLaunchKernelGGL(k_mark_picks, dim3(blocks_for(k), B), dim3(kT), 0, s, N, k, idx, idx_stride, bitmap);
+    return hipGetLastError();
+}
+
+static int bitmap_tiles(int N) { return ((N + 31) / 32 + kTileWords - 1) / kTileWords; }
+
 hipError_t launch_fill(int B, int N, int k, int R, int32_t *idx, long idx_stride, uint32_t *bitmap,
                        hipStream_t s) {
     if (R <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_fill, dim3(B), dim3(1024), 0, s, N, k, R, idx, idx_stride, bitmap);
+    const int tiles = bitmap_tiles(N);
+    if (tiles > 1) {
+        hipError_t e = mark_picks(B, N, k, idx, idx_stride, bitmap, s);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_fill, dim3(tiles, B), dim3(1024), 0, s, N, k, R, idx, idx_stride, bitmap);
     return hipGetLastError();
 }
 
@@ -404,15 +447,21 @@ hipError_t launch_perm_candidates(const float *xyz, int B, int N, int Nc, int st
     const size_t words = (size_t)B * ((N + 31) / 32);
     hipLaunchKernelGGL(k_fill_zero, dim3(blocks_for(words)), dim3(kT), 0, s, bitmap, words);
     hipLaunchKernelGGL(k_perm_mark, dim3(blocks_for(Nc), B), dim3(kT), 0, s, N, Nc, seed, bitmap);
-    hipLaunchKernelGGL(k_perm_compact, dim3(B), dim3(1024), 0, s, xyz, N, Nc, start, seed, bitmap, cand,
+    hipLaunchKernelGGL(k_perm_compact, dim3(bitmap_tiles(N), B), dim3(1024), 0, s, xyz, N, Nc, start, seed, bitmap, cand,
                        cxyz, spos);
     return hipGetLastError();
 }
 
+size_t fill_perm_count_words(int N) { return (size_t)(N + kPermTile - 1) / kPermTile; }
+
 hipError_t launch_fill_perm(int B, int N, int k, int R, uint64_t seed, int32_t *idx, long idx_stride,
-                            uint32_t *bitmap, hipStream_t s) {
+                            uint32_t *bitmap, int *counts, hipStream_t s) {
     if (R <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_fill_perm, dim3(B), dim3(1024), 0, s, N, k, R, seed, idx, idx_stride, bitmap);
+    hipError_t e = mark_picks(B, N, k, idx, idx_stride, bitmap, s);
+    if (e != hipSuccess) return e;
+    const dim3 grid((unsigned)fill_perm_count_words(N), B);
+    hipLaunchKernelGGL(k_fill_perm<true>, grid, dim3(1024), 0, s, N, k, R, seed, idx, idx_stride, bitmap, counts);
+    hipLaunchKernelGGL(k_fill_perm<false>, grid, dim3(1024), 0, s, N, k, R, seed, idx, idx_stride, bitmap, counts);
     return hipGetLastError();
 }
 

@@ -81,7 +81,8 @@ hipError_t launch_perm_candidates(const float *xyz, int B, int N, int Nc, int st
 // idx[b][k + r], r < R = first R indices, in the order of a second seeded permutation,
 // that are not in idx[b][0..k)
 hipError_t launch_fill_perm(int B, int N, int k, int R, uint64_t seed, int32_t *idx, long idx_stride,
-                            uint32_t *bitmap, hipStream_t s);
+                            uint32_t *bitmap, int *counts, hipStream_t s);
+size_t fill_perm_count_words(int N);  // words of `counts` per cloud
 // dst[b][j] = xyz[b][sel[b][j]] for j < S
 hipError_t launch_gather_points(const float *xyz, int B, int N, const int32_t *sel,
                                 long sel_stride, int S, float *dst, hipStream_t s);

@@ -1,0 +1,25 @@
+"""Candidate sets and fills of FPS-Prune at the edges of their tiles (32,768 points of the bitmap,
+4,096 places of the seeded permutation), whole numbers against the oracle."""
+import numpy as np
+import pytest
+
+from paper_2604_17720_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,m,start,b", [(31, 9, 30, 3), (4096, 2048, 0, 2), (4097, 4097, 4096, 1), (32768, 900, 32767, 1),
+                                         (32769, 3000, 32768, 2), (65537, 700, 5, 1), (1100003, 300, 1100002, 1)])
+@pytest.mark.parametrize("flags", [3, 7])
+def test_prune_at_the_edges_of_tiles(oracle, n, m, start, b, flags):
+    import torch
+
+    import paper_2604_17720_amd.binding as fb
+    x = np.stack([inputs.uniform_cube(n, 50 + i) for i in range(b)])
+    ws = fb.make_workspace(b, n, m)
+    for kn, kd in ((1, 2), (2, 3)):
+        print(n, m, start, flags, kn, kd, flush=True)
+        got, k = fb.ffps_prune(torch.from_numpy(x).cuda(), m, kn, kd, flags, start, workspace=ws, seed=11)
+        assert fb.ffps_last_status(ws) == 0
+        for i in range(b):
+            assert np.array_equal(got[i].cpu().numpy(), oracle.fps_prune(x[i], m, kn, kd, flags, start, 11 + i))
