@@ -7,6 +7,7 @@
 #include <mutex>
 
 #include "../../include/flashfps.h"
+#include "fps_block.h"
 #include "fps_launch.h"
 #include "fps_local.h"
 
@@ -161,6 +162,26 @@ int resolve_variant(int B, int N, int variant, const Device &dev) {
     return v;
 }
 
+// Which kernel AUTO takes (clouds of at most 256 points: one wave, one pick per pass).
+//
+// k_fps_block against k_fps_wgm, one cloud: 1024 points to 512 in 73 against 115 us, 4608 to 2304
+// in 400 against 638.  Beyond 4608 points it needs 12 or 16 points per lane and a cloud is
+// faster on many CUs (6144 to 1536: 364 against 340 us), unless there are many clouds, which
+// then wait for one another: 64 x 8192 to 1024 in 379 against 491 us.
+constexpr int kOneWaveMax = 256;
+constexpr int kBlockMax = 4608;
+constexpr int kBlockManyClouds = 32;
+bool takes_block(int B, int N) {
+    return N > kOneWaveMax && (N <= kBlockMax || (N <= block_capacity() && B >= kBlockManyClouds));
+}
+// k_fps_local has a dearer start (two sorts, about 140 us in all) and more rounds as long as the
+// samples are few; its rounds do not grow with the points.  Measured with 1 to 128 clouds the two
+// meet at: 8192 points to 4096 (624 against 641 us), 12,000 to 3000 (479, 468), 16,384
+// to 1400, 24,000 to 1500 (402, 402), eight clouds of 16,384 to 1700: near points x samples = 2^25.
+// The sorts grow with the points, so a hundred samples or so are too few for them in the end: a
+// million points to 34 in 320 against 281 us, three million to 64 in 692 against 560.
+bool takes_local(int N, int M) { return (long)N * M >= (1L << 25) && M >= 96 + N / 32768; }
+
 // Exact FPS of B clouds [N] into idx (row stride idx_stride).  Arguments are
 // already validated.
 int run_exact(const float *xyz, int B, int N, int M, int start, const int *start_dev, int variant,
@@ -168,12 +189,16 @@ int run_exact(const float *xyz, int B, int N, int M, int start, const int *start
               const Workspace &w, const Device &dev, hipStream_t s) {
     int v = resolve_variant(B, N, variant, dev);
     if (v < 0) return v;
+    // AUTO without a cap on the picks of a round, which the kernels that pick local maxima do not know
+    const bool any_rounds = variant_kind(variant) == FFPS_VARIANT_AUTO && ((variant >> 8) & 0xff) == 0 && M > 1;
+    if (any_rounds && takes_block(B, N)) {
+        const BlockArgs a = {xyz, N, nullptr, 0, N, M, start, start_dev, idx, idx_stride, md, md_stride, (int *)(ws + w.status)};
+        return hip_rc(launch_fps_block(a, B, s));
+    }
     if (v == FFPS_VARIANT_WG)
         return hip_rc(launch_fps_wg(xyz, B, N, M, start, start_dev, idx, idx_stride, md, md_stride,
                                     variant_picks(variant), (int *)(ws + w.status), s));
-    // AUTO without a cap on the picks of a round (which the kernel does not know): the local-maximum
-    // kernel wherever its area fits, see its file for the two compared.
-    if (v == FFPS_VARIANT_GRID && variant_kind(variant) == FFPS_VARIANT_AUTO && ((variant >> 8) & 0xff) == 0 && M > 1) {
+    if (v == FFPS_VARIANT_GRID && any_rounds && takes_local(N, M)) {
         const LocalPlan plan = plan_fps_local(B, N, dev.num_cu);
         size_t bytes = 0;
         if (plan.wg_per_cloud > 0) {

@@ -43,6 +43,7 @@
 // that are not finite) ends the kernel with the same status.
 #include "fps_exchange.h"
 #include "fps_local.h"
+#include "fps_space.h"
 
 namespace ffps {
 
@@ -72,10 +73,6 @@ struct LocalArgs {
     int spin_limit;
 };
 
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_all(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xf, 0xf, false);
-}
 // unsigned maximum over eight consecutive lanes, in each of them
 __device__ __forceinline__ uint32_t eight_max_all(uint32_t v) {
     v = umax(v, dpp_all<0xB1>(v));   // quad_perm 1,0,3,2
@@ -84,40 +81,9 @@ __device__ __forceinline__ uint32_t eight_max_all(uint32_t v) {
     return v;
 }
 
-// Workgroup barrier for LDS data alone: stores to memory stay in flight (a barrier of the
-// language would wait for them, which is the latency of the exchange once more).
-__device__ __forceinline__ void wg_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory"); }
-
-// Distances to boxes use the operations of sqdist in its order.  Rounding is monotonic, so the
-// result is never above the distance, as the kernels compute it, to any point of the box.
-struct Box { float lx, ly, lz, hx, hy, hz; };
-__device__ __forceinline__ float gap(float lo, float hi, float p) {
-    return fmaxf(fmaxf(__fsub_rn(lo, p), __fsub_rn(p, hi)), 0.f);
-}
-__device__ __forceinline__ float box_dist(const Box &b, float x, float y, float z) {
-    const float dx = gap(b.lx, b.hx, x), dy = gap(b.ly, b.hy, y), dz = gap(b.lz, b.hz, z);
-    return __fadd_rn(__fadd_rn(__fmul_rn(dx, dx), __fmul_rn(dy, dy)), __fmul_rn(dz, dz));
-}
-__device__ __forceinline__ Box no_box() {
-    const float f = __builtin_inff();
-    return Box{f, f, f, -f, -f, -f};
-}
-__device__ __forceinline__ Box box_or(const Box &a, const Box &b) {
-    return Box{fminf(a.lx, b.lx), fminf(a.ly, b.ly), fminf(a.lz, b.lz), fmaxf(a.hx, b.hx), fmaxf(a.hy, b.hy), fmaxf(a.hz, b.hz)};
-}
-__device__ __forceinline__ Box box_shfl_xor(const Box &a, int o) {
-    return Box{__shfl_xor(a.lx, o), __shfl_xor(a.ly, o), __shfl_xor(a.lz, o), __shfl_xor(a.hx, o), __shfl_xor(a.hy, o), __shfl_xor(a.hz, o)};
-}
 __device__ __forceinline__ Box box_shfl(const Box &a, int l) {
     return Box{__shfl(a.lx, l), __shfl(a.ly, l), __shfl(a.lz, l), __shfl(a.hx, l), __shfl(a.hy, l), __shfl(a.hz, l)};
 }
-__device__ __forceinline__ float box_box(const Box &a, const Box &b) {
-    const float dx = fmaxf(fmaxf(__fsub_rn(a.lx, b.hx), __fsub_rn(b.lx, a.hx)), 0.f);
-    const float dy = fmaxf(fmaxf(__fsub_rn(a.ly, b.hy), __fsub_rn(b.ly, a.hy)), 0.f);
-    const float dz = fmaxf(fmaxf(__fsub_rn(a.lz, b.hz), __fsub_rn(b.lz, a.hz)), 0.f);
-    return __fadd_rn(__fadd_rn(__fmul_rn(dx, dx), __fmul_rn(dy, dy)), __fmul_rn(dz, dz));
-}
-
 // Records of this lane's slots: 16 bytes at `base` + off and 16 at `base2` + off, read past the caches
 // that are not shared by the whole device.
 template <int NS>

@@ -13,6 +13,7 @@
 #include "fps_device.h"
 #include "fps_launch.h"
 #include "fps_local.h"
+#include "fps_space.h"
 
 namespace ffps {
 
@@ -88,38 +89,6 @@ __global__ __launch_bounds__(kOT) void k_order_box(const float *__restrict__ xyz
     if (tid < 6) boxes[((size_t)b * tiles + t) * 6 + tid] = tid < 3 ? e.lo[tid] : e.hi[tid - 3];
 }
 
-// 15-bit code of a cell of a 32^3 grid along the Hilbert curve (Skilling's transpose form).
-__device__ __forceinline__ uint32_t hilbert15(uint32_t x, uint32_t y, uint32_t z) {
-    uint32_t X[3] = {x, y, z};
-#pragma unroll
-    for (uint32_t q = 16; q > 1; q >>= 1) {
-        const uint32_t p = q - 1;
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            if (X[i] & q) {
-                X[0] ^= p;
-            } else {
-                const uint32_t t = (X[0] ^ X[i]) & p;
-                X[0] ^= t;
-                X[i] ^= t;
-            }
-        }
-    }
-    X[1] ^= X[0];
-    X[2] ^= X[1];
-    uint32_t t = 0;
-#pragma unroll
-    for (uint32_t q = 16; q > 1; q >>= 1)
-        if (X[2] & q) t ^= q - 1;
-    uint32_t r = 0;
-#pragma unroll
-    for (int k = 4; k >= 0; --k) {
-#pragma unroll
-        for (int i = 0; i < 3; ++i) r = (r << 1) | (((X[i] ^ t) >> k) & 1u);
-    }
-    return r;
-}
-
 // Codes, and how often each low digit occurs in a tile.
 __global__ __launch_bounds__(kOT) void k_order_code(const float *__restrict__ xyz, int N, int tiles, const float *__restrict__ boxes,
                                                     uint16_t *__restrict__ codes, uint32_t *__restrict__ hist) {
@@ -148,28 +117,12 @@ __global__ __launch_bounds__(kOT) void k_order_code(const float *__restrict__ xy
         uint32_t c[3];
 #pragma unroll
         for (int k = 0; k < 3; ++k) c[k] = (uint32_t)fmaxf(0.f, fminf(31.f, (p[3 * (size_t)i + k] - e.lo[k]) * scale));
-        const uint32_t code = hilbert15(c[0], c[1], c[2]);
+        const uint32_t code = hilbert_code<5>(c[0], c[1], c[2]);
         codes[(size_t)b * N + i] = (uint16_t)code;
         atomicAdd(&cnt[code & (kLowBins - 1)], 1u);
     }
     __syncthreads();
     if (tid < kLowBins) hist[((size_t)b * tiles + t) * kLowBins + tid] = cnt[tid];
-}
-
-// Lanes of the wave whose digit equals this lane's (among the lanes of `valid`).
-template <int BITS>
-__device__ __forceinline__ uint64_t same_digit(uint32_t d, uint64_t valid) {
-    uint64_t m = valid;
-#pragma unroll
-    for (int k = 0; k < BITS; ++k) {
-        const bool on = (d >> k) & 1u;
-        const uint64_t s = __builtin_amdgcn_ballot_w64(on);
-        m &= on ? s : ~s;
-    }
-    return m;
-}
-__device__ __forceinline__ int lanes_below(uint64_t m) {
-    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
 // One pass of a stable radix sort: a block moves the elements of its tile behind those of

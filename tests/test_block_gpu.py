@@ -1,0 +1,56 @@
+"""The local-maximum kernel of one workgroup behind FFPS_VARIANT_AUTO, at the edges of its
+shapes and on clouds with ties, against the oracle bit for bit (indices and squared pick
+distances are the same individually rounded numbers on both sides)."""
+import numpy as np
+import pytest
+
+from paper_2604_17720_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def _shape(b, n):
+    return np.stack([inputs.shape_cloud(n, 61000 + 5 * n + i) for i in range(b)])
+
+
+CASES = {
+    # name: (clouds, M, start); a row of 16 lanes holds 16 points per step, 32 rows make the cloud
+    "smallest": (lambda: _shape(3, 257), 257, 256),
+    "two samples": (lambda: _shape(2, 300), 2, 7),
+    "one point per lane, exactly": (lambda: _shape(2, 512), 500, 1),
+    "one point more": (lambda: _shape(2, 513), 513, 512),
+    "two per lane": (lambda: _shape(4, 1024), 512, 0),
+    "odd": (lambda: _shape(3, 1531), 777, 1530),
+    "three per lane and one": (lambda: _shape(2, 1537), 1537, 3),
+    "five per lane": (lambda: _shape(2, 2049), 1000, 3),
+    "seven per lane": (lambda: _shape(2, 3073), 900, 3072),
+    "eight per lane, exactly": (lambda: _shape(2, 4096), 4096, 5),
+    "largest of a workgroup": (lambda: _shape(2, 4608), 4608, 4607),
+    "many clouds, twelve per lane": (lambda: _shape(32, 4609), 300, 4608),
+    "many clouds, sixteen per lane": (lambda: _shape(33, 8192), 400, 8191),
+    "more clouds than CUs": (lambda: _shape(300, 700), 90, 2),
+    "planes": (lambda: np.stack([inputs.planes_and_clusters(4001, i) for i in range(5)]), 1500, 1),
+    "lattice, many equal values": (lambda: inputs.lattice_grid(16, 16, 12)[None], 2000, 0),
+    "a line": (lambda: inputs.lattice_line(1500)[None], 1500, 0),
+    "duplicates, fewer points than samples": (lambda: np.repeat(inputs.uniform_cube(300, 8), 4, axis=0)[None], 1000, 0),
+    "one place": (lambda: np.ones((2, 600, 3), np.float32), 100, 3),
+    "distances beyond fp32": (lambda: (inputs.uniform_cube(2000, 9) * 3e38).astype(np.float32)[None], 400, 0),
+    "distances below the normal numbers": (lambda: (inputs.uniform_cube(2000, 9) * 3e-20).astype(np.float32)[None], 400, 0),
+    "an outlier": (lambda: np.concatenate([inputs.uniform_cube(3000, 10), [[4e5, -3e5, 1e5]]]).astype(np.float32)[None], 900, 1),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_one_workgroup_gives_the_samples_of_the_greedy_loop(oracle, name):
+    import torch
+
+    import paper_2604_17720_amd.binding as fb
+    make, m, start = CASES[name]
+    x = np.ascontiguousarray(make(), dtype=np.float32)
+    print(name, x.shape, m, start, flush=True)
+    ws = fb.make_workspace(x.shape[0], x.shape[1], m)
+    idx, md = fb.ffps_exact(torch.from_numpy(x).cuda(), m, start, return_maxdist=True, workspace=ws)
+    assert fb.ffps_last_status(ws) == 0
+    ref, rmd = oracle.fps_exact(x, m, start, return_maxdist=True)
+    assert np.array_equal(idx.cpu().numpy(), ref.reshape(idx.shape))
+    assert np.array_equal(md.cpu().numpy().view(np.uint32), rmd.reshape(md.shape).view(np.uint32))

@@ -16,6 +16,14 @@ def _dup(n, seed):
 CASES = {
     # name: (clouds, M, start); a workgroup holds 512 points per row, 256 workgroups are the most
     "smallest": (lambda: inputs.uniform_cube(4609, 1)[None], 4609, 4608),
+    "smallest with the work for it": (lambda: inputs.uniform_cube(5793, 1)[None], 5793, 5792),
+    "just short of it": (lambda: inputs.uniform_cube(8192, 1)[None], 4095, 0),
+    "few samples, still enough": (lambda: inputs.uniform_cube(2097152, 5)[None], 160, 9),
+    "too few samples": (lambda: inputs.uniform_cube(2097152, 5)[None], 159, 9),
+    "a row of units and one point": (lambda: inputs.room(65537, 2)[None], 513, 65536),
+    "more clouds than a launch, enough work": (lambda: np.stack([inputs.planes_and_clusters(9001, i) for i in range(15)]), 3728, 3),
+    "a long line": (lambda: inputs.lattice_line(6000)[None], 6000, 0),
+    "duplicates, fewer points than many samples": (lambda: _dup(16000, 8)[None], 5000, 0),
     "one row, exactly": (lambda: inputs.room(131072, 2)[None], 3000, 7),
     "one point more": (lambda: inputs.room(131073, 2)[None], 3000, 131072),
     "three rows and one point": (lambda: inputs.uniform_cube(393217, 3)[None], 500, 0),
