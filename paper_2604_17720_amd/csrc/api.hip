@@ -168,7 +168,7 @@ int resolve_variant(int B, int N, int variant, const Device &dev) {
 // in 400 against 638.  Beyond 4608 points it needs 12 or 16 points per lane and a cloud is
 // faster on many CUs (6144 to 1536: 364 against 340 us), unless there are many clouds, which
 // then wait for one another: 64 x 8192 to 1024 in 379 against 491 us.
-constexpr int kOneWaveMax = 256;
+constexpr int kOneWaveMax = kWaveCapacity;
 constexpr int kBlockMax = 4608;
 constexpr int kBlockManyClouds = 32;
 bool takes_block(int B, int N) {
@@ -182,23 +182,46 @@ bool takes_block(int B, int N) {
 // million points to 34 in 320 against 281 us, three million to 64 in 692 against 560.
 bool takes_local(int N, int M) { return (long)N * M >= (1L << 25) && M >= 96 + N / 32768; }
 
+// Clouds that are rows of a larger array: point i of cloud b is row idx[b][i] of [B][points]
+// points.  The kernels of one workgroup read through it and write rows, which spares a stage
+// of a chain two launches (about 9 us).
+struct Rows {
+    const int32_t *idx;
+    long stride;
+    int points;
+};
+// AUTO without a cap on the picks of a round, which the kernels that pick local maxima do not know.
+bool any_rounds(int M, int variant) { return variant_kind(variant) == FFPS_VARIANT_AUTO && ((variant >> 8) & 0xff) == 0 && M > 1; }
+bool takes_wave(int N, int v) { return v == FFPS_VARIANT_WG && N <= kWaveCapacity; }
+bool takes_rows(int B, int N, int M, int variant, const Device &dev) {
+    return takes_wave(N, resolve_variant(B, N, variant, dev)) || (any_rounds(M, variant) && takes_block(B, N));
+}
+
 // Exact FPS of B clouds [N] into idx (row stride idx_stride).  Arguments are
-// already validated.
+// already validated.  `clear`: the status block is cleared first, by the kernel itself where
+// that is safe.  `rows` only where takes_rows says so.
 int run_exact(const float *xyz, int B, int N, int M, int start, const int *start_dev, int variant,
               int32_t *idx, long idx_stride, float *md, long md_stride, char *ws,
-              const Workspace &w, const Device &dev, hipStream_t s) {
+              const Workspace &w, const Device &dev, hipStream_t s, bool clear, const Rows *rows = nullptr) {
     int v = resolve_variant(B, N, variant, dev);
     if (v < 0) return v;
-    // AUTO without a cap on the picks of a round, which the kernels that pick local maxima do not know
-    const bool any_rounds = variant_kind(variant) == FFPS_VARIANT_AUTO && ((variant >> 8) & 0xff) == 0 && M > 1;
-    if (any_rounds && takes_block(B, N)) {
-        const BlockArgs a = {xyz, N, nullptr, 0, N, M, start, start_dev, idx, idx_stride, md, md_stride, (int *)(ws + w.status)};
-        return hip_rc(launch_fps_block(a, B, s));
+    const bool wave = takes_wave(N, v), block = any_rounds(M, variant) && takes_block(B, N);
+    if (wave || block) {
+        const bool own = wave || B == 1;
+        int rc = clear && !own ? clear_status(ws, w, s) : FFPS_OK;
+        if (rc) return rc;
+        const BlockArgs a = {xyz, rows ? rows->points : N, rows ? rows->idx : nullptr, rows ? rows->stride : 0, N, M, start, start_dev,
+                             idx, idx_stride, md, md_stride, (int *)(ws + w.status), clear && own};
+        return hip_rc(wave ? launch_fps_wave(a, B, s) : launch_fps_block(a, B, s));
+    }
+    if (clear) {
+        int rc = clear_status(ws, w, s);
+        if (rc) return rc;
     }
     if (v == FFPS_VARIANT_WG)
         return hip_rc(launch_fps_wg(xyz, B, N, M, start, start_dev, idx, idx_stride, md, md_stride,
                                     variant_picks(variant), (int *)(ws + w.status), s));
-    if (v == FFPS_VARIANT_GRID && any_rounds && takes_local(N, M)) {
+    if (v == FFPS_VARIANT_GRID && any_rounds(M, variant) && takes_local(N, M)) {
         const LocalPlan plan = plan_fps_local(B, N, dev.num_cu);
         size_t bytes = 0;
         if (plan.wg_per_cloud > 0) {
@@ -266,7 +289,7 @@ int run_prune(const float *xyz, int B, int N, int M, int start, int keep_num, in
             int *spos = (int *)(ws + w.spos);
             rc = hip_rc(launch_perm_candidates(xyz, B, N, Nc, start, seed, bitmap, cand, cxyz, spos, s));
             if (rc) return rc;
-            rc = run_exact(cxyz, B, Nc, k, 0, spos, variant, loc, k, nullptr, 0, ws, w, dev, s);
+            rc = run_exact(cxyz, B, Nc, k, 0, spos, variant, loc, k, nullptr, 0, ws, w, dev, s, true);
             if (rc) return rc;
             rc = hip_rc(launch_compose(cand, Nc, loc, k, B, k, idx, idx_stride, s));
         } else {
@@ -275,13 +298,13 @@ int run_prune(const float *xyz, int B, int N, int M, int start, int keep_num, in
             long j0 = (((long)N - start) * Nc + N - 1) / N;  // where the strided list wraps
             if (j0 > Nc) j0 = Nc;
             int spos = (int)((Nc - j0) % Nc);  // position of start_idx in the sorted list
-            rc = run_exact(cxyz, B, Nc, k, spos, nullptr, variant, loc, k, nullptr, 0, ws, w, dev, s);
+            rc = run_exact(cxyz, B, Nc, k, spos, nullptr, variant, loc, k, nullptr, 0, ws, w, dev, s, true);
             if (rc) return rc;
             rc = hip_rc(launch_map_candidates(loc, k, B, N, Nc, start, k, idx, idx_stride, s));
         }
         if (rc) return rc;
     } else {
-        rc = run_exact(xyz, B, N, k, start, nullptr, variant, idx, idx_stride, nullptr, 0, ws, w, dev, s);
+        rc = run_exact(xyz, B, N, k, start, nullptr, variant, idx, idx_stride, nullptr, 0, ws, w, dev, s, true);
         if (rc) return rc;
     }
     if (perm) return hip_rc(launch_fill_perm(B, N, k, R, seed, idx, idx_stride, bitmap, (int *)(ws + w.cand), s));  // the list is done with
@@ -341,9 +364,8 @@ int ffps_exact(const float *d_xyz, int B, int N, int M, int start_idx, int varia
     if (dev.ok) return dev.ok;
     if ((rc = resolve_variant(B, N, variant, dev)) < 0) return rc;
     hipStream_t s = (hipStream_t)stream;
-    if ((rc = clear_status((char *)d_ws, w, s))) return rc;
     return run_exact(d_xyz, B, N, M, start_idx, nullptr, variant, d_idx, M, d_maxdist, M,
-                     (char *)d_ws, w, dev, s);
+                     (char *)d_ws, w, dev, s, true);
 }
 
 int ffps_exact_noalloc(const float *d_xyz, int B, int N, int M, int start_idx, int variant,
@@ -366,8 +388,7 @@ int ffps_exact_noalloc(const float *d_xyz, int B, int N, int M, int start_idx, i
     w.local = kAlign; w.local_bytes = kScratchBytes - kAlign;
     w.cxyz = w.loc = w.bitmap = w.mind = w.cand = w.spos = none;  // not part of this path
     hipStream_t s = (hipStream_t)stream;
-    if ((rc = clear_status(ws, w, s))) return rc;
-    rc = run_exact(d_xyz, B, N, M, start_idx, nullptr, variant, d_idx, M, d_maxdist, M, ws, w, dev, s);
+    rc = run_exact(d_xyz, B, N, M, start_idx, nullptr, variant, d_idx, M, d_maxdist, M, ws, w, dev, s, true);
     if (rc) return rc;
     if (d_status)
         rc = hip_rc(launch_copy_prefix((const int32_t *)(ws + w.status), 2, 1, 2, d_status, 2, s));
@@ -389,7 +410,6 @@ int ffps_prune(const float *d_xyz, int B, int N, int M, int start_idx, int keep_
     if (dev.ok) return dev.ok;
     if ((rc = resolve_variant(B, Nc, variant, dev)) < 0) return rc;
     hipStream_t s = (hipStream_t)stream;
-    if ((rc = clear_status((char *)d_ws, w, s))) return rc;
     if (k_out_host) *k_out_host = k;
     return run_prune(d_xyz, B, N, M, start_idx, keep_num, keep_den, flags, seed, variant, d_idx, M,
                      (char *)d_ws, w, dev, s);
@@ -418,30 +438,44 @@ int ffps_cached_stages(const float *d_xyz, int B, int N, int L, const int *M_sta
     if ((rc = resolve_variant(B, Nc, variant, dev)) < 0) return rc;
     hipStream_t s = (hipStream_t)stream;
     char *ws = (char *)d_ws;
-    if ((rc = clear_status(ws, w, s))) return rc;
 
     rc = run_prune(d_xyz, B, N, M_stages[0], start_idx, keep_num, keep_den, flags, seed, variant,
                    d_idx, S, ws, w, dev, s);
     if (rc) return rc;
     long off = M_stages[0];
+    if (mode == FFPS_MODE_CACHED) {
+        for (int l = 1; l < L;) {
+            long at[kMaxPrefixes];
+            int n = 0;
+            for (; n < kMaxPrefixes && l + n < L; ++n) {
+                at[n] = off;
+                off += M_stages[l + n];
+            }
+            rc = hip_rc(launch_copy_prefixes(d_idx, S, B, n, at, M_stages + l, s));
+            if (rc) return rc;
+            l += n;
+        }
+        return FFPS_OK;
+    }
     const int32_t *prev = d_idx;
     for (int l = 1; l < L; ++l) {
         int32_t *cur = d_idx + off;
-        if (mode == FFPS_MODE_CACHED) {
-            rc = hip_rc(launch_copy_prefix(d_idx, S, B, M_stages[l], cur, S, s));
+        const int n = M_stages[l - 1], m = M_stages[l];
+        if (takes_rows(B, n, m, variant, dev)) {
+            const Rows rows = {prev, S, N};
+            rc = run_exact(d_xyz, B, n, m, 0, nullptr, variant, cur, S, nullptr, 0, ws, w, dev, s, false, &rows);
         } else {
             float *pxyz = (float *)(ws + w.cxyz);
             int32_t *loc = (int32_t *)(ws + w.loc);
-            rc = hip_rc(launch_gather_points(d_xyz, B, N, prev, S, M_stages[l - 1], pxyz, s));
+            rc = hip_rc(launch_gather_points(d_xyz, B, N, prev, S, n, pxyz, s));
             if (rc) return rc;
-            rc = run_exact(pxyz, B, M_stages[l - 1], M_stages[l], 0, nullptr, variant, loc,
-                           M_stages[l], nullptr, 0, ws, w, dev, s);
+            rc = run_exact(pxyz, B, n, m, 0, nullptr, variant, loc, m, nullptr, 0, ws, w, dev, s, false);
             if (rc) return rc;
-            rc = hip_rc(launch_compose(prev, S, loc, M_stages[l], B, M_stages[l], cur, S, s));
+            rc = hip_rc(launch_compose(prev, S, loc, m, B, m, cur, S, s));
         }
         if (rc) return rc;
         prev = cur;
-        off += M_stages[l];
+        off += m;
     }
     return FFPS_OK;
 }

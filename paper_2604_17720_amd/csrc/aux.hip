@@ -178,6 +178,19 @@ __global__ void k_copy_prefix(const int32_t *__restrict__ src, long src_stride, 
         out[b * out_stride + j] = src[b * src_stride + j];
 }
 
+// The prefixes of several stages, behind one another in the output: a launch costs more than
+// what it copies (three stages of a room: 14 us in three launches).
+struct Prefixes {
+    int n;
+    long at[kMaxPrefixes];  // first word of the stage in a cloud's row
+    int len[kMaxPrefixes];
+};
+__global__ void k_copy_prefixes(int32_t *__restrict__ idx, long stride, Prefixes p) {
+    int32_t *row = idx + blockIdx.y * stride;
+    for (int l = 0; l < p.n; ++l)
+        for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < p.len[l]; j += gridDim.x * blockDim.x) row[p.at[l] + j] = row[j];
+}
+
 // ---- seeded random select / fill --------------------------------------------
 // Seeded bijection of [0, N): a 4-round Feistel network over 2h bits,
 // 2^(2h) >= N, with a 32-bit integer mixer as round function, walked until the
@@ -490,6 +503,15 @@ hipError_t launch_copy_prefix(const int32_t *src, long src_stride, int B, int S,
                               long out_stride, hipStream_t s) {
     hipLaunchKernelGGL(k_copy_prefix, dim3(blocks_for(S), B), dim3(kT), 0, s, src, src_stride, S,
                        out, out_stride);
+    return hipGetLastError();
+}
+
+hipError_t launch_copy_prefixes(int32_t *idx, long stride, int B, int n, const long *at, const int *len, hipStream_t s) {
+    if (n < 1 || n > kMaxPrefixes) return hipErrorInvalidValue;
+    Prefixes p;
+    p.n = n;
+    for (int k = 0; k < n; ++k) { p.at[k] = at[k]; p.len[k] = len[k]; }
+    hipLaunchKernelGGL(k_copy_prefixes, dim3(blocks_for(p.len[0]), B), dim3(kT), 0, s, idx, stride, p);
     return hipGetLastError();
 }
 

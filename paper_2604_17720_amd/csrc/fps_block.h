@@ -17,8 +17,14 @@ struct BlockArgs {
     float *md;
     long md_stride;
     int *status;          // as for the other kernels
+    bool clear;           // the kernel clears the status block itself
 };
+constexpr int kStatusWords = 64;
+constexpr int kWaveCapacity = 256;  // largest N of one wave
 
+// fps_wg.hip: one wave per cloud, one pick per pass; N <= kWaveCapacity
+hipError_t launch_fps_wave(const BlockArgs &a, int B, hipStream_t s);
+// fps_block.hip.  `clear` only with a single cloud: several write their rounds into the block.
 int block_capacity();  // largest N; the smallest is 32
 hipError_t launch_fps_block(const BlockArgs &a, int B, hipStream_t s);
 

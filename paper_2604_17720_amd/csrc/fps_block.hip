@@ -78,6 +78,8 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_fps_block(BlockArgs a) {
     const int32_t *sel = a.sel ? a.sel + cloud * a.sel_stride : nullptr;
     const int start = a.start_dev ? a.start_dev[cloud] : a.start;
 
+    if (a.clear && tid < kStatusWords) a.status[tid] = 0;
+
     // ---- the points along the curve ----
     const int w0 = wave * kWave * P + lane;  // this lane's points in the caller's order: w0 + 64 r
     uint32_t code[P];

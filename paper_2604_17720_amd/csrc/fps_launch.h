@@ -96,5 +96,8 @@ hipError_t launch_compose(const int32_t *prev, long prev_stride, const int32_t *
 // out[b][j] = src[b][j] for j < S
 hipError_t launch_copy_prefix(const int32_t *src, long src_stride, int B, int S, int32_t *out,
                               long out_stride, hipStream_t s);
+// idx[b][at[l] + j] = idx[b][j] for j < len[l], l < n <= kMaxPrefixes; lengths do not grow
+constexpr int kMaxPrefixes = 16;
+hipError_t launch_copy_prefixes(int32_t *idx, long stride, int B, int n, const long *at, const int *len, hipStream_t s);
 
 }  // namespace ffps

@@ -8,6 +8,7 @@
 // per-lane argmax, a DPP max across the wave, one LDS exchange across waves
 // (double-buffered, so a single s_barrier per pick).  Nothing is re-read from
 // HBM after the initial load.
+#include "fps_block.h"
 #include "fps_exchange.h"
 
 namespace ffps {
@@ -26,7 +27,8 @@ __global__ __launch_bounds__(NT) void k_fps_wg(const float *__restrict__ xyz_all
                                                long idx_stride, float *__restrict__ md_all,
                                                long md_stride) {
     constexpr int NW = NT / kWave;
-    __shared__ WaveSlot slots[2][NW > 1 ? NW : 1];
+    static_assert(NW > 1, "a single wave: k_fps_wave");
+    __shared__ WaveSlot slots[2][NW];
 
     const int b = blockIdx.x;
     const int start = start_dev ? start_dev[b] : start_in;
@@ -83,35 +85,104 @@ __global__ __launch_bounds__(NT) void k_fps_wg(const float *__restrict__ xyz_all
         pick_xyz<P>(x, y, z, wj, wl, wx, wy, wz);
         int widx = (wave * kWave + wl) * P + wj;
 
-        if constexpr (NW == 1) {
-            lx = wx; ly = wy; lz = wz;
-            if (tid == 0) {
-                idx_out[k] = widx;
-                if (md_out) md_out[k] = u2f(wbits);
-            }
-        } else {
-            WaveSlot *buf = slots[k & 1];
-            if (lane == 0) {
-                buf[wave].dbits = wbits;
-                buf[wave].idx = widx;
-                buf[wave].x = wx;
-                buf[wave].y = wy;
-                buf[wave].z = wz;
-            }
-            __syncthreads();
-            // every wave reduces the NW slots on its own: lowest wave wins a tie
-            uint32_t sb = lane < NW ? buf[lane].dbits : 0u;
-            uint32_t gb = (uint32_t)__builtin_amdgcn_readlane((int)row16_max_u32(sb), 15);
-            int ww = first_lane(lane < NW && sb == gb);
-            lx = buf[ww].x;
-            ly = buf[ww].y;
-            lz = buf[ww].z;
-            if (tid == 0) {
-                idx_out[k] = buf[ww].idx;
-                if (md_out) md_out[k] = u2f(gb);
-            }
+        WaveSlot *buf = slots[k & 1];
+        if (lane == 0) {
+            buf[wave].dbits = wbits;
+            buf[wave].idx = widx;
+            buf[wave].x = wx;
+            buf[wave].y = wy;
+            buf[wave].z = wz;
+        }
+        __syncthreads();
+        // every wave reduces the NW slots on its own: lowest wave wins a tie
+        uint32_t sb = lane < NW ? buf[lane].dbits : 0u;
+        uint32_t gb = (uint32_t)__builtin_amdgcn_readlane((int)row16_max_u32(sb), 15);
+        int ww = first_lane(lane < NW && sb == gb);
+        lx = buf[ww].x;
+        ly = buf[ww].y;
+        lz = buf[ww].z;
+        if (tid == 0) {
+            idx_out[k] = buf[ww].idx;
+            if (md_out) md_out[k] = u2f(gb);
         }
     }
+}
+
+// k_fps_wave: clouds that one wave holds, P points per lane, in the order of the lanes.  A pick
+// is one serial chain (distances, maximum over the wave, coordinates of the winner), and
+// the time is its length: the best of a lane carries its coordinates through the comparison, so that
+// nothing has to be chosen by a branch after the maximum, and samples are kept in a register
+// and written 64 at a time.
+template <int P>
+__global__ __launch_bounds__(kWave) void k_fps_wave(BlockArgs a) {
+    const int b = blockIdx.x, lane = threadIdx.x, N = a.N;
+    if (a.clear && b == 0) a.status[lane] = 0;
+    static_assert(kStatusWords == kWave, "a word per lane");
+    const float *xyz = a.xyz + (size_t)b * a.cloud_points * 3;
+    const int32_t *sel = a.sel ? a.sel + b * a.sel_stride : nullptr;
+    const int start = a.start_dev ? a.start_dev[b] : a.start;
+    int32_t *idx = a.idx + b * a.idx_stride;
+    float *md = a.md ? a.md + b * a.md_stride : nullptr;
+    float x[P], y[P], z[P], m[P];
+    int row[P];  // what is written for a point
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+        const int i = lane * P + j;
+        const bool ok = i < N;
+        row[j] = ok && sel ? sel[i] : i;
+        const float *q = xyz + 3 * (size_t)(ok ? row[j] : 0);
+        x[j] = q[0]; y[j] = q[1]; z[j] = q[2];
+        // padding holds distance 0 and the highest indices: it never wins
+        m[j] = ok ? __builtin_inff() : 0.f;
+    }
+    int keep_i = sel ? sel[start] : start;
+    float keep_d = __builtin_inff();
+    const float *q = xyz + 3 * (size_t)keep_i;
+    float lx = q[0], ly = q[1], lz = q[2];
+    for (int k = 1; k < a.M; ++k) {
+        if ((k & 63) == 0) {
+            idx[k - kWave + lane] = keep_i;
+            if (md) md[k - kWave + lane] = keep_d;
+        }
+        // best of the lane, strictly greater so that the earlier one keeps a tie
+        float v[P], cx[P], cy[P], cz[P];
+        int ci[P];
+#pragma unroll
+        for (int j = 0; j < P; ++j) {
+            m[j] = min_dist(m[j], sqdist(x[j], y[j], z[j], lx, ly, lz));
+            v[j] = m[j]; cx[j] = x[j]; cy[j] = y[j]; cz[j] = z[j]; ci[j] = row[j];
+        }
+#pragma unroll
+        for (int w = 1; w < P; w <<= 1) {
+#pragma unroll
+            for (int j = 0; j + w < P; j += 2 * w) {
+                const bool g = v[j + w] > v[j];
+                v[j] = g ? v[j + w] : v[j];
+                cx[j] = g ? cx[j + w] : cx[j]; cy[j] = g ? cy[j + w] : cy[j]; cz[j] = g ? cz[j + w] : cz[j];
+                ci[j] = g ? ci[j + w] : ci[j];
+            }
+        }
+        const uint32_t top = wave_max_u32(f2u(v[0]));
+        const int wl = first_lane(f2u(v[0]) == top);
+        lx = readlane_f(cx[0], wl); ly = readlane_f(cy[0], wl); lz = readlane_f(cz[0], wl);
+        const int wi = readlane_i(ci[0], wl);
+        const bool here = lane == (k & 63);
+        keep_i = here ? wi : keep_i;
+        keep_d = here ? u2f(top) : keep_d;
+    }
+    const int k = (a.M - 1) / kWave * kWave + lane;
+    if (k < a.M) {
+        idx[k] = keep_i;
+        if (md) md[k] = keep_d;
+    }
+}
+
+hipError_t launch_fps_wave(const BlockArgs &a, int B, hipStream_t s) {
+    if (a.N <= kWave) k_fps_wave<1><<<dim3(B), dim3(kWave), 0, s>>>(a);
+    else if (a.N <= 2 * kWave) k_fps_wave<2><<<dim3(B), dim3(kWave), 0, s>>>(a);
+    else if (a.N <= kWaveCapacity) k_fps_wave<4><<<dim3(B), dim3(kWave), 0, s>>>(a);
+    else return hipErrorInvalidValue;
+    return hipGetLastError();
 }
 
 template <int NT, int P>
@@ -339,7 +410,7 @@ int wg_capacity() { return 1024 * 24; }
 int wgm_capacity() { return 4608; }  // <= 7 * 64 * 11
 
 int wg_units(int N) {
-    if (N <= 64 * 4 || N > wgm_capacity()) return 0;
+    if (N <= kWaveCapacity || N > wgm_capacity()) return 0;
     return 7 * kWave;  // one reporting unit per worker lane
 }
 
@@ -352,7 +423,10 @@ hipError_t launch_fps_wg(const float *xyz, int B, int N, int M, int start, const
 #define FFPS_WG_CASE(NT, P) \
     if (N <= (NT) * (P))    \
         return launch_wg_t<NT, P>(xyz, B, N, M, start, start_dev, idx, idx_stride, md, md_stride, s);
-    FFPS_WG_CASE(64, 4)
+    if (N <= kWaveCapacity) {
+        const BlockArgs a = {xyz, N, nullptr, 0, N, M, start, start_dev, idx, idx_stride, md, md_stride, status, false};
+        return launch_fps_wave(a, B, s);
+    }
     if (N <= wgm_capacity()) {
         WgmArgs a;
         a.xyz = xyz; a.N = N; a.M = M; a.start = start; a.start_dev = start_dev;

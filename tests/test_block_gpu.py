@@ -54,3 +54,37 @@ def test_one_workgroup_gives_the_samples_of_the_greedy_loop(oracle, name):
     ref, rmd = oracle.fps_exact(x, m, start, return_maxdist=True)
     assert np.array_equal(idx.cpu().numpy(), ref.reshape(idx.shape))
     assert np.array_equal(md.cpu().numpy().view(np.uint32), rmd.reshape(md.shape).view(np.uint32))
+
+
+@pytest.mark.parametrize("n,m", [(1, 1), (2, 2), (63, 63), (64, 64), (65, 65), (127, 64), (128, 128), (129, 65), (200, 50), (256, 256)])
+def test_one_wave_gives_the_samples_of_the_greedy_loop(oracle, n, m):
+    import torch
+
+    import paper_2604_17720_amd.binding as fb
+    x = np.round(_shape(3, max(n, 2))[:, :n] * 8) / 8 if n % 2 else _shape(3, n)  # odd sizes: many equal values
+    x = np.ascontiguousarray(x, dtype=np.float32)
+    ws = fb.make_workspace(3, n, m)
+    ws.fill_(0x5A)  # whatever an earlier call left
+    idx, md = fb.ffps_exact(torch.from_numpy(x).cuda(), m, n - 1, return_maxdist=True, workspace=ws)
+    assert fb.ffps_last_status(ws) == 0 and fb.ffps_last_rounds(ws) == 0
+    ref, rmd = oracle.fps_exact(x, m, n - 1, return_maxdist=True)
+    assert np.array_equal(idx.cpu().numpy(), ref.reshape(idx.shape))
+    assert np.array_equal(md.cpu().numpy().view(np.uint32), rmd.reshape(md.shape).view(np.uint32))
+
+
+@pytest.mark.parametrize("b", [1, 3])
+@pytest.mark.parametrize("n,stages", [(9000, (4608, 1024, 257, 256, 64, 5)), (300, (150, 150, 20, 1)), (20, (20, 7, 7, 2) + (1,) * 20)])
+def test_stages_read_through_the_samples_of_the_one_before(oracle, b, n, stages):
+    import torch
+
+    import paper_2604_17720_amd.binding as fb
+    x = np.ascontiguousarray(_shape(b, n), dtype=np.float32)
+    for mode in (fb.FFPS_MODE_CHAIN, fb.FFPS_MODE_CACHED):
+        for num, den, flags in ((1, 1, 0), (1, 2, fb.FFPS_FLAG_CP | fb.FFPS_FLAG_IP)):
+            ws = fb.make_workspace(b, n, stages[0])
+            ws.fill_(0x5A)
+            print(b, n, stages, mode, num, den, flush=True)
+            outs = fb.ffps_cached_stages(torch.from_numpy(x).cuda(), stages, mode, num, den, flags, n // 3, workspace=ws)
+            assert fb.ffps_last_status(ws) == 0
+            got = np.concatenate([o.cpu().numpy() for o in outs], axis=1)
+            assert np.array_equal(got, oracle.fps_stages(x, stages, mode, num, den, flags, n // 3))
