@@ -4,9 +4,11 @@
 // Points: 15-bit Hilbert codes of a 32^3 grid over the cloud (finer grids make no fewer rounds:
 // a unit of 98 points of the 200,000-point room covers about two cells), a radix sort of 8 and 7
 // bits.  Both passes are stable, so the order, and with it every round of the kernel, is the
-// same in each run.  Four launches: boxes of tiles; codes and counts of the low digit; low digit
-// (which also counts the high one, tile by tile of the result); high digit with the gather of
-// the coordinates.  A block adds up the counts of all tiles itself instead of a scan of its own.
+// same in each run.  Five launches: boxes of tiles; codes and counts of the low digit; low digit;
+// counts of the high digit in tiles of that order; high digit with the gather of the coordinates.
+// A block adds up the counts of all tiles itself instead of a scan of its own.  (The high digits
+// counted by the pass that moves the low ones, with an atomic in memory per point, took 256 us of
+// five million points; the pass and the counts by themselves take 56 and 19 us.)
 //
 // Picks: k_fps_local counts them in 8192 bins by value (32 bins to a factor of two), so a pick's
 // bin is known at once; bins are sorted in LDS.
@@ -32,7 +34,6 @@ __device__ __forceinline__ void tile_range(int N, int tiles, int t, int &lo, int
     lo = min(N, t * per);
     hi = min(N, lo + per);
 }
-__device__ __forceinline__ int tile_points(int N, int tiles) { return ((N + tiles - 1) / tiles + kOT - 1) / kOT * kOT; }
 
 struct Ext { float lo[3], hi[3]; };
 
@@ -64,13 +65,11 @@ __device__ __forceinline__ void block_box(Ext &e, float (*sh)[6], int tid) {
 
 // Box of each tile; clears the words the later kernels count and poll in.
 __global__ __launch_bounds__(kOT) void k_order_box(const float *__restrict__ xyz, int N, int tiles, float *__restrict__ boxes,
-                                                   uint32_t *__restrict__ zero, long zero_words, uint32_t *__restrict__ zero2,
-                                                   long zero2_words) {
+                                                   uint32_t *__restrict__ zero, long zero_words) {
     __shared__ float sh[kOW][6];
     const int tid = threadIdx.x, t = blockIdx.x, b = blockIdx.y;
     const long nthr = (long)gridDim.x * gridDim.y * kOT, me = ((long)b * gridDim.x + t) * kOT + tid;
     for (long i = me; i < zero_words; i += nthr) zero[i] = 0u;
-    for (long i = me; i < zero2_words; i += nthr) zero2[i] = 0u;
     int lo, hi;
     tile_range(N, tiles, t, lo, hi);
     const float *p = xyz + (size_t)b * N * 3;
@@ -181,38 +180,49 @@ __device__ __forceinline__ void stable_pass(const uint32_t *__restrict__ hist, i
     }
 }
 
+// An element on its way: index below, high digit above.
+constexpr int kIndexBits = 25;
+
 __global__ __launch_bounds__(kOT) void k_order_low(int N, int tiles, const uint16_t *__restrict__ codes, const uint32_t *__restrict__ hist,
-                                                   u32x2 *__restrict__ pairs, uint32_t *__restrict__ hist2) {
+                                                   uint32_t *__restrict__ elems) {
     __shared__ uint32_t cnt[kOW][kLowBins], part[kLowBins];
     const int tid = threadIdx.x, t = blockIdx.x, b = blockIdx.y;
     int lo, hi;
     tile_range(N, tiles, t, lo, hi);
-    const int per = tile_points(N, tiles);
     const uint16_t *c = codes + (size_t)b * N;
-    u32x2 *out = pairs + (size_t)b * N;
-    uint32_t *h2 = hist2 + (size_t)b * tiles * kHighBins;
+    uint32_t *out = elems + (size_t)b * N;
     stable_pass<8>(hist + (size_t)b * tiles * kLowBins, tiles, t, lo, hi, tid, cnt, part,
                    [&](int i) { return (uint32_t)c[i] & (kLowBins - 1); },
-                   [&](int i, uint32_t pos) {
-                       const uint32_t h = (uint32_t)c[i] >> 8;
-                       out[pos] = u32x2{(uint32_t)i, h};
-                       atomicAdd(&h2[(pos / (uint32_t)per) * kHighBins + h], 1u);
-                   });
+                   [&](int i, uint32_t pos) { out[pos] = ((uint32_t)c[i] >> 8) << kIndexBits | (uint32_t)i; });
 }
 
-__global__ __launch_bounds__(kOT) void k_order_high(const float *__restrict__ xyz, int N, int tiles, const u32x2 *__restrict__ pairs,
+// How often each high digit occurs in a tile.
+__global__ __launch_bounds__(kOT) void k_order_count(int N, int tiles, const uint32_t *__restrict__ elems, uint32_t *__restrict__ hist2) {
+    __shared__ uint32_t cnt[kHighBins];
+    const int tid = threadIdx.x, t = blockIdx.x, b = blockIdx.y;
+    if (tid < kHighBins) cnt[tid] = 0;
+    __syncthreads();
+    int lo, hi;
+    tile_range(N, tiles, t, lo, hi);
+    const uint32_t *in = elems + (size_t)b * N;
+    for (int i = lo + tid; i < hi; i += kOT) atomicAdd(&cnt[in[i] >> kIndexBits], 1u);
+    __syncthreads();
+    if (tid < kHighBins) hist2[((size_t)b * tiles + t) * kHighBins + tid] = cnt[tid];
+}
+
+__global__ __launch_bounds__(kOT) void k_order_high(const float *__restrict__ xyz, int N, int tiles, const uint32_t *__restrict__ elems,
                                                     const uint32_t *__restrict__ hist2, u32x4 *__restrict__ pts) {
     __shared__ uint32_t cnt[kOW][kHighBins], part[kHighBins];
     const int tid = threadIdx.x, t = blockIdx.x, b = blockIdx.y;
     int lo, hi;
     tile_range(N, tiles, t, lo, hi);
-    const u32x2 *in = pairs + (size_t)b * N;
+    const uint32_t *in = elems + (size_t)b * N;
     const float *p = xyz + (size_t)b * N * 3;
     u32x4 *out = pts + (size_t)b * N;
     stable_pass<7>(hist2 + (size_t)b * tiles * kHighBins, tiles, t, lo, hi, tid, cnt, part,
-                   [&](int i) { return in[i].y; },
+                   [&](int i) { return in[i] >> kIndexBits; },
                    [&](int i, uint32_t pos) {
-                       const uint32_t k = in[i].x;
+                       const uint32_t k = in[i] & ((1u << kIndexBits) - 1u);
                        out[pos] = u32x4{f2u(p[3 * (size_t)k]), f2u(p[3 * (size_t)k + 1]), f2u(p[3 * (size_t)k + 2]), k};
                    });
 }
@@ -423,14 +433,15 @@ int order_tiles(int N) {
 }
 
 hipError_t launch_order(const float *xyz, int B, int N, const LocalBuffers &l, hipStream_t s) {
+    if (N > 1 << kIndexBits) return hipErrorInvalidValue;
     const int tiles = order_tiles(N);
     const dim3 grid(tiles, B);
-    u32x2 *pairs = (u32x2 *)l.picks;  // the picks come later
-    k_order_box<<<grid, dim3(kOT), 0, s>>>(xyz, N, tiles, l.boxes, (uint32_t *)l.zeroed, (long)(l.zero_bytes / 4), l.hist2,
-                                           (long)B * tiles * kHighBins);
+    uint32_t *elems = (uint32_t *)l.picks;  // the picks come later
+    k_order_box<<<grid, dim3(kOT), 0, s>>>(xyz, N, tiles, l.boxes, (uint32_t *)l.zeroed, (long)(l.zero_bytes / 4));
     k_order_code<<<grid, dim3(kOT), 0, s>>>(xyz, N, tiles, l.boxes, l.codes, l.hist1);
-    k_order_low<<<grid, dim3(kOT), 0, s>>>(N, tiles, l.codes, l.hist1, pairs, l.hist2);
-    k_order_high<<<grid, dim3(kOT), 0, s>>>(xyz, N, tiles, pairs, l.hist2, (u32x4 *)l.pts);
+    k_order_low<<<grid, dim3(kOT), 0, s>>>(N, tiles, l.codes, l.hist1, elems);
+    k_order_count<<<grid, dim3(kOT), 0, s>>>(N, tiles, elems, l.hist2);
+    k_order_high<<<grid, dim3(kOT), 0, s>>>(xyz, N, tiles, elems, l.hist2, (u32x4 *)l.pts);
     return hipGetLastError();
 }
 
