@@ -37,7 +37,7 @@ Workspace carve(int B, int N, int M) {
     w.cand = o;     o += align_up((size_t)B * N * sizeof(int32_t));
     w.spos = o;     o += align_up((size_t)B * sizeof(int));
     // the local-maximum kernel's area comes last; clouds of one workgroup do not need it
-    w.local = o;    w.local_bytes = N > wgm_capacity() ? local_workspace_bound(B, N) : 0;
+    w.local = o;    w.local_bytes = N > wgm_capacity() && N <= local_capacity() ? local_workspace_bound(B, N) : 0;
     o += align_up(w.local_bytes);
     w.total = o;
     return w;
@@ -179,8 +179,12 @@ bool takes_block(int B, int N) {
 // meet at: 8192 points to 4096 (624 against 641 us), 12,000 to 3000 (479, 468), 16,384
 // to 1400, 24,000 to 1500 (402, 402), eight clouds of 16,384 to 1700: near points x samples = 2^25.
 // The sorts grow with the points, so a hundred samples or so are too few for them in the end: a
-// million points to 34 in 320 against 281 us, three million to 64 in 692 against 560.
-bool takes_local(int N, int M) { return (long)N * M >= (1L << 25) && M >= 96 + N / 32768; }
+// million points to 34 in 320 against 281 us.  Beyond the registers' 3.1 million points, where
+// k_fps_grid gives way to k_fps_stream, the two meet near 80 samples (four million uniform points
+// to 64: 655 against 618 us, to 128: 747, 846; a room of five million to 64: 790, 1042; to 1024: 1240, 4711).
+bool takes_local(int N, int M, int v) {
+    return (long)N * M >= (1L << 25) && M >= (v == FFPS_VARIANT_STREAM ? 80 : 96 + N / 65536);
+}
 
 // Clouds that are rows of a larger array: point i of cloud b is row idx[b][i] of [B][points]
 // points.  The kernels of one workgroup read through it and write rows, which spares a stage
@@ -221,7 +225,7 @@ int run_exact(const float *xyz, int B, int N, int M, int start, const int *start
     if (v == FFPS_VARIANT_WG)
         return hip_rc(launch_fps_wg(xyz, B, N, M, start, start_dev, idx, idx_stride, md, md_stride,
                                     variant_picks(variant), (int *)(ws + w.status), s));
-    if (v == FFPS_VARIANT_GRID && any_rounds(M, variant) && takes_local(N, M)) {
+    if ((v == FFPS_VARIANT_GRID || v == FFPS_VARIANT_STREAM) && any_rounds(M, variant) && takes_local(N, M, v)) {
         const LocalPlan plan = plan_fps_local(B, N, dev.num_cu);
         size_t bytes = 0;
         if (plan.wg_per_cloud > 0) {

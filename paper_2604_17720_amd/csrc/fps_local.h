@@ -41,6 +41,7 @@ struct LocalBuffers {  // device memory of one call
 int order_tiles(int N);
 // Bytes of a call's device memory, and its parts in an area of that size (256-byte aligned).
 LocalBuffers carve_local(char *base, int B, int N, const LocalPlan &p, size_t *bytes);
+int local_capacity();  // largest N on any device
 size_t local_workspace_bound(int B, int N);  // over all devices
 
 hipError_t launch_order(const float *xyz, int B, int N, const LocalBuffers &l, hipStream_t s);

@@ -19,8 +19,10 @@
 // What is left is the latency of a round, which is what everything below is about.
 //
 //   - Points are sorted along a space-filling curve first (spatial.hip); a UNIT, one
-//     wave, holds a stretch of it in registers (up to 24 rows of 64 points), eight units
-//     make a workgroup.
+//     wave, holds a stretch of it in registers (up to 40 rows of 64 points), eight units
+//     make a workgroup.  From 24 rows on some values of the slots below are spilled (40 rows: 244
+//     registers); with the boxes in LDS, records gathered two slots at a time and the rows
+//     kept in their order (few_rows) a round of five million points takes 10 us, 21 without.
 //   - Per round a unit publishes its best point (value, index, coordinates), the value of
 //     its second best, and whether the candidate it published the round before was picked:
 //     32 bytes.  Every lane reads the records of up to four units, eight lanes for a
@@ -37,7 +39,8 @@
 //     beyond the samples (10 to 15 % of them) are left out by the final sort (spatial.hip).
 //
 // Measured, exact FPS of a room of 200,000 points to 50,000 samples, sorts included:
-// 0.87 ms against 4.44 ms with k_fps_grid; 45,678 points to 5,001: 0.45 against 0.84 ms.
+// 0.84 ms against 4.44 ms with k_fps_grid; 45,678 points to 5,001: 0.43 against 0.84 ms;
+// five million to 1024: 1.24 ms against 4.71 ms with k_fps_stream.
 //
 // Every wait is bounded as in fps_exchange.h, and a point that is picked twice (coordinates
 // that are not finite) ends the kernel with the same status.
@@ -107,6 +110,13 @@ __device__ __forceinline__ void load_pairs(const char *base, const char *base2, 
     }
 }
 
+// Where a lane has many points, every few rows the compiler may not mix with those before them: its
+// own order would hold the results of dozens of rows at once and spill the points.
+template <int P>
+__device__ __forceinline__ void few_rows(int j) {
+    if (P > 16 && (j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+}
+
 // the best point of a unit and the value that follows it, the same in all lanes of the unit
 struct Best {
     float v, sec, x, y, z;
@@ -166,6 +176,7 @@ __device__ __forceinline__ Best unit_best(const float (&x)[P], const float (&y)[
     for (int j = 1; j < P; ++j) {
         t2 = __builtin_amdgcn_fmed3f(t1, t2, m[j]);
         t1 = fmaxf(t1, m[j]);
+        few_rows<P>(j);
     }
     const uint32_t T1 = wave_max_u32(f2u(t1));
     uint64_t own = __builtin_amdgcn_ballot_w64(f2u(t1) == T1);
@@ -183,6 +194,7 @@ __device__ __forceinline__ Best unit_best(const float (&x)[P], const float (&y)[
             const bool e = f2u(m[j]) == T1 && i < mi;
             mi = e ? i : mi;
             jr = e ? j : jr;
+            few_rows<P>(j);
         }
         const uint32_t lo = wave_min_u32(mi);
         own = __builtin_amdgcn_ballot_w64(mi == lo);
@@ -215,14 +227,20 @@ __device__ __forceinline__ Best unit_best(const float (&x)[P], const float (&y)[
     return b;
 }
 
+// Rows up to which the records of four slots are gathered at once; beyond, the registers that
+// takes are dearer than a second wait.
+constexpr int kGatherRows = 16;
+
 template <int P>
 __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
     constexpr int kSlots = 4;
     constexpr int kList = kSlots * kThreads;
     __shared__ __attribute__((aligned(16))) u32x4 plist[kList];     // new picks that may matter here
-    __shared__ __attribute__((aligned(16))) u32x4 rlist[kList][3];  // units that may hold a candidate back
+    __shared__ __attribute__((aligned(16))) u32x4 rlist[kList][2];  // units that may hold a candidate back
+    __shared__ Box sbox[kList];                                     // boxes of all units
     __shared__ u32x4 candA[kWaves], candB[kWaves];
-    __shared__ Box ubox[kWaves], ubox2[kWaves];  // a unit's two boxes, later their union
+    __shared__ Box ubox[kWaves], boxA[kWaves], boxB[kWaves];  // a unit's two boxes and their union
+    __shared__ Box wboxes[2];                                 // the workgroup's two boxes
     __shared__ uint32_t s_n[2], s_sum[2], s_bad, s_wv[2];
 
     const int G = a.G, U = G * kWaves;
@@ -253,6 +271,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
         x[j] = u2f(p.x); y[j] = u2f(p.y); z[j] = u2f(p.z);
         id.set(j, p.w);
         m[j] = ok ? __builtin_inff() : 0.f;
+        few_rows<P>(j);
     }
     // The unit's points in their order as two boxes, cut at the widest step: the order jumps
     // now and then, and one box around both ends of a jump would be met by most picks.
@@ -271,6 +290,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
             const float d = i + 1 < p1 ? sqdist(x[j], y[j], z[j], nx, ny, nz) : 0.f;
             at = d > g ? i : at;
             g = fmaxf(g, d);
+            few_rows<P>(j);
         }
         const uint32_t top = wave_max_u32(f2u(g));
         at = readlane_i(at, first_lane(f2u(g) == top));
@@ -280,6 +300,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
             const Box o = {x[j], y[j], z[j], x[j], y[j], z[j]};
             if (i < p1 && i <= at) ba = box_or(ba, o);
             if (i < p1 && i > at) bb = box_or(bb, o);
+            few_rows<P>(j);
         }
 #pragma unroll
         for (int o = 1; o < kWave; o <<= 1) {
@@ -292,6 +313,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
         for (int j = 0; j < P; ++j) {
             const float d = sqdist(x[j], y[j], z[j], qx, qy, qz);
             m[j] = min_dist(m[j], d < qv ? d : __builtin_inff());
+            few_rows<P>(j);
         }
     };
     {
@@ -323,15 +345,15 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
         };
         put(0, ba.lx, ba.ly, ba.lz); put(1, ba.hx, ba.hy, ba.hz);
         put(2, bb.lx, bb.ly, bb.lz); put(3, bb.hx, bb.hy, bb.hz);
-        ubox[wave] = ba;
-        ubox2[wave] = bb;
+        boxA[wave] = ba;
+        boxB[wave] = bb;
+        ubox[wave] = box_or(ba, bb);
     }
     publish(1, false, false);
     if (tid < 2) s_n[tid] = s_sum[tid] = s_wv[tid] = 0;
     if (tid == 0) s_bad = 0;
 
     // ---- slots: the units this lane keeps track of, eight lanes per workgroup ----
-    Box sb[kSlots];                 // unit boxes
     float wd[kSlots], ud[kSlots];   // distance of its workgroup's box, and of its own, from this workgroup's box
     float sv[kSlots], ss[kSlots], sx[kSlots], sy[kSlots], sz[kSlots];
     uint32_t si[kSlots], off[kSlots];
@@ -340,41 +362,62 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
     bool bad = false;
     __syncthreads();
     Box w1, w2;  // the workgroup's points
-    two_boxes(ubox[lane & 7], ubox2[lane & 7], lane, w1, w2);
-    __syncthreads();
-    if (lane == 0) ubox[wave] = box_or(ba, bb);
-    {
+    two_boxes(boxA[lane & 7], boxB[lane & 7], lane, w1, w2);
+    if (tid == 0) { wboxes[0] = w1; wboxes[1] = w2; }
+    // many points in registers: the boxes are read again where they are needed
+    constexpr bool kBoxesInLds = P > kGatherRows;
+    auto unit_dist = [&](float qx, float qy, float qz) {
+        if constexpr (kBoxesInLds) return fminf(box_dist(boxA[wave], qx, qy, qz), box_dist(boxB[wave], qx, qy, qz));
+        else return fminf(box_dist(ba, qx, qy, qz), box_dist(bb, qx, qy, qz));
+    };
+    auto group_dist = [&](float qx, float qy, float qz) {
+        if constexpr (kBoxesInLds) return fminf(box_dist(wboxes[0], qx, qy, qz), box_dist(wboxes[1], qx, qy, qz));
+        else return fminf(box_dist(w1, qx, qy, qz), box_dist(w2, qx, qy, qz));
+    };
+    auto find_units = [&](auto tag, auto first) {
+        constexpr int NS = decltype(tag)::value, Q0 = decltype(first)::value;
         u32x4 ra[4], rb[4], rc[4], rd[4];
+        uint32_t o[4];
 #pragma unroll
-        for (int q = 0; q < kSlots; ++q) {
+        for (int q = 0; q < NS; ++q) {
             // workgroup q * 64 + (lane / 8) * 8 + wave: neighbours along the order go to different waves
-            const int g = q * 64 + (lane >> 3) * 8 + wave;
+            const int g = (Q0 + q) * 64 + (lane >> 3) * 8 + wave;
             const bool ok = g < G;
-            off[q] = (uint32_t)(ok ? g * 8 + (lane & 7) : unit) * 16;
-            fl[q] = (ok ? 3u : 0u) | (g == w ? 8u : 0u);
+            o[q] = off[Q0 + q] = (uint32_t)(ok ? g * 8 + (lane & 7) : unit) * 16;
+            fl[Q0 + q] = (ok ? 3u : 0u) | (g == w ? 8u : 0u);
         }
         for (int spin = 0;; ++spin) {
-            load_pairs<4>(ex, ex + plane, off, ra, rb);
-            load_pairs<4>(ex + 2 * plane, ex + 3 * plane, off, rc, rd);
+            load_pairs<NS>(ex, ex + plane, o, ra, rb);
+            load_pairs<NS>(ex + 2 * plane, ex + 3 * plane, o, rc, rd);
             bool all = true;
 #pragma unroll
-            for (int q = 0; q < kSlots; ++q)
+            for (int q = 0; q < NS; ++q)
                 all = all && chunk_round(ra[q], kTagBox) == 1u && chunk_round(rb[q], kTagBox) == 2u &&
                       chunk_round(rc[q], kTagBox) == 3u && chunk_round(rd[q], kTagBox) == 4u;
             if (__builtin_amdgcn_ballot_w64(!all) == 0) break;
             if (spin >= a.spin_limit) { bad = true; break; }
         }
 #pragma unroll
-        for (int q = 0; q < kSlots; ++q) {
+        for (int q = 0; q < NS; ++q) {
             const Box A = {u2f(ra[q].x), u2f(ra[q].y), u2f(ra[q].z), u2f(rb[q].x), u2f(rb[q].y), u2f(rb[q].z)};
             const Box B = {u2f(rc[q].x), u2f(rc[q].y), u2f(rc[q].z), u2f(rd[q].x), u2f(rd[q].y), u2f(rd[q].z)};
-            sb[q] = box_or(A, B);
-            ud[q] = fminf(fminf(box_box(w1, A), box_box(w1, B)), fminf(box_box(w2, A), box_box(w2, B)));
+            const int s = Q0 + q;
+            if (fl[s] & 1u) sbox[off[s] >> 4] = box_or(A, B);
+            ud[s] = fminf(fminf(box_box(w1, A), box_box(w1, B)), fminf(box_box(w2, A), box_box(w2, B)));
             Box o1, o2;
             two_boxes(A, B, lane, o1, o2);
-            wd[q] = fminf(fminf(box_box(w1, o1), box_box(w1, o2)), fminf(box_box(w2, o1), box_box(w2, o2)));
-            sv[q] = ss[q] = 0.f; sx[q] = sy[q] = sz[q] = 0.f; si[q] = kNoIndex;
+            wd[s] = fminf(fminf(box_box(w1, o1), box_box(w1, o2)), fminf(box_box(w2, o1), box_box(w2, o2)));
+            sv[s] = ss[s] = 0.f; sx[s] = sy[s] = sz[s] = 0.f; si[s] = kNoIndex;
         }
+    };
+    constexpr std::integral_constant<int, 0> s0;
+    constexpr std::integral_constant<int, 1> s1;
+    constexpr std::integral_constant<int, 2> s2;
+    constexpr std::integral_constant<int, 3> s3;
+    if constexpr (kBoxesInLds) {
+        find_units(s1, s0); find_units(s1, s1); find_units(s1, s2); find_units(s1, s3);
+    } else {
+        find_units(std::integral_constant<int, 4>{}, s0);
     }
     uint32_t maxbin = 0;
     float wv = __builtin_inff();  // largest value of this workgroup's points
@@ -386,19 +429,19 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
     uint32_t open = 0;      // bit c: candidate c is not held back by a unit of this workgroup
     float thr = 0.f;        // the smallest value among those
     // Gathers the records of this round and adds to the two lists.
-    auto gather = [&](auto tag) {
-        constexpr int NS = decltype(tag)::value;
+    auto gather = [&](auto tag, auto first) {
+        constexpr int NS = decltype(tag)::value, Q0 = decltype(first)::value;
         u32x4 ra[4], rb[4];
         const uint32_t par = round & 1;
         {
             const char *buf = ex + plane * (4 + 2 * par);
             uint32_t o[4];
 #pragma unroll
-            for (int q = 0; q < NS; ++q) o[q] = (fl[q] & 6u) == 2u ? off[q] : (uint32_t)unit * 16;
+            for (int q = 0; q < NS; ++q) o[q] = (fl[Q0 + q] & 6u) == 2u ? off[Q0 + q] : (uint32_t)unit * 16;
             auto missing = [&](int q) {
                 const uint32_t da = chunk_round(ra[q], kTagA) - round, db = chunk_round(rb[q], kTagB) - round;
-                const bool ok = (fl[q] & 1u) ? (da | db) == 0u : da < kTagWindow;
-                return !ok && (fl[q] & 6u) == 2u;
+                const bool ok = (fl[Q0 + q] & 1u) ? (da | db) == 0u : da < kTagWindow;
+                return !ok && (fl[Q0 + q] & 6u) == 2u;
             };
             load_pairs<NS>(buf, buf + plane, o, ra, rb);
             for (int spin = 0;; ++spin) {
@@ -415,7 +458,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
                 // those who are waited for
                 u32x4 ta[4], tb[4];
 #pragma unroll
-                for (int q = 0; q < NS; ++q) o[q] = ms[q] ? off[q] : (uint32_t)unit * 16;
+                for (int q = 0; q < NS; ++q) o[q] = ms[q] ? off[Q0 + q] : (uint32_t)unit * 16;
                 load_pairs<NS>(buf, buf + plane, o, ta, tb);
 #pragma unroll
                 for (int q = 0; q < NS; ++q)
@@ -427,17 +470,17 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
         u32x4 pe[NS];
 #pragma unroll
         for (int q = 0; q < NS; ++q) {
-            const bool use = (fl[q] & 5u) == 1u;
-            pe[q] = u32x4{f2u(sx[q]), f2u(sy[q]), f2u(sz[q]), f2u(sv[q])};
-            pk[q] = use && (ra[q].y & 0x80000000u) && fminf(box_dist(w1, sx[q], sy[q], sz[q]), box_dist(w2, sx[q], sy[q], sz[q])) < fminf(wv, sv[q]);
+            const bool use = (fl[Q0 + q] & 5u) == 1u;
+            pe[q] = u32x4{f2u(sx[Q0 + q]), f2u(sy[Q0 + q]), f2u(sz[Q0 + q]), f2u(sv[Q0 + q])};
+            pk[q] = use && (ra[q].y & 0x80000000u) && group_dist(sx[Q0 + q], sy[Q0 + q], sz[Q0 + q]) < fminf(wv, sv[Q0 + q]);
             if (use) {
-                fl[q] |= (ra[q].x >> 31) << 2;
-                sv[q] = u2f(ra[q].x & 0x7fffffffu);
-                si[q] = ra[q].y & 0x7fffffffu;
-                ss[q] = u2f(ra[q].z);
-                sx[q] = u2f(rb[q].x); sy[q] = u2f(rb[q].y); sz[q] = u2f(rb[q].z);
+                fl[Q0 + q] |= (ra[q].x >> 31) << 2;
+                sv[Q0 + q] = u2f(ra[q].x & 0x7fffffffu);
+                si[Q0 + q] = ra[q].y & 0x7fffffffu;
+                ss[Q0 + q] = u2f(ra[q].z);
+                sx[Q0 + q] = u2f(rb[q].x); sy[Q0 + q] = u2f(rb[q].y); sz[Q0 + q] = u2f(rb[q].z);
             }
-            rel[q] = (fl[q] & 9u) == 1u && ud[q] < wv && sv[q] >= thr;
+            rel[q] = (fl[Q0 + q] & 9u) == 1u && ud[Q0 + q] < wv && sv[Q0 + q] >= thr;
             pm[q] = __builtin_amdgcn_ballot_w64(pk[q]);
             rm[q] = __builtin_amdgcn_ballot_w64(rel[q]);
         }
@@ -454,9 +497,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
                 if (pk[q]) plist[pbase + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(pm[q] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)pm[q], 0u))] = pe[q];
                 if (rel[q]) {
                     const int at = rbase + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(rm[q] >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)rm[q], 0u));
-                    rlist[at][0] = u32x4{f2u(sv[q]), si[q], f2u(ss[q]), f2u(sx[q])};
-                    rlist[at][1] = u32x4{f2u(sy[q]), f2u(sz[q]), f2u(sb[q].lx), f2u(sb[q].ly)};
-                    rlist[at][2] = u32x4{f2u(sb[q].lz), f2u(sb[q].hx), f2u(sb[q].hy), f2u(sb[q].hz)};
+                    rlist[at][0] = u32x4{f2u(sv[Q0 + q]), si[Q0 + q], f2u(ss[Q0 + q]), f2u(sx[Q0 + q])};
+                    rlist[at][1] = u32x4{f2u(sy[Q0 + q]), f2u(sz[Q0 + q]), off[Q0 + q] >> 4, 0u};
                 }
                 pbase += __builtin_popcountll(pm[q]);
                 rbase += __builtin_popcountll(rm[q]);
@@ -465,14 +507,14 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
         if (round == 1) {
             uint32_t mx = 0;
 #pragma unroll
-            for (int q = 0; q < NS; ++q) mx = umax(mx, f2u(sv[q]));
+            for (int q = 0; q < NS; ++q) mx = umax(mx, f2u(sv[Q0 + q]));
             mx = wave_max_u32(mx);
             if (lane == 0) atomicMax(&s_sum[1], mx);
         }
 #pragma unroll
         for (int q = 0; q < NS; ++q) {
-            const uint32_t ov = eight_max_all(f2u(sv[q]));
-            if ((fl[q] & 8u) && (lane & 7) == 0) s_wv[par] = ov;
+            const uint32_t ov = eight_max_all(f2u(sv[Q0 + q]));
+            if ((fl[Q0 + q] & 8u) && (lane & 7) == 0) s_wv[par] = ov;
         }
     };
     // Which workgroups matter from the next round on; packs the slots when half of them will do.
@@ -523,14 +565,6 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
 #pragma unroll
                     for (int d = 0; d < ND; ++d) arr[d] = t[d];
                 };
-                auto move_box = [&](float Box::*f) {
-                    float t[4] = {sb[0].*f, sb[1].*f, sb[2].*f, sb[3].*f};
-                    move(t);
-#pragma unroll
-                    for (int d = 0; d < ND; ++d) sb[d].*f = t[d];
-                };
-                move_box(&Box::lx); move_box(&Box::ly); move_box(&Box::lz);
-                move_box(&Box::hx); move_box(&Box::hy); move_box(&Box::hz);
                 move(wd); move(ud); move(sv); move(ss); move(sx); move(sy); move(sz); move(si); move(off); move(fl);
 #pragma unroll
                 for (int d = 0; d < ND; ++d)
@@ -572,9 +606,14 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
             open = ~o & 0xffu;
             thr = u2f(~row_max_uniform(lane < 8 && ((open >> c) & 1u) ? ~mA.x : 0u));
         }
-        if (cur == 1) gather(std::integral_constant<int, 1>{});
-        else if (cur == 2) gather(std::integral_constant<int, 2>{});
-        else gather(std::integral_constant<int, 4>{});
+        if (cur == 1) {
+            gather(std::integral_constant<int, 1>{}, s0);
+        } else if (cur == 2 || P > kGatherRows) {
+            gather(std::integral_constant<int, 2>{}, s0);
+            if (cur == 4) gather(std::integral_constant<int, 2>{}, s2);
+        } else {
+            gather(std::integral_constant<int, 4>{}, s0);
+        }
         // the unit's pick of the round before goes to the list now, out of the exchange's way
         if (!logged) {
             if (np >= p1 - p0) bad = true;  // a point picked twice: coordinates that are not finite
@@ -594,7 +633,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
         wg_barrier();  // 1: both lists, s_wv, s_sum
         const uint32_t seen = s_sum[par], counts = s_n[par];
         const uint32_t wvb = s_wv[par], isbad = s_bad;
-        const u32x4 e_first = plist[lane], r0 = rlist[lane][0], r1 = rlist[lane][1], r2 = rlist[lane][2];
+        const u32x4 e_first = plist[lane], r0 = rlist[lane][0], r1 = rlist[lane][1];
         wv = u2f(wvb);
         if (isbad) break;
         if (round == 1) maxbin = seen >> kLocalBinShift;
@@ -615,7 +654,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
             u32x4 e = c0 == 0 ? e_first : plist[c0 + lane];
             const float ex_ = u2f(e.x), ey_ = u2f(e.y), ez_ = u2f(e.z), ev_ = fminf(best.v, u2f(e.w));
             const bool in = c0 + lane < npl;
-            const bool hit = in && fminf(box_dist(ba, ex_, ey_, ez_), box_dist(bb, ex_, ey_, ez_)) < ev_;
+            const bool hit = in && unit_dist(ex_, ey_, ez_) < ev_;
             const bool low = in && sqdist(best.x, best.y, best.z, ex_, ey_, ez_) < ev_;
             pick = pick && __builtin_amdgcn_ballot_w64(low) == 0;
             uint64_t hits = __builtin_amdgcn_ballot_w64(hit);
@@ -634,28 +673,29 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
                     d = d < av ? d : __builtin_inff();
                     f = f < cv ? f : __builtin_inff();
                     m[j] = min3_dist(m[j], d, f);
+                    few_rows<P>(j);
                 }
             }
         }
         // ---- does a unit come before it with a point in its ball? ----
         if (pick) {
             const uint64_t kp = ((uint64_t)f2u(best.v) << 32) | ~best.i;
-            auto holds = [&](const u32x4 &e0, const u32x4 &e1, const u32x4 &e2, int c) {
+            auto holds = [&](const u32x4 &e0, const u32x4 &e1, int c) {
                 const uint64_t ke = ((uint64_t)e0.x << 32) | ~e0.y;
                 const bool above = c < nrl && ke > kp;
                 if (__builtin_amdgcn_ballot_w64(above) == 0) return false;
-                const Box eb = {u2f(e1.z), u2f(e1.w), u2f(e2.x), u2f(e2.y), u2f(e2.z), u2f(e2.w)};
+                const Box eb = sbox[above ? e1.z : 0u];
                 const bool blk = above && box_dist(eb, best.x, best.y, best.z) < best.v &&
                                  (u2f(e0.z) >= best.v || sqdist(u2f(e0.w), u2f(e1.x), u2f(e1.y), best.x, best.y, best.z) < best.v);
                 return __builtin_amdgcn_ballot_w64(blk) != 0;
             };
-            pick = !holds(r0, r1, r2, lane);
+            pick = !holds(r0, r1, lane);
             for (int c0 = kWave; c0 < nrl && pick; c0 += 2 * kWave) {
                 const int c = c0 + lane, d = (c + kWave) & (kList - 1);
-                const u32x4 a0 = rlist[c][0], a1 = rlist[c][1], a2 = rlist[c][2];
-                const u32x4 b0 = rlist[d][0], b1 = rlist[d][1], b2 = rlist[d][2];
-                pick = !holds(a0, a1, a2, c);
-                if (pick && c0 + kWave < nrl) pick = !holds(b0, b1, b2, c + kWave);
+                const u32x4 a0 = rlist[c][0], a1 = rlist[c][1];
+                const u32x4 b0 = rlist[d][0], b1 = rlist[d][1];
+                pick = !holds(a0, a1, c);
+                if (pick && c0 + kWave < nrl) pick = !holds(b0, b1, c + kWave);
             }
         }
         if (pick) {
@@ -688,8 +728,8 @@ hipError_t launch_t(LocalArgs &a, int clouds, hipStream_t s) {
 }
 
 // Rows of 64 points per unit.
-#define FFPS_LOCAL_ROWS(X) X(1) X(2) X(3) X(4) X(6) X(8) X(12) X(16) X(24)
-constexpr int kMaxRows = 24;
+#define FFPS_LOCAL_ROWS(X) X(1) X(2) X(3) X(4) X(6) X(8) X(12) X(16) X(24) X(32) X(40)
+constexpr int kMaxRows = 40;
 constexpr int kUnitMax = kMaxRows * kWave;
 
 }  // namespace
@@ -736,6 +776,8 @@ LocalBuffers carve_local(char *base, int B, int N, const LocalPlan &p, size_t *b
     if (bytes) *bytes = o;
     return l;
 }
+
+int local_capacity() { return kMaxGridWG * kWaves * kUnitMax; }
 
 size_t local_workspace_bound(int B, int N) {
     // no device gives a cloud more workgroups than this, whatever it has

@@ -18,8 +18,13 @@ CASES = {
     "smallest": (lambda: inputs.uniform_cube(4609, 1)[None], 4609, 4608),
     "smallest with the work for it": (lambda: inputs.uniform_cube(5793, 1)[None], 5793, 5792),
     "just short of it": (lambda: inputs.uniform_cube(8192, 1)[None], 4095, 0),
-    "few samples, still enough": (lambda: inputs.uniform_cube(2097152, 5)[None], 160, 9),
-    "too few samples": (lambda: inputs.uniform_cube(2097152, 5)[None], 159, 9),
+    "few samples, still enough": (lambda: inputs.uniform_cube(2097152, 5)[None], 128, 9),
+    "too few samples": (lambda: inputs.uniform_cube(2097152, 5)[None], 127, 9),
+    "twenty-four rows, exactly": (lambda: inputs.uniform_cube(3145728, 6)[None], 150, 3145727),
+    "thirty-two rows": (lambda: inputs.uniform_cube(3145729, 6)[None], 90, 0),
+    "forty rows": (lambda: inputs.room(4194305, 6)[None], 100, 77),
+    "the most a device holds": (lambda: inputs.uniform_cube(5242880, 7)[None], 80, 5242879),
+    "beyond it": (lambda: inputs.uniform_cube(5242881, 7)[None], 80, 5),
     "a row of units and one point": (lambda: inputs.room(65537, 2)[None], 513, 65536),
     "more clouds than a launch, enough work": (lambda: np.stack([inputs.planes_and_clusters(9001, i) for i in range(15)]), 3728, 3),
     "a long line": (lambda: inputs.lattice_line(6000)[None], 6000, 0),
