@@ -11,17 +11,16 @@ per second of exact FPS at N = 200,000, M = 50,000, i.e. N (M - 1) over the time
 of call (a), taken with events on the launch stream inside the timed steps;
 `ms_per_step` is the wall time of a whole step (a) + (b) + (c).
 
-Roofline of the dominant kernel (k_fps_grid, call (a)): the cloud and its running
-minimum distances stay in registers for the whole call, so no memory system
-bounds it; what the hardware limits is the fp32 vector arithmetic of the
-updates themselves.  An update is 3 subtractions, 3 multiplications, 2
-additions and 1 minimum, each individually rounded: 9 operations that can
-not be fused (the method fixes the rounding of each).  Peak for such code = half
-the published 157.3 TFLOP/s fp32 vector rate, which counts a fused multiply-add
-as two: 256 CUs x 4 SIMDs x 32 lanes per clock x 2.4 GHz = 78.6 T operations/s.
-The rate that plain, unfused and unpacked fp32 instructions sustain on the
-device is measured in the same run (`alu_probe`, the library's diagnostic
-kernel) and reported beside it.
+Roofline of the dominant kernel (k_fps_local, call (a)): neither memory nor
+arithmetic bounds it.  The cloud stays in registers (the counters see 135 MB, the
+records that travel between the CUs), and a pick is applied only where it can
+matter, about 130 distances per point instead of 50,000.  What is left is the
+latency of a round: publish, gather, judge.  The floor of a round is one trip of a
+record from CU to CU and back into registers, 1.39 us as measured inside
+k_fps_grid; the achieved figure is the time of call (a), sorts included, over its rounds.
+`update_equivalent_tops` is what the greedy loop's arithmetic (9 individually rounded
+operations per update) would come to in that time: no rate of this kernel, hence no
+fraction of the 78.6 T operations/s peak.
 The HBM-equivalent rate (20 B per update over the same time: what a streaming
 loop would have to move) is reported as an extra key, not as a roofline.
 
@@ -44,6 +43,7 @@ OPS_PER_UPDATE = 9             # 3 sub + 3 mul + 2 add + 1 min, none fused
 BYTES_PER_UPDATE = 20          # xyz 12 B + min-distance read 4 B + write 4 B
 HBM_PEAK_GBS = 8000.0
 MI355X_CUS, MI355X_GHZ, SIMDS_PER_CU, LANES_PER_SIMD_CLOCK = 256, 2.4, 4, 32
+ROUND_TRIP_US = 1.39  # gather of one round, profiles/k_fps_grid_config4_round_phases.md
 ALU_PEAK_TOPS = MI355X_CUS * SIMDS_PER_CU * LANES_PER_SIMD_CLOCK * MI355X_GHZ / 1e3   # 78.6
 
 
@@ -141,7 +141,8 @@ def main():
     ms_cached = sum(e[1].elapsed_time(e[2]) for e in evs) / args.steps
     ms_chain = sum(e[2].elapsed_time(e[3]) for e in evs) / args.steps
     achieved_tops = upd_exact * OPS_PER_UPDATE / (ms_exact * 1e-3) / 1e12
-    traffic, traffic_src = traffic_from_profile("k_fps_grid_config4_hbm_counters.md")
+    traffic, traffic_src = traffic_from_profile("k_fps_local_config4_hbm_counters.md")
+    us_per_round = ms_exact * 1e3 / max(rounds_exact, 1)
 
     if args.calibrate_copy:
         src = torch.empty(64 * 1024 * 1024, dtype=torch.float32, device="cuda").normal_()
@@ -150,7 +151,6 @@ def main():
         torch.cuda.synchronize()
         del src, dst
 
-    plan = fb.ffps_describe_plan(1, N, fb.FFPS_VARIANT_AUTO, props.multi_processor_count)
     result = {
         "metric": "point_distance_updates_per_s",
         "value": upd_exact / (ms_exact * 1e-3),
@@ -180,19 +180,14 @@ def main():
         "hbm_equivalent_gbs": upd_exact * BYTES_PER_UPDATE / (ms_exact * 1e-3) / 1e9,
         "device": {"name": props.name, "compute_units": props.multi_processor_count,
                    "clock_mhz": getattr(props, "clock_rate", 0) / 1e3 or None},
-        "roofline": {"bound": "alu", "achieved": achieved_tops, "peak": ALU_PEAK_TOPS,
-                     "unit": "TFLOP/s", "frac": achieved_tops / ALU_PEAK_TOPS,
+        "roofline": {"bound": "latency", "achieved": us_per_round, "peak": ROUND_TRIP_US,
+                     "unit": "us/round", "frac": ROUND_TRIP_US / us_per_round,
                      "traffic": traffic, "traffic_source": traffic_src,
-                     "kernel_time_profile": "profiles/k_fps_grid_bench_config4_kernel_stats.md (this command "
-                                            "with --no-per-config: config 3's batch runs on the same "
-                                            "instantiation and launch size)",
-                     "kernel": f"k_fps_grid (exact FPS, N={N}, M={M1}; {plan[1]} workgroups, "
-                               f"{plan[2]} reporting units)",
+                     "kernel_time_profile": "profiles/k_fps_local_bench_config4_kernel_stats.md",
+                     "kernel": f"k_fps_local (exact FPS, N={N}, M={M1}) and the sorts around it",
+                     "update_equivalent_tops": achieved_tops, "alu_peak_tops": ALU_PEAK_TOPS,
                      "ops_per_update": OPS_PER_UPDATE,
                      "algorithmic_ops_per_launch": upd_exact * OPS_PER_UPDATE,
-                     "peak_derivation": "256 CUs x 4 SIMDs x 32 lanes per clock x 2.4 GHz = half the "
-                                        "published 157.3 TFLOP/s, which counts a fused multiply-add as two "
-                                        "(the method fixes the rounding of every operation, so none is fused)",
                      "note": "points and minimum distances stay in registers; `traffic` is what the "
                              "hardware counters saw for one launch (exchange records), from the "
                              "committed profile"},
@@ -250,7 +245,7 @@ def main():
             wsc = fb.make_workspace(B, n, st[0])
             o1 = torch.empty((B, st[0]), dtype=torch.int32, device="cuda")
             oc = torch.empty((B, sum(st)), dtype=torch.int32, device="cuda")
-            kernel, wg, units, clouds = fb.ffps_describe_plan(B, n, 0, props.multi_processor_count)
+            kernel = fb.ffps_describe_plan(B, n, 0, props.multi_processor_count)[0]
             t_exact = timed(lambda: fb.ffps_exact(xc, st[0], 0, workspace=wsc, out=o1))
             t_chain = timed(lambda: fb.ffps_cached_stages(xc, st, fb.FFPS_MODE_CHAIN, workspace=wsc, out=oc))
             t_flash = timed(lambda: fb.ffps_cached_stages(xc, st, fb.FFPS_MODE_CACHED, KEEP[0], KEEP[1],
@@ -259,8 +254,7 @@ def main():
             upd = B * n * (st[0] - 1)
             per[f"config{c}"] = {
                 "B": B, "N": n, "stages": list(st),
-                "kernel": {1: "k_fps_wgm", 2: "k_fps_grid", 3: "k_fps_stream"}[kernel],
-                "workgroups_per_cloud": wg, "units_per_cloud": units,
+                "kernel": {1: "one workgroup per cloud", 2: "clouds over many CUs", 3: "streamed"}[kernel],
                 "exact_layer1_ms": t_exact, "us_per_pick": t_exact * 1e3 / (st[0] - 1),
                 "exact_updates_per_s": upd / (t_exact * 1e-3),
                 "exact_chain_ms": t_chain, "prune75_cache_ms": t_flash,

@@ -230,6 +230,9 @@ int ffps_last_rounds(const void *d_ws, void *stream);
  *                        that serves clouds of at most 256 points, and clouds
  *                        beyond 4608 points when WG is forced)
  *   *clouds_per_launch   clouds one kernel launch carries
+ * The layout is that of the explicit variants.  Where AUTO samples by local
+ * maxima instead (no cap on the picks of a round), the units are rows or waves
+ * of points along a curve and their number is not reported here.
  * Any output pointer may be NULL.  FFPS_ERR_INVALID_ARG for B, N, num_cu < 1,
  * FFPS_ERR_UNSUPPORTED_SIZE when the requested variant cannot hold N.
  */
