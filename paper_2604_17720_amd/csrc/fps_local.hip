@@ -20,8 +20,8 @@
 //
 //   - Points are sorted along a space-filling curve first (spatial.hip); a UNIT, one
 //     wave, holds a stretch of it in registers (up to 40 rows of 64 points), eight units
-//     make a workgroup.  From 24 rows on some values of the slots below are spilled (40 rows: 244
-//     registers); with the boxes in LDS, records gathered two slots at a time and the rows
+//     make a workgroup.  From 24 rows on some values of the slots below are spilled (40 rows: about
+//     250 registers); with the boxes in LDS, records gathered two slots at a time and the rows
 //     kept in their order (few_rows) a round of five million points takes 10 us, 21 without.
 //   - Per round a unit publishes its best point (value, index, coordinates), the value of
 //     its second best, and whether the candidate it published the round before was picked:
@@ -39,8 +39,8 @@
 //     beyond the samples (10 to 15 % of them) are left out by the final sort (spatial.hip).
 //
 // Measured, exact FPS of a room of 200,000 points to 50,000 samples, sorts included:
-// 0.84 ms against 4.44 ms with k_fps_grid; 45,678 points to 5,001: 0.43 against 0.84 ms;
-// five million to 1024: 1.24 ms against 4.71 ms with k_fps_stream.
+// 0.82 ms against 4.44 ms with k_fps_grid; 45,678 points to 5,001: 0.42 against 0.84 ms;
+// five million to 1024: 1.22 ms against 4.71 ms with k_fps_stream.
 //
 // Every wait is bounded as in fps_exchange.h, and a point that is picked twice (coordinates
 // that are not finite) ends the kernel with the same status.
@@ -78,9 +78,9 @@ struct LocalArgs {
 
 // unsigned maximum over eight consecutive lanes, in each of them
 __device__ __forceinline__ uint32_t eight_max_all(uint32_t v) {
-    v = umax(v, dpp_all<0xB1>(v));   // quad_perm 1,0,3,2
-    v = umax(v, dpp_all<0x4E>(v));   // quad_perm 2,3,0,1
-    v = umax(v, dpp_all<0x141>(v));  // row_half_mirror
+    v = umax(v, dpp_or_zero<0xB1>(v));   // quad_perm 1,0,3,2
+    v = umax(v, dpp_or_zero<0x4E>(v));   // quad_perm 2,3,0,1
+    v = umax(v, dpp_or_zero<0x141>(v));  // row_half_mirror
     return v;
 }
 
@@ -355,6 +355,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
 
     // ---- slots: the units this lane keeps track of, eight lanes per workgroup ----
     float wd[kSlots], ud[kSlots];   // distance of its workgroup's box, and of its own, from this workgroup's box
+    float gv[kSlots];               // largest value of its workgroup (found twice where registers are short)
     float sv[kSlots], ss[kSlots], sx[kSlots], sy[kSlots], sz[kSlots];
     uint32_t si[kSlots], off[kSlots];
     uint32_t fl[kSlots];            // 1: wanted, 2: waited for, 4: stopped, 8: this workgroup's own
@@ -514,6 +515,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
 #pragma unroll
         for (int q = 0; q < NS; ++q) {
             const uint32_t ov = eight_max_all(f2u(sv[Q0 + q]));
+            gv[Q0 + q] = u2f(ov);
             if ((fl[Q0 + q] & 8u) && (lane & 7) == 0) s_wv[par] = ov;
         }
     };
@@ -524,8 +526,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
         uint64_t act[NS];
 #pragma unroll
         for (int q = 0; q < NS; ++q) {
-            const float ov = u2f(eight_max_all(f2u(sv[q])));
-            const bool keep = (fl[q] & 1u) && wd[q] < fmaxf(ov, wv);
+            if constexpr (kBoxesInLds) gv[q] = u2f(eight_max_all(f2u(sv[q])));
+            const bool keep = (fl[q] & 1u) && wd[q] < fmaxf(gv[q], wv);
             // waited for: wanted until now
             fl[q] = (fl[q] & 12u) | ((fl[q] & 1u) << 1) | (keep ? 1u : 0u);
             act[q] = __builtin_amdgcn_ballot_w64((fl[q] & 3u) != 0 && (lane & 7) == 0);
@@ -598,8 +600,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
             const float pv = u2f(mA.x), px = u2f(mB.x), py = u2f(mB.y), pz = u2f(mB.z);
             const uint64_t kp = ((uint64_t)mA.x << 32) | ~mA.y, ku = ((uint64_t)oA.x << 32) | ~oA.y;
             const bool near = box_dist(ob, px, py, pz) < pv;
-            const bool hid = u2f(oA.z) >= pv || sqdist(u2f(oB.x), u2f(oB.y), u2f(oB.z), px, py, pz) < pv;
-            const uint64_t bm = __builtin_amdgcn_ballot_w64(mA.x == 0u || (c != k && ku > kp && near && hid));
+            const bool hid = (u2f(oA.z) >= pv) | (sqdist(u2f(oB.x), u2f(oB.y), u2f(oB.z), px, py, pz) < pv);
+            const uint64_t bm = __builtin_amdgcn_ballot_w64((mA.x == 0u) | ((ku > kp) & near & hid));  // of itself no key is greater
             uint32_t o = (uint32_t)bm | (uint32_t)(bm >> 32);
             o |= o >> 16;
             o |= o >> 8;

@@ -5,11 +5,6 @@
 
 namespace ffps {
 
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_all(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, 0xf, 0xf, false);
-}
-
 // Workgroup barrier for LDS data alone: stores to memory stay in flight (a barrier of the
 // language would wait for them, which is the latency of the exchange once more).
 __device__ __forceinline__ void wg_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory"); }
