@@ -240,6 +240,20 @@ int ffps_describe_plan(int B, int N, int variant, int num_cu, int *kernel, int *
                        int *units_per_cloud, int *clouds_per_launch);
 
 /*
+ * The kernel that ffps_exact would run for B clouds of N points and M samples
+ * with a workspace of ws_bytes on a device with num_cu compute units, without
+ * touching any device.  Host only.  *kernel receives FFPS_KERNEL_*.
+ * Errors as ffps_exact's for the same sizes.
+ */
+#define FFPS_KERNEL_WAVE 1   /* one wave per cloud, one pick per pass                     */
+#define FFPS_KERNEL_BLOCK 2  /* one workgroup per cloud, by local maxima                  */
+#define FFPS_KERNEL_WG 3     /* one workgroup per cloud, rounds of candidates or one pick */
+#define FFPS_KERNEL_GRID 4   /* each cloud across many CUs, rounds of candidates          */
+#define FFPS_KERNEL_LOCAL 5  /* each cloud across many CUs, by local maxima               */
+#define FFPS_KERNEL_STREAM 6 /* streamed from HBM, rounds of candidates                   */
+int ffps_describe_kernel(int B, int N, int M, int variant, int num_cu, size_t ws_bytes, int *kernel);
+
+/*
  * Reference measurement for the multi-workgroup kernels: runs `iters`
  * (1 .. 2^20) plain grid barriers (one device-scope atomic arrive plus a spin
  * on the counter each) over one workgroup per CU, the launch shape of the GRID

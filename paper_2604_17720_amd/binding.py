@@ -28,8 +28,12 @@ FFPS_VARIANT_AUTO = 0
 FFPS_VARIANT_WG = 1
 FFPS_VARIANT_GRID = 2
 FFPS_VARIANT_STREAM = 3
-
-
+FFPS_KERNEL_WAVE = 1
+FFPS_KERNEL_BLOCK = 2
+FFPS_KERNEL_WG = 3
+FFPS_KERNEL_GRID = 4
+FFPS_KERNEL_LOCAL = 5
+FFPS_KERNEL_STREAM = 6
 
 FFPS_VARIANT_TEST_NO_WAIT = 1 << 16
 
@@ -42,7 +46,7 @@ def variant_with_picks(variant: int, picks: int) -> int:
 EXPORTS = ["ffps_version", "ffps_strerror", "ffps_prune_sizes", "ffps_workspace_bytes",
            "ffps_exact", "ffps_prune", "ffps_cached_stages", "ffps_last_status",
            "ffps_last_rounds", "ffps_barrier_probe", "ffps_alu_probe", "ffps_gather_rows", "ffps_describe_plan",
-           "ffps_exact_noalloc"]
+           "ffps_exact_noalloc", "ffps_describe_kernel"]
 
 
 class FlashFPSError(RuntimeError):
@@ -82,6 +86,7 @@ def lib() -> ctypes.CDLL:
         L.ffps_barrier_probe.argtypes = [c_int, c_vp, c_sz, c_vp, ctypes.POINTER(ctypes.c_float)]
         L.ffps_alu_probe.argtypes = [c_int, c_int, c_vp, c_sz, c_vp, ctypes.POINTER(ctypes.c_double)]
         L.ffps_describe_plan.argtypes = [c_int, c_int, c_int, c_int, ip, ip, ip, ip]
+        L.ffps_describe_kernel.argtypes = [c_int, c_int, c_int, c_int, c_int, c_sz, ip]
         for n in EXPORTS:
             if n not in ("ffps_strerror",):
                 getattr(L, n).restype = c_int
@@ -116,6 +121,16 @@ def ffps_describe_plan(B, N, variant=FFPS_VARIANT_AUTO, num_cu=256):
     if rc:
         raise FlashFPSError(rc, "ffps_describe_plan")
     return k.value, g.value, u.value, c.value
+
+
+def ffps_describe_kernel(B, N, M, variant=FFPS_VARIANT_AUTO, num_cu=256, ws_bytes=None) -> int:
+    """FFPS_KERNEL_* that ffps_exact would run; ws_bytes None: a workspace of ffps_workspace_bytes."""
+    k = ctypes.c_int()
+    rc = lib().ffps_describe_kernel(B, N, M, variant, num_cu, ffps_workspace_bytes(B, N, M) if ws_bytes is None else ws_bytes,
+                                    ctypes.byref(k))
+    if rc:
+        raise FlashFPSError(rc, "ffps_describe_kernel")
+    return k.value
 
 
 def ffps_workspace_bytes(B, N, M) -> int:

@@ -182,8 +182,10 @@ bool takes_block(int B, int N) {
 // million points to 34 in 320 against 281 us.  Beyond the registers' 3.1 million points, where
 // k_fps_grid gives way to k_fps_stream, the two meet near 80 samples (four million uniform points
 // to 64: 655 against 618 us, to 128: 747, 846; a room of five million to 64: 790, 1042; to 1024: 1240, 4711).
-bool takes_local(int N, int M, int v) {
-    return (long)N * M >= (1L << 25) && M >= (v == FFPS_VARIANT_STREAM ? 80 : 96 + N / 65536);
+// The sorts around it put the cloud number in gridDim.y: more clouds than that stay with k_fps_grid,
+// which takes them in batches.
+bool takes_local(int B, int N, int M, int v) {
+    return B <= kMaxBatchHelpers && (long)N * M >= (1L << 25) && M >= (v == FFPS_VARIANT_STREAM ? 80 : 96 + N / 65536);
 }
 
 // Clouds that are rows of a larger array: point i of cloud b is row idx[b][i] of [B][points]
@@ -201,49 +203,62 @@ bool takes_rows(int B, int N, int M, int variant, const Device &dev) {
     return takes_wave(N, resolve_variant(B, N, variant, dev)) || (any_rounds(M, variant) && takes_block(B, N));
 }
 
+// The kernel that samples B clouds of N points to M, FFPS_KERNEL_*, or a negative error.  `local_bytes`:
+// what the workspace has for k_fps_local; where that is too little the kernels without it run.
+int kernel_for(int B, int N, int M, int variant, const Device &dev, size_t local_bytes) {
+    const int v = resolve_variant(B, N, variant, dev);
+    if (v < 0) return v;
+    if (takes_wave(N, v)) return FFPS_KERNEL_WAVE;
+    if (any_rounds(M, variant) && takes_block(B, N)) return FFPS_KERNEL_BLOCK;
+    if (v == FFPS_VARIANT_WG) return FFPS_KERNEL_WG;
+    if (any_rounds(M, variant) && takes_local(B, N, M, v)) {
+        const LocalPlan plan = plan_fps_local(B, N, dev.num_cu);
+        size_t bytes = 0;
+        if (plan.wg_per_cloud > 0) {
+            carve_local(nullptr, B, N, plan, &bytes);
+            if (bytes <= local_bytes) return FFPS_KERNEL_LOCAL;
+        }
+    }
+    return v == FFPS_VARIANT_GRID ? FFPS_KERNEL_GRID : FFPS_KERNEL_STREAM;
+}
+
 // Exact FPS of B clouds [N] into idx (row stride idx_stride).  Arguments are
 // already validated.  `clear`: the status block is cleared first, by the kernel itself where
 // that is safe.  `rows` only where takes_rows says so.
 int run_exact(const float *xyz, int B, int N, int M, int start, const int *start_dev, int variant,
               int32_t *idx, long idx_stride, float *md, long md_stride, char *ws,
               const Workspace &w, const Device &dev, hipStream_t s, bool clear, const Rows *rows = nullptr) {
-    int v = resolve_variant(B, N, variant, dev);
-    if (v < 0) return v;
-    const bool wave = takes_wave(N, v), block = any_rounds(M, variant) && takes_block(B, N);
-    if (wave || block) {
-        const bool own = wave || B == 1;
+    const int kernel = kernel_for(B, N, M, variant, dev, w.local_bytes);
+    if (kernel < 0) return kernel;
+    if (kernel == FFPS_KERNEL_WAVE || kernel == FFPS_KERNEL_BLOCK) {
+        const bool own = kernel == FFPS_KERNEL_WAVE || B == 1;
         int rc = clear && !own ? clear_status(ws, w, s) : FFPS_OK;
         if (rc) return rc;
         const BlockArgs a = {xyz, rows ? rows->points : N, rows ? rows->idx : nullptr, rows ? rows->stride : 0, N, M, start, start_dev,
                              idx, idx_stride, md, md_stride, (int *)(ws + w.status), clear && own};
-        return hip_rc(wave ? launch_fps_wave(a, B, s) : launch_fps_block(a, B, s));
+        return hip_rc(kernel == FFPS_KERNEL_WAVE ? launch_fps_wave(a, B, s) : launch_fps_block(a, B, s));
     }
     if (clear) {
         int rc = clear_status(ws, w, s);
         if (rc) return rc;
     }
-    if (v == FFPS_VARIANT_WG)
+    if (kernel == FFPS_KERNEL_WG)
         return hip_rc(launch_fps_wg(xyz, B, N, M, start, start_dev, idx, idx_stride, md, md_stride,
                                     variant_picks(variant), (int *)(ws + w.status), s));
-    if ((v == FFPS_VARIANT_GRID || v == FFPS_VARIANT_STREAM) && any_rounds(M, variant) && takes_local(N, M, v)) {
+    if (kernel == FFPS_KERNEL_LOCAL) {
         const LocalPlan plan = plan_fps_local(B, N, dev.num_cu);
-        size_t bytes = 0;
-        if (plan.wg_per_cloud > 0) {
-            const LocalBuffers l = carve_local(ws + w.local, B, N, plan, &bytes);
-            if (bytes <= w.local_bytes) {
-                int *status = (int *)(ws + w.status);
-                int rc = hip_rc(launch_order(xyz, B, N, l, s));
-                if (rc == FFPS_OK)
-                    rc = hip_rc(launch_local(xyz, l, B, N, M, start, start_dev, plan, status,
-                                             (variant & FFPS_VARIANT_TEST_NO_WAIT) ? 0 : -1, s));
-                if (rc == FFPS_OK)
-                    rc = hip_rc(launch_finish(l, B, N, M, plan.units_per_cloud, start, start_dev, idx, idx_stride, md,
-                                              md_stride, status, s));
-                return rc;
-            }
-        }
+        const LocalBuffers l = carve_local(ws + w.local, B, N, plan, nullptr);
+        int *status = (int *)(ws + w.status);
+        int rc = hip_rc(launch_order(xyz, B, N, l, s));
+        if (rc == FFPS_OK)
+            rc = hip_rc(launch_local(xyz, l, B, N, M, start, start_dev, plan, status,
+                                     (variant & FFPS_VARIANT_TEST_NO_WAIT) ? 0 : -1, s));
+        if (rc == FFPS_OK)
+            rc = hip_rc(launch_finish(l, B, N, M, plan.units_per_cloud, start, start_dev, idx, idx_stride, md,
+                                      md_stride, status, s));
+        return rc;
     }
-    if (v == FFPS_VARIANT_GRID) {
+    if (kernel == FFPS_KERNEL_GRID) {
         const GridPlan plan = plan_fps_grid(B, N, dev.num_cu);
         for (int b = 0; b < B; b += plan.clouds_per_launch) {
             const int clouds = B - b < plan.clouds_per_launch ? B - b : plan.clouds_per_launch;
@@ -260,21 +275,18 @@ int run_exact(const float *xyz, int B, int N, int M, int start, const int *start
         }
         return FFPS_OK;
     }
-    if (v == FFPS_VARIANT_STREAM) {
-        for (int b = 0; b < B; ++b) {
-            int rc = clear_exchange(ws, w, 1, s);
-            if (rc) return rc;
-            hipError_t e = launch_fps_stream(xyz + (size_t)b * N * 3, (float *)(ws + w.mind) + (size_t)b * N,
-                                             N, M, start, start_dev ? start_dev + b : nullptr,
-                                             idx + b * idx_stride,
-                                             md ? md + b * md_stride : nullptr, ws + w.exchange,
-                                             (int *)(ws + w.status), dev.num_cu,
-                                             variant_picks(variant), s);
-            if (e != hipSuccess) return FFPS_ERR_LAUNCH_FAILED;
-        }
-        return FFPS_OK;
+    for (int b = 0; b < B; ++b) {
+        int rc = clear_exchange(ws, w, 1, s);
+        if (rc) return rc;
+        hipError_t e = launch_fps_stream(xyz + (size_t)b * N * 3, (float *)(ws + w.mind) + (size_t)b * N,
+                                         N, M, start, start_dev ? start_dev + b : nullptr,
+                                         idx + b * idx_stride,
+                                         md ? md + b * md_stride : nullptr, ws + w.exchange,
+                                         (int *)(ws + w.status), dev.num_cu,
+                                         variant_picks(variant), s);
+        if (e != hipSuccess) return FFPS_ERR_LAUNCH_FAILED;
     }
-    return FFPS_ERR_UNSUPPORTED_SIZE;
+    return FFPS_OK;
 }
 
 int run_prune(const float *xyz, int B, int N, int M, int start, int keep_num, int keep_den,
@@ -507,6 +519,17 @@ int ffps_describe_plan(int B, int N, int variant, int num_cu, int *kernel, int *
     if (wg_per_cloud) *wg_per_cloud = wg;
     if (units_per_cloud) *units_per_cloud = units;
     if (clouds_per_launch) *clouds_per_launch = clouds;
+    return FFPS_OK;
+}
+
+int ffps_describe_kernel(int B, int N, int M, int variant, int num_cu, size_t ws_bytes, int *kernel) {
+    if (!kernel || B < 1 || N < 1 || M < 1 || M > N || num_cu < 1 || check_variant(variant)) return FFPS_ERR_INVALID_ARG;
+    if ((long)B * N > (1L << 31) - 1) return FFPS_ERR_INVALID_ARG;
+    const Workspace w = carve(B, N, M);
+    if (ws_bytes < w.total) return FFPS_ERR_WORKSPACE_TOO_SMALL;
+    const int k = kernel_for(B, N, M, variant, Device{FFPS_OK, num_cu}, w.local_bytes);
+    if (k < 0) return k;
+    *kernel = k;
     return FFPS_OK;
 }
 
