@@ -43,7 +43,7 @@ extern "C" {
 
 #define FFPS_OK 0
 #define FFPS_ERR_INVALID_ARG (-1)         /* null pointer, size out of range, M > N, bad ratio ... */
-#define FFPS_ERR_WORKSPACE_TOO_SMALL (-2) /* ws_bytes < ffps_workspace_bytes(...)                  */
+#define FFPS_ERR_WORKSPACE_TOO_SMALL (-2) /* ws_bytes below what every kernel needs                 */
 #define FFPS_ERR_UNSUPPORTED_DEVICE (-3)  /* current device is not gfx950                          */
 #define FFPS_ERR_LAUNCH_FAILED (-4)       /* a HIP call failed                                     */
 #define FFPS_ERR_TIMEOUT (-5)             /* a kernel gave up waiting for another workgroup        */
@@ -98,6 +98,13 @@ int ffps_prune_sizes(int N, int M, int keep_num, int keep_den, unsigned flags, i
  * Upper bound, in bytes, of the device workspace any entry point below needs
  * for B clouds of N points and at most M samples per cloud.  Host only.
  * The workspace needs 256-byte alignment and no initialisation.
+ * 20 to 24 bytes per point and 12 MiB are needed by every call; clouds of 4609
+ * to 5,242,880 points with points x samples >= 2^25 and 80 samples or more
+ * have 34 bytes per point (and 140 KB per cloud) on top for the local-maximum
+ * kernel.  A workspace that lacks only that area, one sized for other clouds for
+ * instance, is accepted: AUTO then takes the kernels that do without it, with the
+ * same results (ffps_describe_kernel tells).  Clouds of more points have no such area, also
+ * not for fewer candidates or stages that are sampled out of them.
  */
 int ffps_workspace_bytes(int B, int N, int M, size_t *bytes);
 
@@ -110,7 +117,7 @@ int ffps_workspace_bytes(int B, int N, int M, size_t *bytes);
  *   d_idx      out  [B][M] int32; d_idx[b][0] = start_idx, then the picks in order
  *   d_maxdist  out  [B][M] fp32 or NULL: squared minimum distance each pick had
  *                   when it was chosen; entry 0 is +inf
- *   d_ws       workspace of ws_bytes >= ffps_workspace_bytes(B, N, M)
+ *   d_ws       workspace of ws_bytes >= ffps_workspace_bytes(B, N, M) (see there)
  */
 int ffps_exact(const float *d_xyz, int B, int N, int M, int start_idx, int variant,
                int32_t *d_idx, float *d_maxdist, void *d_ws, size_t ws_bytes, void *stream);

@@ -21,9 +21,23 @@ using namespace ffps;
 constexpr size_t kAlign = 256;
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
+// The helper kernels of FPS-Prune and of the stage chain put the cloud number
+// in gridDim.y, which the hardware limits to 65535.
+constexpr int kMaxBatchHelpers = 65535;
+
 struct Workspace {  // byte offsets into the caller's workspace
-    size_t status, exchange, cxyz, loc, bitmap, mind, cand, spos, local, local_bytes, total;
+    size_t status, exchange, cxyz, loc, bitmap, mind, cand, spos, local, local_bytes;
+    size_t least;  // what every call needs
+    size_t total;  // with the local-maximum kernel's area, which comes last
+    // A workspace between the two holds for the kernels without that area.
+    void limit(size_t ws_bytes) {
+        if (ws_bytes < total) local_bytes = ws_bytes - local;
+    }
 };
+
+// Least points x samples of k_fps_local, and its least samples (see takes_local).
+constexpr long kLocalWork = 1L << 25;
+constexpr int kLocalSamples = 80;
 
 Workspace carve(int B, int N, int M) {
     Workspace w;
@@ -36,10 +50,13 @@ Workspace carve(int B, int N, int M) {
     w.mind = o;     o += align_up((size_t)B * N * sizeof(float));
     w.cand = o;     o += align_up((size_t)B * N * sizeof(int32_t));
     w.spos = o;     o += align_up((size_t)B * sizeof(int));
-    // the local-maximum kernel's area comes last; clouds of one workgroup do not need it
-    w.local = o;    w.local_bytes = N > wgm_capacity() && N <= local_capacity() ? local_workspace_bound(B, N) : 0;
-    o += align_up(w.local_bytes);
-    w.total = o;
+    // Neither clouds of one workgroup nor too few samples go to the local-maximum kernel, and what a call
+    // samples on the way (candidates, stages) has no more points and no more samples.
+    const bool local = N > wgm_capacity() && N <= local_capacity() && (long)N * M >= kLocalWork && M >= kLocalSamples &&
+                       B <= kMaxBatchHelpers;
+    w.least = w.local = o;
+    w.local_bytes = local ? align_up(local_workspace_bound(B, N)) : 0;
+    w.total = o + w.local_bytes;
     return w;
 }
 
@@ -116,10 +133,6 @@ int check_common(const void *xyz, int B, int N, int M, int start, const void *id
     return FFPS_OK;
 }
 
-// The helper kernels of FPS-Prune and of the stage chain put the cloud number
-// in gridDim.y, which the hardware limits to 65535.
-constexpr int kMaxBatchHelpers = 65535;
-
 // `variant` carries the kernel choice in its low byte and the optional
 // picks-per-round cap above it (FFPS_VARIANT_WITH_PICKS).
 inline int variant_kind(int variant) { return variant & 0xff; }
@@ -185,7 +198,7 @@ bool takes_block(int B, int N) {
 // The sorts around it put the cloud number in gridDim.y: more clouds than that stay with k_fps_grid,
 // which takes them in batches.
 bool takes_local(int B, int N, int M, int v) {
-    return B <= kMaxBatchHelpers && (long)N * M >= (1L << 25) && M >= (v == FFPS_VARIANT_STREAM ? 80 : 96 + N / 65536);
+    return B <= kMaxBatchHelpers && (long)N * M >= kLocalWork && M >= (v == FFPS_VARIANT_STREAM ? kLocalSamples : 96 + N / 65536);
 }
 
 // Clouds that are rows of a larger array: point i of cloud b is row idx[b][i] of [B][points]
@@ -375,7 +388,8 @@ int ffps_exact(const float *d_xyz, int B, int N, int M, int start_idx, int varia
     if (rc) return rc;
     if ((rc = check_variant(variant))) return rc;
     Workspace w = carve(B, N, M);
-    if (ws_bytes < w.total) return FFPS_ERR_WORKSPACE_TOO_SMALL;
+    if (ws_bytes < w.least) return FFPS_ERR_WORKSPACE_TOO_SMALL;
+    w.limit(ws_bytes);
     Device dev = query_device();
     if (dev.ok) return dev.ok;
     if ((rc = resolve_variant(B, N, variant, dev)) < 0) return rc;
@@ -400,7 +414,7 @@ int ffps_exact_noalloc(const float *d_xyz, int B, int N, int M, int start_idx, i
     Workspace w;
     const size_t none = ~(size_t)0;
     // the local-maximum kernel takes the exchange areas' place where its own area fits there
-    w.status = 0; w.exchange = kAlign; w.total = kScratchBytes;
+    w.status = 0; w.exchange = kAlign; w.least = w.total = kScratchBytes;
     w.local = kAlign; w.local_bytes = kScratchBytes - kAlign;
     w.cxyz = w.loc = w.bitmap = w.mind = w.cand = w.spos = none;  // not part of this path
     hipStream_t s = (hipStream_t)stream;
@@ -421,7 +435,8 @@ int ffps_prune(const float *d_xyz, int B, int N, int M, int start_idx, int keep_
     int Nc, k, R;
     if ((rc = ffps_prune_sizes(N, M, keep_num, keep_den, flags, &Nc, &k, &R))) return rc;
     Workspace w = carve(B, N, M);
-    if (ws_bytes < w.total) return FFPS_ERR_WORKSPACE_TOO_SMALL;
+    if (ws_bytes < w.least) return FFPS_ERR_WORKSPACE_TOO_SMALL;
+    w.limit(ws_bytes);
     Device dev = query_device();
     if (dev.ok) return dev.ok;
     if ((rc = resolve_variant(B, Nc, variant, dev)) < 0) return rc;
@@ -448,7 +463,8 @@ int ffps_cached_stages(const float *d_xyz, int B, int N, int L, const int *M_sta
     int Nc, k, R;
     if ((rc = ffps_prune_sizes(N, M_stages[0], keep_num, keep_den, flags, &Nc, &k, &R))) return rc;
     Workspace w = carve(B, N, M_stages[0]);
-    if (ws_bytes < w.total) return FFPS_ERR_WORKSPACE_TOO_SMALL;
+    if (ws_bytes < w.least) return FFPS_ERR_WORKSPACE_TOO_SMALL;
+    w.limit(ws_bytes);
     Device dev = query_device();
     if (dev.ok) return dev.ok;
     if ((rc = resolve_variant(B, Nc, variant, dev)) < 0) return rc;
@@ -525,8 +541,9 @@ int ffps_describe_plan(int B, int N, int variant, int num_cu, int *kernel, int *
 int ffps_describe_kernel(int B, int N, int M, int variant, int num_cu, size_t ws_bytes, int *kernel) {
     if (!kernel || B < 1 || N < 1 || M < 1 || M > N || num_cu < 1 || check_variant(variant)) return FFPS_ERR_INVALID_ARG;
     if ((long)B * N > (1L << 31) - 1) return FFPS_ERR_INVALID_ARG;
-    const Workspace w = carve(B, N, M);
-    if (ws_bytes < w.total) return FFPS_ERR_WORKSPACE_TOO_SMALL;
+    Workspace w = carve(B, N, M);
+    if (ws_bytes < w.least) return FFPS_ERR_WORKSPACE_TOO_SMALL;
+    w.limit(ws_bytes);
     const int k = kernel_for(B, N, M, variant, Device{FFPS_OK, num_cu}, w.local_bytes);
     if (k < 0) return k;
     *kernel = k;
@@ -554,7 +571,7 @@ int ffps_gather_rows(const float *d_rows, int B, int N, int C, const int32_t *d_
 int ffps_barrier_probe(int iters, void *d_ws, size_t ws_bytes, void *stream, float *us_per_barrier) {
     if (!d_ws || !us_per_barrier || iters < 1 || iters > (1 << 20)) return FFPS_ERR_INVALID_ARG;
     Workspace w = carve(1, 1, 1);
-    if (ws_bytes < w.total) return FFPS_ERR_WORKSPACE_TOO_SMALL;
+    if (ws_bytes < w.least) return FFPS_ERR_WORKSPACE_TOO_SMALL;
     Device dev = query_device();
     if (dev.ok) return dev.ok;
     hipStream_t s = (hipStream_t)stream;
@@ -589,7 +606,7 @@ int ffps_alu_probe(int waves_per_cu, int iters, void *d_ws, size_t ws_bytes, voi
     if (!d_ws || !ops_per_s || iters < 1 || iters > (1 << 20) || waves_per_cu < 1 || waves_per_cu > 32)
         return FFPS_ERR_INVALID_ARG;
     Workspace w = carve(1, 1, 1);
-    if (ws_bytes < w.total) return FFPS_ERR_WORKSPACE_TOO_SMALL;
+    if (ws_bytes < w.least) return FFPS_ERR_WORKSPACE_TOO_SMALL;
     Device dev = query_device();
     if (dev.ok) return dev.ok;
     hipStream_t s = (hipStream_t)stream;

@@ -32,3 +32,27 @@ def test_more_clouds_than_a_grid_dimension_holds():
     assert kernel(65535, 8193, 4097) == fb.FFPS_KERNEL_LOCAL
     assert kernel(65536, 8193, 4097) == fb.FFPS_KERNEL_GRID
     assert kernel(65536, 30000, 30000) == fb.FFPS_KERNEL_GRID
+
+
+def test_a_workspace_sized_for_other_clouds():
+    """What a workspace held before the local-maximum kernel had an area of its own still suffices:
+    such a call runs the kernels without it."""
+    other = fb.ffps_workspace_bytes(1, 6000000, 1024)  # of a larger cloud, which has no such area
+    assert other < fb.ffps_workspace_bytes(1, 5000000, 1024)
+    assert kernel(1, 5000000, 1024, ws_bytes=other) == fb.FFPS_KERNEL_STREAM
+    assert kernel(1, 5000000, 1024) == fb.FFPS_KERNEL_LOCAL
+    # bytes per call: status, exchange, coordinates, samples, bitmap, distances, candidates, starts
+    up = lambda v: (v + 255) // 256 * 256
+    least = 256 + 256 * 2 * 6 * 256 * 16 + up(12 * 200000) + up(4 * 50000) + up(4 * 6250) + 2 * up(4 * 200000) + up(4)
+    assert kernel(1, 200000, 50000, ws_bytes=least) == fb.FFPS_KERNEL_GRID
+    with pytest.raises(fb.FlashFPSError) as e:
+        kernel(1, 200000, 50000, ws_bytes=least - 1)
+    assert e.value.code == fb.FFPS_ERR_WORKSPACE_TOO_SMALL
+
+
+@pytest.mark.parametrize("b,n,m", [(4096, 4700, 90), (1, 200000, 167), (1, 1000000, 33), (1, 5000000, 6), (70000, 9000, 4000)])
+def test_no_area_for_calls_that_cannot_use_it(b, n, m):
+    assert kernel(b, n, m) != fb.FFPS_KERNEL_LOCAL
+    up = lambda v: (v + 255) // 256 * 256
+    assert fb.ffps_workspace_bytes(b, n, m) == 256 + 256 * 2 * 6 * 256 * 16 + up(12 * b * n) + up(4 * b * m) + \
+        up(4 * b * ((n + 31) // 32)) + 2 * up(4 * b * n) + up(4 * b)
