@@ -50,8 +50,6 @@ __device__ __forceinline__ uint32_t row_bits(uint64_t m, int lane) {
     return (half >> (lane & 16)) & 0xffffu;
 }
 __device__ __forceinline__ uint64_t key_of(const u32x4 &rec) { return ((uint64_t)rec.y << 32) | rec.x; }
-// LDS of the wave's own is read and written in order: only the compiler has to be held.
-__device__ __forceinline__ void wave_lds_order() { asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory"); }
 
 template <int P>
 __global__ __launch_bounds__(kBlockThreads, 2) void k_fps_block(BlockArgs a) {

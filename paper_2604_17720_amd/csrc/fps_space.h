@@ -9,6 +9,9 @@ namespace ffps {
 // language would wait for them, which is the latency of the exchange once more).
 __device__ __forceinline__ void wg_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory"); }
 
+// LDS that lanes of one wave pass on to one another is read and written in order: only the compiler has to be held.
+__device__ __forceinline__ void wave_lds_order() { asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory"); }
+
 // Distances to boxes use the operations of sqdist in its order.  Rounding is monotonic, so the
 // result is never above the distance, as the kernels compute it, to any point of the box.
 struct Box { float lx, ly, lz, hx, hy, hz; };

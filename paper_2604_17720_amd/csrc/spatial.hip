@@ -171,12 +171,12 @@ __device__ __forceinline__ void stable_pass(const uint32_t *__restrict__ hist, i
         const bool ok = i < hi;
         const uint32_t d = ok ? digit(i) : 0u;
         const uint64_t m = same_digit<BITS>(d, __builtin_amdgcn_ballot_w64(ok));
-        if (ok) {
-            const uint32_t base = cnt[wave][d];
-            const int r_in = lanes_below(m);
-            move(i, base + r_in);
-            if (r_in == 0) cnt[wave][d] = base + (uint32_t)__builtin_popcountll(m);
-        }
+        const uint32_t base = cnt[wave][d];
+        const int r_in = lanes_below(m);
+        wave_lds_order();  // all lanes have read the count
+        if (ok && r_in == 0) cnt[wave][d] = base + (uint32_t)__builtin_popcountll(m);
+        wave_lds_order();  // and it is written before the next row reads it
+        if (ok) move(i, base + r_in);
     }
 }
 
@@ -407,11 +407,12 @@ __global__ __launch_bounds__(256) void k_finish_sort(FinishArgs a) {
                     const uint32_t d = (uint32_t)(~key >> shift) & 255u;
                     const uint64_t m = same_digit<8>(d, __builtin_amdgcn_ballot_w64(ok));
                     for (int v = 0; v < 4; ++v) {
-                        if (wave == v && ok) {
+                        if (wave == v) {
                             const uint32_t base = cnt[d];
                             const int r_in = lanes_below(m);
-                            dst[base + r_in] = key;
-                            if (r_in == 0) cnt[d] = base + (uint32_t)__builtin_popcountll(m);
+                            wave_lds_order();  // all lanes have read the count
+                            if (ok && r_in == 0) cnt[d] = base + (uint32_t)__builtin_popcountll(m);
+                            if (ok) dst[base + r_in] = key;
                         }
                         __syncthreads();
                     }
