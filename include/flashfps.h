@@ -68,9 +68,9 @@ extern "C" {
  * points (1 = one pick per pass; 0 = library default).  The result never
  * depends on it. */
 #define FFPS_VARIANT_WITH_PICKS(variant, picks) ((variant) | ((picks) << 8))
-/* Test knob for the error path: a workgroup of the GRID kernel that does not find
- * the records of all other workgroups at its first look gives up at once instead
- * of after the library's bound on waiting.  Every workgroup then leaves the
+/* Test knob for the error path: a workgroup of the GRID kernel, or of the
+ * local-maximum kernel that AUTO takes, that does not find the records it waits
+ * for at its first look gives up at once instead of after the library's bound on waiting.  Every workgroup then leaves the
  * kernel in the ordinary way and the status word reads FFPS_ERR_TIMEOUT; the
  * outputs of such a call are unspecified. */
 #define FFPS_VARIANT_TEST_NO_WAIT (1 << 16)
@@ -212,9 +212,9 @@ int ffps_gather_rows(const float *d_rows, int B, int N, int C, const int32_t *d_
  * Status word the kernels of the last call on this workspace left behind:
  * synchronises `stream`, copies one int from the workspace and returns it
  * (FFPS_OK; FFPS_ERR_TIMEOUT when a workgroup stopped waiting for another;
- * FFPS_ERR_INTERNAL when a round of a multi-pick kernel named no pick, which
- * the method rules out, and the kernel went on only in order to end; the
- * outputs of such a call are undefined).
+ * FFPS_ERR_INTERNAL when a round of a multi-pick kernel named no pick or picked a
+ * point again, which the method rules out for finite coordinates, and the kernel
+ * went on only in order to end; the outputs of such a call are undefined).
  */
 int ffps_last_status(const void *d_ws, void *stream);
 

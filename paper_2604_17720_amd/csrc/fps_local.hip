@@ -42,8 +42,9 @@
 // 0.82 ms against 4.44 ms with k_fps_grid; 45,678 points to 5,001: 0.42 against 0.84 ms;
 // five million to 1024: 1.22 ms against 4.71 ms with k_fps_stream.
 //
-// Every wait is bounded as in fps_exchange.h, and a point that is picked twice (coordinates
-// that are not finite) ends the kernel with the same status.
+// Every wait is bounded as in fps_exchange.h.  A point that is picked twice (coordinates that are not
+// finite) ends the workgroup with the status of inconsistent results; those that wait for it look at the
+// status now and then and leave, too.
 #include "fps_exchange.h"
 #include "fps_local.h"
 #include "fps_space.h"
@@ -59,6 +60,7 @@ constexpr int kThreads = kWaves * kWave;
 // alternates) is told from a new one.
 constexpr uint32_t kTagA = 0x9E3779B1u, kTagB = 0x85EBCA6Bu, kTagBox = 0x5F356495u;
 constexpr uint32_t kTagWindow = 1u << 20;  // "this round or a later one"
+constexpr int kPollsPerLook = 1024;        // at records that are missing, between two looks at the status
 
 __device__ __forceinline__ uint32_t chunk_round(const u32x4 &c, uint32_t which) { return c.x ^ c.y ^ c.z ^ c.w ^ which; }
 
@@ -241,7 +243,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
     __shared__ u32x4 candA[kWaves], candB[kWaves];
     __shared__ Box ubox[kWaves], boxA[kWaves], boxB[kWaves];  // a unit's two boxes and their union
     __shared__ Box wboxes[2];                                 // the workgroup's two boxes
-    __shared__ uint32_t s_n[2], s_sum[2], s_bad, s_wv[2];
+    __shared__ uint32_t s_n[2], s_sum[2], s_bad, s_twice, s_wv[2];
 
     const int G = a.G, U = G * kWaves;
     const int cloud = blockIdx.x / G, w = blockIdx.x - cloud * G;
@@ -351,7 +353,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
     }
     publish(1, false, false);
     if (tid < 2) s_n[tid] = s_sum[tid] = s_wv[tid] = 0;
-    if (tid == 0) s_bad = 0;
+    if (tid == 0) s_bad = s_twice = 0;
 
     // ---- slots: the units this lane keeps track of, eight lanes per workgroup ----
     float wd[kSlots], ud[kSlots];   // distance of its workgroup's box, and of its own, from this workgroup's box
@@ -454,7 +456,11 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
                     any = any || ms[q];
                 }
                 if (__builtin_amdgcn_ballot_w64(any) == 0) break;
-                if (spin >= a.spin_limit) { bad = true; break; }
+                if (spin >= a.spin_limit || ((spin & (kPollsPerLook - 1)) == kPollsPerLook - 1 &&
+                                             __hip_atomic_load(a.status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+                    bad = true;
+                    break;
+                }
                 // only what is missing is read again: polling everything would be in the way of
                 // those who are waited for
                 u32x4 ta[4], tb[4];
@@ -618,8 +624,10 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
         }
         // the unit's pick of the round before goes to the list now, out of the exchange's way
         if (!logged) {
-            if (np >= p1 - p0) bad = true;  // a point picked twice: coordinates that are not finite
-            else if (lane == 0) {
+            if (np >= p1 - p0) {  // a point picked twice: coordinates that are not finite
+                bad = true;
+                s_twice = 1;
+            } else if (lane == 0) {
                 picks[np] = u32x4{f2u(lv), li, round - 1, 0u};
                 atomicAdd(&hist[local_bin_place(f2u(lv) >> kLocalBinShift)], 1u);
             }
@@ -717,8 +725,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
     if (tid == 0) {
         if (s_bad) {
             int expected = 0;
-            __hip_atomic_compare_exchange_strong(a.status, &expected, kErrGaveUp, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_compare_exchange_strong(a.status, &expected, s_twice ? kErrInconsistent : kErrGaveUp, __ATOMIC_RELAXED,
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
     }
 }

@@ -94,3 +94,38 @@ def test_auto_in_a_hip_graph(oracle):
         eager = fb.ffps_exact(xd, m, 5, workspace=ws)
         torch.cuda.synchronize()
         assert np.array_equal(eager.cpu().numpy(), oracle.fps_exact(x, m, 5))
+
+
+@pytest.mark.parametrize("n,m", [(60000, 1500), (9000, 8000)])
+def test_give_up_path_of_local_maxima_ends_cleanly(oracle, n, m):
+    """FFPS_ERR_TIMEOUT, forced from the host: a workgroup that misses a record at its first look gives
+    up, all leave in the ordinary way, and the next call on the workspace is right again."""
+    import torch
+
+    import paper_2604_17720_amd.binding as fb
+    x = inputs.room(n, 3)[None]
+    assert fb.ffps_describe_kernel(1, n, m) == fb.FFPS_KERNEL_LOCAL
+    xd, ws = torch.from_numpy(x).cuda(), fb.make_workspace(1, n, m)
+    fb.ffps_exact(xd, m, 0, fb.FFPS_VARIANT_AUTO | fb.FFPS_VARIANT_TEST_NO_WAIT, workspace=ws)
+    assert fb.ffps_last_status(ws) == fb.FFPS_ERR_TIMEOUT
+    got = fb.ffps_exact(xd, m, 0, workspace=ws)
+    assert fb.ffps_last_status(ws) == 0
+    assert np.array_equal(got.cpu().numpy(), oracle.fps_exact(x, m, 0))
+
+
+@pytest.mark.parametrize("n,m", [(1500, 700), (9000, 8000)])  # one workgroup, many
+def test_a_coordinate_that_is_not_finite_is_reported(oracle, n, m):
+    """Outputs are undefined then, but the call ends with FFPS_ERR_INTERNAL on either kernel (a point
+    is picked again, which the kernels check themselves), and the workspace stays usable."""
+    import torch
+
+    import paper_2604_17720_amd.binding as fb
+    x = inputs.uniform_cube(n, 4)[None]
+    bad = x.copy()
+    bad[0, n // 3, 1] = np.nan
+    ws = fb.make_workspace(1, n, m)
+    fb.ffps_exact(torch.from_numpy(bad).cuda(), m, 0, workspace=ws)
+    assert fb.ffps_last_status(ws) == fb.FFPS_ERR_INTERNAL
+    got = fb.ffps_exact(torch.from_numpy(x).cuda(), m, 0, workspace=ws)
+    assert fb.ffps_last_status(ws) == 0
+    assert np.array_equal(got.cpu().numpy(), oracle.fps_exact(x, m, 0))
