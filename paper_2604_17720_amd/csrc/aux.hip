@@ -65,6 +65,7 @@ __global__ void k_mark_picks(int N, int k, const int32_t *__restrict__ idx_all, 
 }
 
 constexpr int kTileWords = 1024;  // bitmap words of a tile, one per thread: 32,768 points
+constexpr int kTileBlocks = 256;  // blocks of a cloud at most: each counts the words before its own tiles again
 
 // Exclusive prefix over the block of one count per thread; `total` receives the sum.
 __device__ __forceinline__ int block_prefix(int cnt, int *part, int tid, int *total) {
@@ -82,7 +83,11 @@ __device__ __forceinline__ int block_prefix(int cnt, int *part, int tid, int *to
     return r;
 }
 
-// Fill of FPS-Prune, a tile of the bitmap per block: ranks of the free indices by popcount
+// First tile of a block.
+__device__ __forceinline__ int first_tile(int tiles, int block, int blocks) { return (int)((long)tiles * block / blocks); }
+
+// Fill of FPS-Prune, a tile of the bitmap per block (beyond 8.4 million points several, so that the
+// counting does not grow with the square of the points): ranks of the free indices by popcount
 // (a block counts the words of the tiles before its own again: 25 KB for 200,000 points) and
 // scan, then every free index decides on its own whether
 // some j maps to its rank: fill[j] = free[floor(j*F/R)], F = N - k.  Since
@@ -90,16 +95,16 @@ __device__ __forceinline__ int block_prefix(int cnt, int *part, int tid, int *to
 // j = ceil(r*R/F) when floor(j*F/R) == r.
 // Clouds of one tile are marked here as well, in the same launch.  One block did clouds of all
 // sizes before: 51 us for 200,000 points, with tiles 14 us in three launches.
-__global__ __launch_bounds__(1024) void k_fill(int N, int k, int R, int32_t *__restrict__ idx_all,
+__global__ __launch_bounds__(1024) void k_fill(int N, int tiles, int k, int R, int32_t *__restrict__ idx_all,
                                                long idx_stride, uint32_t *__restrict__ bitmap_all) {
     __shared__ int part[1024];
-    const int b = blockIdx.y, tile = blockIdx.x;
+    const int b = blockIdx.y;
     const int tid = threadIdx.x;
     const int words = (N + 31) / 32;
     uint32_t *bm = bitmap_all + (size_t)b * words;
     int32_t *idx = idx_all + b * idx_stride;
 
-    if (gridDim.x == 1) {
+    if (tiles == 1) {
         for (int i = tid; i < words; i += 1024) bm[i] = 0u;
         __syncthreads();
         for (int j = tid; j < k; j += 1024) {
@@ -109,26 +114,31 @@ __global__ __launch_bounds__(1024) void k_fill(int N, int k, int R, int32_t *__r
         __syncthreads();
     }
     int before = 0;
-    for (int wd = tid; wd < tile * kTileWords; wd += 1024) before += __popc(~bm[wd]);
-    if (tile > 0) (void)block_prefix(before, part, tid, &before);
-    const int wd = tile * kTileWords + tid;
-    uint32_t free_bits = 0u;
-    if (wd < words) free_bits = ~bm[wd] & ((wd == words - 1 && (N & 31)) ? ((1u << (N & 31)) - 1u) : 0xffffffffu);
-    // Rank r is taken by fill slot j = ceil(r*R/F) iff floor(j*F/R) == r, i.e. iff
-    // acc = j*F - r*R lies in [0, R).  One division finds j for the thread's first
-    // rank; from rank to rank acc drops by R and, when it goes negative, j steps up.
-    const long r = before + block_prefix(__popc(free_bits), part, tid, nullptr);  // rank of the first free index
+    const int t0 = first_tile(tiles, blockIdx.x, gridDim.x), t1 = first_tile(tiles, blockIdx.x + 1, gridDim.x);
+    for (int wd = tid; wd < t0 * kTileWords; wd += 1024) before += __popc(~bm[wd]);
+    if (t0 > 0) (void)block_prefix(before, part, tid, &before);
     const long F = (long)N - k;
-    long j = (r * R + F - 1) / F;
-    long acc = j * F - r * R;
-    while (free_bits) {
-        const int bit = __ffs(free_bits) - 1;
-        free_bits &= free_bits - 1;
-        if (acc < R && j < R) idx[k + j] = wd * 32 + bit;
-        acc -= R;
-        if (acc < 0) {
-            ++j;
-            acc += F;
+    for (int tile = t0; tile < t1; ++tile) {
+        const int wd = tile * kTileWords + tid;
+        uint32_t free_bits = 0u;
+        if (wd < words) free_bits = ~bm[wd] & ((wd == words - 1 && (N & 31)) ? ((1u << (N & 31)) - 1u) : 0xffffffffu);
+        // Rank r is taken by fill slot j = ceil(r*R/F) iff floor(j*F/R) == r, i.e. iff
+        // acc = j*F - r*R lies in [0, R).  One division finds j for the thread's first
+        // rank; from rank to rank acc drops by R and, when it goes negative, j steps up.
+        int total = 0;
+        const long r = before + block_prefix(__popc(free_bits), part, tid, &total);  // rank of the first free index
+        before += total;
+        long j = (r * R + F - 1) / F;
+        long acc = j * F - r * R;
+        while (free_bits) {
+            const int bit = __ffs(free_bits) - 1;
+            free_bits &= free_bits - 1;
+            if (acc < R && j < R) idx[k + j] = wd * 32 + bit;
+            acc -= R;
+            if (acc < 0) {
+                ++j;
+                acc += F;
+            }
         }
     }
 }
@@ -249,7 +259,7 @@ __global__ void k_perm_mark(int N, int Nc, uint64_t seed, uint32_t *__restrict__
 // block; `start` takes the place of the last drawn candidate when it was not drawn.  A wave takes
 // two words at a time, a lane per bit, so that list and coordinates are written side by side.
 // (One block with a stretch of words per thread took 429 us for 300,000 points.)
-__global__ __launch_bounds__(1024) void k_perm_compact(const float *__restrict__ xyz_all, int N, int Nc,
+__global__ __launch_bounds__(1024) void k_perm_compact(const float *__restrict__ xyz_all, int N, int tiles, int Nc,
                                                        int start, uint64_t seed,
                                                        const uint32_t *__restrict__ bitmap_all,
                                                        int32_t *__restrict__ cand_all,
@@ -258,7 +268,7 @@ __global__ __launch_bounds__(1024) void k_perm_compact(const float *__restrict__
     __shared__ int part[1024];
     __shared__ uint32_t bits_of[kTileWords];
     __shared__ int rank_of[kTileWords];
-    const int b = blockIdx.y, tile = blockIdx.x;
+    const int b = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int words = (N + 31) / 32;
     const uint32_t *bm = bitmap_all + (size_t)b * words;
@@ -276,25 +286,30 @@ __global__ __launch_bounds__(1024) void k_perm_compact(const float *__restrict__
         return v;
     };
     int before = 0;
-    for (int wd = tid; wd < tile * kTileWords; wd += 1024) before += __popc(word(wd));
-    if (tile > 0) (void)block_prefix(before, part, tid, &before);
-    const int wd0 = tile * kTileWords;
-    const uint32_t own = wd0 + tid < words ? word(wd0 + tid) : 0u;
-    const int r = before + block_prefix(__popc(own), part, tid, nullptr);
-    bits_of[tid] = own;
-    rank_of[tid] = r;
-    __syncthreads();
-    for (int p = wave; p < kTileWords / 2; p += 16) {
-        const int t = 2 * p + (lane >> 5);
-        const uint32_t v = bits_of[t];
-        if ((v >> (lane & 31)) & 1u) {
-            const int at = rank_of[t] + __popc(v & ((1u << (lane & 31)) - 1u));
-            const int i = (wd0 + t) * 32 + (lane & 31);
-            cand[at] = i;
-            cxyz[3 * (size_t)at + 0] = xyz[3 * (size_t)i + 0];
-            cxyz[3 * (size_t)at + 1] = xyz[3 * (size_t)i + 1];
-            cxyz[3 * (size_t)at + 2] = xyz[3 * (size_t)i + 2];
-            if (i == start) spos_all[b] = at;
+    const int t0 = first_tile(tiles, blockIdx.x, gridDim.x), t1 = first_tile(tiles, blockIdx.x + 1, gridDim.x);
+    for (int wd = tid; wd < t0 * kTileWords; wd += 1024) before += __popc(word(wd));
+    if (t0 > 0) (void)block_prefix(before, part, tid, &before);
+    for (int tile = t0; tile < t1; ++tile) {
+        const int wd0 = tile * kTileWords;
+        const uint32_t own = wd0 + tid < words ? word(wd0 + tid) : 0u;
+        int total = 0;
+        const int r = before + block_prefix(__popc(own), part, tid, &total);
+        before += total;
+        bits_of[tid] = own;
+        rank_of[tid] = r;
+        __syncthreads();
+        for (int p = wave; p < kTileWords / 2; p += 16) {
+            const int t = 2 * p + (lane >> 5);
+            const uint32_t v = bits_of[t];
+            if ((v >> (lane & 31)) & 1u) {
+                const int at = rank_of[t] + __popc(v & ((1u << (lane & 31)) - 1u));
+                const int i = (wd0 + t) * 32 + (lane & 31);
+                cand[at] = i;
+                cxyz[3 * (size_t)at + 0] = xyz[3 * (size_t)i + 0];
+                cxyz[3 * (size_t)at + 1] = xyz[3 * (size_t)i + 1];
+                cxyz[3 * (size_t)at + 2] = xyz[3 * (size_t)i + 2];
+                if (i == start) spos_all[b] = at;
+            }
         }
     }
 }
@@ -327,7 +342,7 @@ __global__ __launch_bounds__(1024) void k_fill_perm(int N, int k, int R, uint64_
     bool is_free[per];
 #pragma unroll
     for (int e = 0; e < per; ++e) {
-        const int j = tile * kPermTile + tid * per + e;
+        const long j = (long)tile * kPermTile + tid * per + e;
         is_free[e] = false;
         if (j < N) {
             at[e] = perm_at(p, (uint32_t)j);
@@ -440,6 +455,7 @@ static hipError_t mark_picks(int B, int N, int k, const int32_t *idx, long idx_s
     return hipGetLastError();
 }
 
+static int tile_blocks(int tiles) { return tiles < kTileBlocks ? tiles : kTileBlocks; }
 static int bitmap_tiles(int N) { return ((N + 31) / 32 + kTileWords - 1) / kTileWords; }
 
 hipError_t launch_fill(int B, int N, int k, int R, int32_t *idx, long idx_stride, uint32_t *bitmap,
@@ -450,7 +466,7 @@ hipError_t launch_fill(int B, int N, int k, int R, int32_t *idx, long idx_stride
         hipError_t e = mark_picks(B, N, k, idx, idx_stride, bitmap, s);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_fill, dim3(tiles, B), dim3(1024), 0, s, N, k, R, idx, idx_stride, bitmap);
+    hipLaunchKernelGGL(k_fill, dim3(tile_blocks(tiles), B), dim3(1024), 0, s, N, tiles, k, R, idx, idx_stride, bitmap);
     return hipGetLastError();
 }
 
@@ -460,7 +476,8 @@ hipError_t launch_perm_candidates(const float *xyz, int B, int N, int Nc, int st
     const size_t words = (size_t)B * ((N + 31) / 32);
     hipLaunchKernelGGL(k_fill_zero, dim3(blocks_for(words)), dim3(kT), 0, s, bitmap, words);
     hipLaunchKernelGGL(k_perm_mark, dim3(blocks_for(Nc), B), dim3(kT), 0, s, N, Nc, seed, bitmap);
-    hipLaunchKernelGGL(k_perm_compact, dim3(bitmap_tiles(N), B), dim3(1024), 0, s, xyz, N, Nc, start, seed, bitmap, cand,
+    const int tiles = bitmap_tiles(N);
+    hipLaunchKernelGGL(k_perm_compact, dim3(tile_blocks(tiles), B), dim3(1024), 0, s, xyz, N, tiles, Nc, start, seed, bitmap, cand,
                        cxyz, spos);
     return hipGetLastError();
 }

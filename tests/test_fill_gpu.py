@@ -1,5 +1,6 @@
 """Candidate sets and fills of FPS-Prune at the edges of their tiles (32,768 points of the bitmap,
-4,096 places of the seeded permutation), whole numbers against the oracle."""
+4,096 places of the seeded permutation; beyond 256 tiles of the bitmap a block takes several), whole
+numbers against the oracle."""
 import numpy as np
 import pytest
 
@@ -9,7 +10,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("n,m,start,b", [(31, 9, 30, 3), (4096, 2048, 0, 2), (4097, 4097, 4096, 1), (32768, 900, 32767, 1),
-                                         (32769, 3000, 32768, 2), (65537, 700, 5, 1), (1100003, 300, 1100002, 1)])
+                                         (32769, 3000, 32768, 2), (65537, 700, 5, 1), (1100003, 300, 1100002, 1),
+                                         (8421377, 40, 8421376, 1)])
 @pytest.mark.parametrize("flags", [3, 7])
 def test_prune_at_the_edges_of_tiles(oracle, n, m, start, b, flags):
     import torch
