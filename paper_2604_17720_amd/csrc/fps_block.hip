@@ -29,7 +29,10 @@ namespace {
 constexpr int kBlockWaves = 8;
 constexpr int kBlockThreads = kBlockWaves * kWave;
 constexpr int kBlockUnits = kBlockThreads / 16;
-constexpr int kDigits = 64;  // six bits of the twelve of a 16^3 grid
+constexpr int kDigits = 64;   // six of the twelve bits of a key: of a 16^3 grid, or splitters and places between two
+constexpr int kCodeBits = 8;  // per axis, of the codes that have splitters
+constexpr int kSplitBits = 6, kSplitters = 1 << kSplitBits;
+static_assert(kSplitters == kDigits && kSplitters == kWave && kFramePoints == kWave, "a splitter per lane");
 static_assert(kDigits * kBlockWaves == kBlockThreads, "one counter per thread");
 constexpr int kBins = 4 * kBlockThreads;  // of pick values, in the final sort
 constexpr uint32_t kBinMax = 64;          // picks of a bin that are compared with one another
@@ -60,6 +63,9 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_fps_block(BlockArgs a) {
     __shared__ uint32_t bins[kBins];  // first the digits' counters, one set per wave
     uint32_t(*cnt)[kDigits] = reinterpret_cast<uint32_t(*)[kDigits]>(bins);
     __shared__ float wbox[kBlockWaves][6];
+    __shared__ Spread part[3];
+    __shared__ float per_code[kSplitters];
+    __shared__ uint32_t split[kSplitters];
     __shared__ uint32_t wsum[kBlockWaves], wtop[kBlockWaves];
     __shared__ __attribute__((aligned(16))) u32x4 recA[kBlockUnits];  // {~index, value, second value, x}
     __shared__ __attribute__((aligned(8))) u32x2 recB[kBlockUnits];   // {y, z}
@@ -124,9 +130,34 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_fps_block(BlockArgs a) {
             }
         const float side = fmaxf(fmaxf(hi[0] - lo[0], hi[1] - lo[1]), hi[2] - lo[2]);
         const float scale = side > 0.f ? 16.f / side : 0.f;
-        auto cell = [&](float v, float l) { return (uint32_t)fmaxf(0.f, fminf(15.f, (v - l) * scale)); };
+        const int sample = sample_index<kSplitBits>(lane, N);
+        if (fills_box(sx[sample], sx[kCap + sample], sx[2 * kCap + sample], lo, side)) {
+            auto cell = [&](float v, float l) { return (uint32_t)fmaxf(0.f, fminf(15.f, (v - l) * scale)); };
 #pragma unroll
-        for (int r = 0; r < P; ++r) code[r] = hilbert_code<4>(cell(rx[r], lo[0]), cell(ry[r], lo[1]), cell(rz[r], lo[2]));
+            for (int r = 0; r < P; ++r) code[r] = hilbert_code<4>(cell(rx[r], lo[0]), cell(ry[r], lo[1]), cell(rz[r], lo[2]));
+        } else {
+            if (wave < 3) {
+                const Spread s = spread_of(sx[wave * kCap + sample], lane);
+                if (lane == 0) part[wave] = s;
+            }
+            __syncthreads();
+            const Spread parts[3] = {part[0], part[1], part[2]};
+            const Frame f = frame_of(parts);
+            if (wave == 0) {
+                const uint32_t c = code_of<kCodeBits>(f, sx[sample], sx[kCap + sample], sx[2 * kCap + sample]);
+                const uint32_t key = wave_sort(c << kSplitBits | (uint32_t)lane, lane);
+                const uint32_t mine = lane ? key >> kSplitBits : 0u, up = (uint32_t)__shfl_down((int)(key >> kSplitBits), 1);
+                split[lane] = mine;
+                per_code[lane] = (float)kDigits / (float)((lane < 63 ? up : 1u << (3 * kCodeBits)) - mine);
+            }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < P; ++r) {
+                const uint32_t c = code_of<kCodeBits>(f, rx[r], ry[r], rz[r]);
+                const uint32_t s = splitter_of<kSplitBits>(split, c);
+                code[r] = s * kDigits + umin(kDigits - 1, (uint32_t)((float)(c - split[s]) * per_code[s]));
+            }
+        }
     }
     // Stable pass over six bits: elements keep the order of waves, rows and lanes.
     auto sort_pass = [&](const uint32_t (&el)[P], int shift) {

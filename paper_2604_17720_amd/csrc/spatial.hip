@@ -2,9 +2,10 @@
 // before it, the picks by (value descending, index ascending) after it.
 //
 // Points: 15-bit Hilbert codes of a 32^3 grid over the cloud (finer grids make no fewer rounds:
-// a unit of 98 points of the 200,000-point room covers about two cells), a radix sort of 8 and 7
-// bits.  Both passes are stable, so the order, and with it every round of the kernel, is the
-// same in each run.  Five launches: boxes of tiles; codes and counts of the low digit; low digit;
+// a unit of 98 points of the 200,000-point room covers about two cells) or, for a cloud that does not fill
+// its box, 15-bit keys that ascend with 30-bit codes (fps_space.h: 256 splitters, 128 places between two);
+// a radix sort of 8 and 7 bits.  Both passes are stable, so the order, and with it every round of the
+// kernel, is the same in each run.  Five launches: boxes of tiles; keys and counts of the low digit; low digit;
 // counts of the high digit in tiles of that order; high digit with the gather of the coordinates.
 // A block adds up the counts of all tiles itself instead of a scan of its own.  (The high digits
 // counted by the pass that moves the low ones, with an atomic in memory per point, took 256 us of
@@ -88,12 +89,66 @@ __global__ __launch_bounds__(kOT) void k_order_box(const float *__restrict__ xyz
     if (tid < 6) boxes[((size_t)b * tiles + t) * 6 + tid] = tid < 3 ? e.lo[tid] : e.hi[tid - 3];
 }
 
-// Codes, and how often each low digit occurs in a tile.
+// Frame and splitters of a cloud that does not fill its box, from one point of each of 256 stretches of it.
+// Every block finds the same ones by itself (about 3 us, in clouds of this kind alone).
+constexpr int kSplitBits = 8, kSplitters = 1 << kSplitBits, kPlaces = 128, kCodeBits = 10;  // code bits per axis
+static_assert(2 * kSplitters == kOT && kSplitters * kPlaces == kLowBins * kHighBins, "two threads per splitter; keys of two digits");
+struct Splits {
+    float co[3][kSplitters];
+    Spread part[3];
+    __attribute__((aligned(16))) uint32_t codes[kSplitters];
+    uint32_t rank[kSplitters];
+    uint32_t at[kSplitters + 1];  // the splitters
+    float per[kSplitters];        // places per code from one to the next
+};
+__device__ __forceinline__ Frame find_splitters(const float *__restrict__ p, int N, int tid, Splits &sh) {
+    const int lane = tid & 63, wave = tid >> 6, j = tid & (kSplitters - 1);
+    const float *q = p + (size_t)sample_index<kSplitBits>(j, N) * 3;
+    const float x = q[0], y = q[1], z = q[2];
+    if (tid < kSplitters) {
+        sh.co[0][j] = x; sh.co[1][j] = y; sh.co[2][j] = z;
+        sh.rank[j] = 0u;
+    }
+    __syncthreads();
+    if (wave < 3) {
+        const Spread s = spread_of(sh.co[wave][lane * (kSplitters / kFramePoints)], lane);
+        if (lane == 0) sh.part[wave] = s;
+    }
+    __syncthreads();
+    const Spread parts[3] = {sh.part[0], sh.part[1], sh.part[2]};
+    const Frame f = frame_of(parts);
+    // the last bits of a code tell equal ones apart
+    const uint32_t code = (code_of<kCodeBits>(f, x, y, z) & ~(uint32_t)(kSplitters - 1)) | (uint32_t)j;
+    if (tid < kSplitters) sh.codes[j] = code;
+    __syncthreads();
+    // a splitter's place: the two threads of it compare one half of the others each
+    const int h0 = tid < kSplitters ? 0 : kSplitters / 2;
+    uint32_t n = 0;
+#pragma unroll 8
+    for (int i = h0; i < h0 + kSplitters / 2; i += 4) {
+        const u32x4 o = *reinterpret_cast<const u32x4 *>(&sh.codes[i]);
+        n += (o.x < code ? 1u : 0u) + (o.y < code ? 1u : 0u) + (o.z < code ? 1u : 0u) + (o.w < code ? 1u : 0u);
+    }
+    atomicAdd(&sh.rank[j], n);
+    __syncthreads();
+    if (tid < kSplitters) sh.at[sh.rank[j]] = sh.rank[j] ? code : 0u;
+    if (tid == kSplitters) sh.at[kSplitters] = 1u << (3 * kCodeBits);
+    __syncthreads();
+    if (tid < kSplitters) sh.per[tid] = (float)kPlaces / (float)(sh.at[tid + 1] - sh.at[tid]);
+    __syncthreads();
+    return f;
+}
+
+// Keys, and how often each low digit occurs in a tile.
 __global__ __launch_bounds__(kOT) void k_order_code(const float *__restrict__ xyz, int N, int tiles, const float *__restrict__ boxes,
                                                     uint16_t *__restrict__ codes, uint32_t *__restrict__ hist) {
     __shared__ float sh[kOW][6];
     __shared__ uint32_t cnt[kLowBins];
+    __shared__ Splits sp;
     const int tid = threadIdx.x, t = blockIdx.x, b = blockIdx.y;
+    const float *p = xyz + (size_t)b * N * 3;
+    const float *q = p + (size_t)sample_index<kSplitBits>((tid & 63) * (kSplitters / kFramePoints), N) * 3;
+    const float qx = q[0], qy = q[1], qz = q[2];
     if (tid < kLowBins) cnt[tid] = 0;
     Ext e;
 #pragma unroll
@@ -111,14 +166,35 @@ __global__ __launch_bounds__(kOT) void k_order_code(const float *__restrict__ xy
     const float scale = side > 0.f ? 32.f / side : 0.f;
     int lo, hi;
     tile_range(N, tiles, t, lo, hi);
-    const float *p = xyz + (size_t)b * N * 3;
-    for (int i = lo + tid; i < hi; i += kOT) {
-        uint32_t c[3];
+    auto put = [&](int i, uint32_t key) {
+        codes[(size_t)b * N + i] = (uint16_t)key;
+        atomicAdd(&cnt[key & (kLowBins - 1)], 1u);
+    };
+    if (fills_box(qx, qy, qz, e.lo, side)) {
+        for (int i = lo + tid; i < hi; i += kOT) {
+            uint32_t c[3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) c[k] = (uint32_t)fmaxf(0.f, fminf(31.f, (p[3 * (size_t)i + k] - e.lo[k]) * scale));
-        const uint32_t code = hilbert_code<5>(c[0], c[1], c[2]);
-        codes[(size_t)b * N + i] = (uint16_t)code;
-        atomicAdd(&cnt[code & (kLowBins - 1)], 1u);
+            for (int k = 0; k < 3; ++k) c[k] = (uint32_t)fmaxf(0.f, fminf(31.f, (p[3 * (size_t)i + k] - e.lo[k]) * scale));
+            put(i, hilbert_code<5>(c[0], c[1], c[2]));
+        }
+    } else {
+        const Frame f = find_splitters(p, N, tid, sp);
+        constexpr int kTogether = 4;  // points of a thread whose searches do not wait for one another
+        for (int i0 = lo + tid; i0 < hi; i0 += kTogether * kOT) {
+            uint32_t code[kTogether], s[kTogether];
+#pragma unroll
+            for (int k = 0; k < kTogether; ++k) {
+                const float *v = p + 3 * (size_t)min(i0 + k * kOT, hi - 1);
+                code[k] = code_of<kCodeBits>(f, v[0], v[1], v[2]);
+            }
+#pragma unroll
+            for (int k = 0; k < kTogether; ++k) s[k] = splitter_of<kSplitBits>(sp.at, code[k]);
+#pragma unroll
+            for (int k = 0; k < kTogether; ++k) {
+                const uint32_t place = umin(kPlaces - 1, (uint32_t)((float)(code[k] - sp.at[s[k]]) * sp.per[s[k]]));
+                if (i0 + k * kOT < hi) put(i0 + k * kOT, s[k] * kPlaces + place);
+            }
+        }
     }
     __syncthreads();
     if (tid < kLowBins) hist[((size_t)b * tiles + t) * kLowBins + tid] = cnt[tid];
