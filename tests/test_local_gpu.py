@@ -13,37 +13,61 @@ def _dup(n, seed):
     return np.repeat(inputs.uniform_cube(n // 4, seed), 4, axis=0)
 
 
+def _outlier(n):
+    return np.concatenate([inputs.uniform_cube(n, 10), [[4e5, -3e5, 1e5]]]).astype(np.float32)[None]
+
+
+def _denser(n, seed):
+    """A cube in which a tenth of the points lies in a corner a thousand times as small."""
+    x = inputs.uniform_cube(n, seed)
+    x[: n // 10] *= 1e-3
+    return x
+
+
 CASES = {
-    # name: (clouds, M, start); a workgroup holds 512 points per row, 256 workgroups are the most
-    "smallest": (lambda: inputs.uniform_cube(4609, 1)[None], 4609, 4608),
+    # name: (clouds, M, start[, kernel, where it is another one]); a workgroup holds 512 points per row,
+    # 256 workgroups are the most; points x samples of 2^25 and about a hundred samples are the least
+    "smallest": (lambda: inputs.uniform_cube(4609, 1)[None], 4609, 4608, "GRID"),
     "smallest with the work for it": (lambda: inputs.uniform_cube(5793, 1)[None], 5793, 5792),
-    "just short of it": (lambda: inputs.uniform_cube(8192, 1)[None], 4095, 0),
+    "just short of it": (lambda: inputs.uniform_cube(8192, 1)[None], 4095, 0, "GRID"),
     "few samples, still enough": (lambda: inputs.uniform_cube(2097152, 5)[None], 128, 9),
-    "too few samples": (lambda: inputs.uniform_cube(2097152, 5)[None], 127, 9),
+    "too few samples": (lambda: inputs.uniform_cube(2097152, 5)[None], 127, 9, "GRID"),
     "twenty-four rows, exactly": (lambda: inputs.uniform_cube(3145728, 6)[None], 150, 3145727),
     "thirty-two rows": (lambda: inputs.uniform_cube(3145729, 6)[None], 90, 0),
     "forty rows": (lambda: inputs.room(4194305, 6)[None], 100, 77),
     "the most a device holds": (lambda: inputs.uniform_cube(5242880, 7)[None], 80, 5242879),
-    "beyond it": (lambda: inputs.uniform_cube(5242881, 7)[None], 80, 5),
+    "beyond it": (lambda: inputs.uniform_cube(5242881, 7)[None], 80, 5, "STREAM"),
     "a row of units and one point": (lambda: inputs.room(65537, 2)[None], 513, 65536),
-    "more clouds than a launch, enough work": (lambda: np.stack([inputs.planes_and_clusters(9001, i) for i in range(15)]), 3728, 3),
+    "as many clouds as fit one launch": (lambda: np.stack([inputs.planes_and_clusters(9001, i) for i in range(15)]), 3728, 3),
+    "two launches, the second one short": (lambda: np.stack([inputs.uniform_cube(300001, i) for i in range(20)]), 112, 4),
+    "a launch per cloud": (lambda: np.stack([inputs.uniform_cube(2700001, i) for i in range(2)]), 150, 2700000),
     "a long line": (lambda: inputs.lattice_line(6000)[None], 6000, 0),
     "duplicates, fewer points than many samples": (lambda: _dup(16000, 8)[None], 5000, 0),
     "one row, exactly": (lambda: inputs.room(131072, 2)[None], 3000, 7),
     "one point more": (lambda: inputs.room(131073, 2)[None], 3000, 131072),
     "three rows and one point": (lambda: inputs.uniform_cube(393217, 3)[None], 500, 0),
     "many rows": (lambda: inputs.uniform_cube(1600001, 4)[None], 200, 5),
-    "largest": (lambda: inputs.uniform_cube(3145728, 5)[None], 60, 9),
-    "more clouds than fit one launch": (lambda: np.stack([inputs.uniform_cube(4700, i) for i in range(270)]), 90, 3),
-    "clusters": (lambda: np.stack([inputs.planes_and_clusters(5003, i) for i in range(37)]), 600, 1),
-    "one pick": (lambda: inputs.uniform_cube(5000, 6)[None], 2, 0),
+    "largest": (lambda: inputs.uniform_cube(3145728, 5)[None], 60, 9, "GRID"),
+    "many clouds of few samples": (lambda: np.stack([inputs.uniform_cube(4700, i) for i in range(270)]), 90, 3, "BLOCK"),
+    "clusters in many clouds": (lambda: np.stack([inputs.planes_and_clusters(5003, i) for i in range(37)]), 600, 1, "BLOCK"),
+    "clusters": (lambda: np.stack([inputs.planes_and_clusters(9001, 50 + i) for i in range(4)]), 4000, 1),
+    "one pick": (lambda: inputs.uniform_cube(5000, 6)[None], 2, 0, "GRID"),
     "equal values, bins too large for one sort in LDS": (lambda: inputs.lattice_grid(60, 60, 12)[None], 20000, 0),
-    "a line": (lambda: inputs.lattice_line(5000)[None], 5000, 0),
-    "duplicates, fewer points than samples": (lambda: _dup(16000, 8)[None], 5000, 0),
-    "one place": (lambda: np.ones((1, 6000, 3), np.float32), 100, 3),
-    "distances beyond fp32": (lambda: (inputs.uniform_cube(5000, 9) * 3e38).astype(np.float32)[None], 400, 0),
-    "distances below the normal numbers": (lambda: (inputs.uniform_cube(5000, 9) * 3e-20).astype(np.float32)[None], 400, 0),
-    "an outlier": (lambda: np.concatenate([inputs.uniform_cube(9000, 10), [[4e5, -3e5, 1e5]]]).astype(np.float32)[None], 2000, 1),
+    "a line": (lambda: inputs.lattice_line(5000)[None], 5000, 0, "GRID"),
+    "duplicates, fewer points than samples": (lambda: _dup(24000, 8)[None], 7000, 0),
+    "one place, few samples": (lambda: np.ones((1, 6000, 3), np.float32), 100, 3, "GRID"),
+    "one place": (lambda: np.ones((1, 6000, 3), np.float32), 5700, 3),
+    "one place but for two points": (lambda: np.concatenate([np.zeros((6000, 3)), [[1, 2, 3], [-1, 0, 2]]]).astype(np.float32)[None], 5700, 3),
+    "distances beyond fp32, few samples": (lambda: (inputs.uniform_cube(5000, 9) * 3e38).astype(np.float32)[None], 400, 0, "GRID"),
+    "distances beyond fp32": (lambda: (inputs.uniform_cube(6000, 9) * 3e38).astype(np.float32)[None], 5700, 0),
+    "some distances beyond fp32": (lambda: (inputs.uniform_cube(9000, 9) * 1.4e19).astype(np.float32)[None], 4000, 8),
+    "distances below the normal numbers, few samples": (lambda: (inputs.uniform_cube(5000, 9) * 3e-20).astype(np.float32)[None], 400, 0, "GRID"),
+    "distances below the normal numbers": (lambda: (inputs.uniform_cube(6000, 9) * 3e-20).astype(np.float32)[None], 5700, 0),
+    "distances that round to 0": (lambda: (inputs.uniform_cube(6000, 9) * 1e-22).astype(np.float32)[None], 5700, 0),
+    "an outlier, few samples": (lambda: _outlier(9000), 2000, 1, "GRID"),
+    "an outlier": (lambda: _outlier(9000), 6000, 1),
+    "an outlier, most points left": (lambda: _outlier(40000), 1000, 40000),
+    "places of different density": (lambda: _denser(20000, 3)[None], 8000, 0),
 }
 
 
@@ -52,15 +76,62 @@ def test_local_maxima_give_the_samples_of_the_greedy_loop(oracle, name):
     import torch
 
     import paper_2604_17720_amd.binding as fb
-    make, m, start = CASES[name]
+    make, m, start, *other = CASES[name]
     x = np.ascontiguousarray(make(), dtype=np.float32)
     print(name, x.shape, m, start, flush=True)
+    assert fb.ffps_describe_kernel(x.shape[0], x.shape[1], m) == getattr(fb, "FFPS_KERNEL_" + (other[0] if other else "LOCAL"))
     ws = fb.make_workspace(x.shape[0], x.shape[1], m)
     idx, md = fb.ffps_exact(torch.from_numpy(x).cuda(), m, start, return_maxdist=True, workspace=ws)
     assert fb.ffps_last_status(ws) == 0
     ref, rmd = oracle.fps_exact(x, m, start, return_maxdist=True)
     assert np.array_equal(idx.cpu().numpy(), ref.reshape(idx.shape))
     assert np.array_equal(md.cpu().numpy().view(np.uint32), rmd.reshape(md.shape).view(np.uint32))
+
+
+def test_more_clouds_than_workgroups(oracle):
+    """258 clouds, one workgroup each: two launches.  All against the grid kernel, some against the oracle."""
+    import torch
+
+    import paper_2604_17720_amd.binding as fb
+    b, n, m = 258, 8193, 4097
+    assert fb.ffps_describe_kernel(b, n, m) == fb.FFPS_KERNEL_LOCAL
+    x = np.stack([inputs.uniform_cube(n, 300 + i) if i % 2 else inputs.shape_cloud(n, 300 + i) for i in range(b)])
+    xd, ws = torch.from_numpy(x).cuda(), fb.make_workspace(b, n, m)
+    got, md = fb.ffps_exact(xd, m, 11, return_maxdist=True, workspace=ws)
+    assert fb.ffps_last_status(ws) == 0
+    ref, rmd = fb.ffps_exact(xd, m, 11, fb.FFPS_VARIANT_GRID, return_maxdist=True)
+    assert torch.equal(got, ref) and torch.equal(md, rmd)
+    for i in (0, 255, 256, 257):
+        assert np.array_equal(got[i].cpu().numpy(), oracle.fps_exact(x[i], m, 11))
+
+
+@pytest.mark.parametrize("flags", [3, 7])
+def test_candidates_sampled_by_local_maxima(oracle, flags):
+    """FPS-Prune whose candidates go to the kernel; drawn ones (7) have a first sample of their own per cloud."""
+    import torch
+
+    import paper_2604_17720_amd.binding as fb
+    n, m = 24000, 6000
+    assert fb.ffps_describe_kernel(3, n // 2, m // 2) == fb.FFPS_KERNEL_LOCAL
+    x = np.stack([inputs.planes_and_clusters(n, 80 + i) for i in range(3)])
+    ws = fb.make_workspace(3, n, m)
+    got, k = fb.ffps_prune(torch.from_numpy(x).cuda(), m, 1, 2, flags, 777, workspace=ws, seed=5)
+    assert fb.ffps_last_status(ws) == 0 and k == m // 2
+    assert np.array_equal(got.cpu().numpy(), oracle.fps_prune(x, m, 1, 2, flags, 777, 5))
+
+
+@pytest.mark.parametrize("n,m", [(45678, 1501), (400000, 120)])  # the kernel's area fits the library's array, and does not
+def test_local_maxima_without_a_workspace(oracle, n, m):
+    import torch
+
+    import paper_2604_17720_amd.binding as fb
+    assert fb.ffps_describe_kernel(1, n, m) == fb.FFPS_KERNEL_LOCAL
+    x = inputs.room(n, 21)
+    out = torch.empty((1, m), dtype=torch.int32, device="cuda")
+    st = torch.empty(2, dtype=torch.int32, device="cuda")
+    fb.ffps_exact_noalloc(torch.from_numpy(x).cuda(), m, out, 3, out_status=st)
+    assert st[0].item() == 0 and st[1].item() > 0
+    assert np.array_equal(out[0].cpu().numpy(), oracle.fps_exact(x, m, 3))
 
 
 def test_auto_in_a_hip_graph(oracle):
