@@ -177,28 +177,46 @@ int resolve_variant(int B, int N, int variant, const Device &dev) {
 
 // Which kernel AUTO takes (clouds of at most 256 points: one wave, one pick per pass).
 //
-// k_fps_block against k_fps_wgm, one cloud: 1024 points to 512 in 73 against 115 us, 4608 to 2304
-// in 400 against 638.  Beyond 4608 points it needs 12 or 16 points per lane and a cloud is
-// faster on many CUs (6144 to 1536: 364 against 340 us), unless there are many clouds, which
-// then wait for one another: 64 x 8192 to 1024 in 379 against 491 us.
+// k_fps_block against k_fps_wgm, one cloud, uniform / planes / a stretch of a LiDAR frame: 1024 points
+// to 512 in 79, 70 against 121, 119 us; 4096 to 1024 in 198, 230 against 336, 364; 4608 to 2304 in
+// 379, 400, 705 against 639, 646, 705 us.  Beyond 4608 points it needs 12 or 16 points per lane and a cloud
+// is faster on many CUs, unless there are many, which then wait for one another: 8192 points to 4096,
+// 64 clouds 853, 963, 1667 against 1346, 1376, 1479 us of k_fps_grid, 80 clouds 850, 963, 1672 against 1717, 1850, 1974.
 constexpr int kOneWaveMax = kWaveCapacity;
 constexpr int kBlockMax = 4608;
-constexpr int kBlockManyClouds = 32;
+constexpr int kBlockManyClouds = 80;
 bool takes_block(int B, int N) {
     return N > kOneWaveMax && (N <= kBlockMax || (N <= block_capacity() && B >= kBlockManyClouds));
 }
-// k_fps_local has a dearer start (two sorts, about 140 us in all) and more rounds as long as the
-// samples are few; its rounds do not grow with the points.  Measured with 1 to 128 clouds the two
-// meet at: 8192 points to 4096 (624 against 641 us), 12,000 to 3000 (479, 468), 16,384
-// to 1400, 24,000 to 1500 (402, 402), eight clouds of 16,384 to 1700: near points x samples = 2^25.
-// The sorts grow with the points, so a hundred samples or so are too few for them in the end: a
-// million points to 34 in 320 against 281 us.  Beyond the registers' 3.1 million points, where
-// k_fps_grid gives way to k_fps_stream, the two meet near 80 samples (four million uniform points
-// to 64: 655 against 618 us, to 128: 747, 846; a room of five million to 64: 790, 1042; to 1024: 1240, 4711).
-// The sorts around it put the cloud number in gridDim.y: more clouds than that stay with k_fps_grid,
-// which takes them in batches.
-bool takes_local(int B, int N, int M, int v) {
-    return B <= kMaxBatchHelpers && (long)N * M >= kLocalWork && M >= (v == FFPS_VARIANT_STREAM ? kLocalSamples : 96 + N / 65536);
+// k_fps_local against k_fps_grid: it has a dearer start (two sorts, 50 us in all at 45,678 points, 95 at 200,000) and
+// more rounds as long as the samples are few; its rounds do not grow with the points.  One to
+// eight clouds, uniform / planes / LiDAR, in us: 8192 points to 4096 548, 579, 640 against 584, 642, 677;
+// 12,000 to 1500 359, 366, 399 against 333, 362, 441, to 2800 423, 443, 499 against 458, 506, 581; 24,000 to
+// 1400 351, 369, 396 against 371, 411, 494; 60,000 to 560 334, 342, 308 against 340, 451, 525: points x samples = 2^25.
+// The sorts grow with the points, and uniform clouds gain least: 100,000 to 336 361 against 308, to
+// 800 404 against 406; 200,000 to 168 348 against 289, to 512 408 against 396; a million to 300 490 against 470.
+// Rooms and LiDAR frames gain half as much again there (100,000 to 600: 326 and 340 against 460 and 610), so the line
+// beyond 65,536 points is 2^26.  Beyond the registers' 3.1 million points, where k_fps_grid gives way to
+// k_fps_stream, the two meet near 80 samples (four million uniform points to 80: 673 against 738 us, five million to
+// 64: 886 against 769, to 128: 972 against 1086; a room of five million to 64: 747 against 1168).
+// Clouds of long tails are the ones that lose: normally distributed points need four to ten times the
+// samples (200,000 to 2048 707 against 527 us, a million to 2048 742 against 887).
+//
+// Many clouds leave each few workgroups, and what is gained shrinks, for LiDAR stretches first: 12 clouds of
+// 30,000 to 7500 812, 890, 1591 against 1310, 1405, 1687; 16 clouds (16 workgroups each) of 16,384 to 4096 668, 717,
+// 848 against 804, 834, 967, but of 30,000 to 7500 982, 1069, 1970 against 1554, 1613, 1860; 32 of 9000 to 4500 925, 974, 1454 against 930, 999, 1071; 64 of 30,000 to 7500 3117, 3522,
+// 6051 against 4625, 4732, 5154, to 15,000 5283, 5955, 9111 against 8798, 8940, 9377: from 12 x 2^25 on.
+// The sorts put the cloud number in gridDim.y: more clouds than that stay with k_fps_grid, which takes
+// them in batches.
+constexpr long kLocalWorkLarge = 1L << 26;  // beyond 65,536 points
+constexpr long kLocalWorkMany = 3L << 27;   // many clouds
+bool takes_local(int B, int N, int M, int v, int num_cu) {
+    const long work = (long)N * M;
+    if (B > kMaxBatchHelpers || work < kLocalWork || M < kLocalSamples) return false;
+    if (v == FFPS_VARIANT_STREAM) return true;
+    const int share = (num_cu < kMaxGridWG ? num_cu : kMaxGridWG) / B;  // workgroups of a cloud
+    if (B > 1 && (share < 16 || (share == 16 && N > 1024 * share))) return work >= kLocalWorkMany;
+    return work >= (N > 65536 ? kLocalWorkLarge : kLocalWork) && M >= 96 + N / 65536;
 }
 
 // Clouds that are rows of a larger array: point i of cloud b is row idx[b][i] of [B][points]
@@ -224,7 +242,7 @@ int kernel_for(int B, int N, int M, int variant, const Device &dev, size_t local
     if (takes_wave(N, v)) return FFPS_KERNEL_WAVE;
     if (any_rounds(M, variant) && takes_block(B, N)) return FFPS_KERNEL_BLOCK;
     if (v == FFPS_VARIANT_WG) return FFPS_KERNEL_WG;
-    if (any_rounds(M, variant) && takes_local(B, N, M, v)) {
+    if (any_rounds(M, variant) && takes_local(B, N, M, v, dev.num_cu)) {
         const LocalPlan plan = plan_fps_local(B, N, dev.num_cu);
         size_t bytes = 0;
         if (plan.wg_per_cloud > 0) {

@@ -26,8 +26,8 @@ CASES = {
     "seven per lane": (lambda: _shape(2, 3073), 900, 3072),
     "eight per lane, exactly": (lambda: _shape(2, 4096), 4096, 5),
     "largest of a workgroup": (lambda: _shape(2, 4608), 4608, 4607),
-    "many clouds, twelve per lane": (lambda: _shape(32, 4609), 300, 4608),
-    "many clouds, sixteen per lane": (lambda: _shape(33, 8192), 400, 8191),
+    "many clouds, twelve per lane": (lambda: _shape(80, 4609), 300, 4608),
+    "many clouds, sixteen per lane": (lambda: _shape(81, 8192), 400, 8191),
     "more clouds than CUs": (lambda: _shape(300, 700), 90, 2),
     "planes": (lambda: np.stack([inputs.planes_and_clusters(4001, i) for i in range(5)]), 1500, 1),
     "lattice, many equal values": (lambda: inputs.lattice_grid(16, 16, 12)[None], 2000, 0),
@@ -48,6 +48,7 @@ def test_one_workgroup_gives_the_samples_of_the_greedy_loop(oracle, name):
     make, m, start = CASES[name]
     x = np.ascontiguousarray(make(), dtype=np.float32)
     print(name, x.shape, m, start, flush=True)
+    assert fb.ffps_describe_kernel(x.shape[0], x.shape[1], m) == fb.FFPS_KERNEL_BLOCK
     ws = fb.make_workspace(x.shape[0], x.shape[1], m)
     idx, md = fb.ffps_exact(torch.from_numpy(x).cuda(), m, start, return_maxdist=True, workspace=ws)
     assert fb.ffps_last_status(ws) == 0

@@ -14,8 +14,8 @@ def test_the_kernels_of_the_sizes():
     assert kernel(1, 1024, 512, fb.FFPS_VARIANT_WG) == fb.FFPS_KERNEL_WG
     assert kernel(1, 1024, 512, fb.variant_with_picks(0, 7)) == fb.FFPS_KERNEL_WG
     assert kernel(1, 4608, 9) == fb.FFPS_KERNEL_BLOCK
-    assert kernel(32, 8192, 9) == fb.FFPS_KERNEL_BLOCK
-    assert kernel(31, 8192, 9) == fb.FFPS_KERNEL_GRID
+    assert kernel(80, 8192, 9) == fb.FFPS_KERNEL_BLOCK
+    assert kernel(79, 8192, 9) == fb.FFPS_KERNEL_GRID
     assert kernel(1, 200000, 50000) == fb.FFPS_KERNEL_LOCAL
     assert kernel(1, 200000, 50000, fb.FFPS_VARIANT_GRID) == fb.FFPS_KERNEL_GRID
     assert kernel(1, 5000011, 1024) == fb.FFPS_KERNEL_LOCAL
@@ -29,9 +29,24 @@ def test_the_kernels_of_the_sizes():
 def test_more_clouds_than_a_grid_dimension_holds():
     """The sorts around the local-maximum kernel have a grid row per cloud, at most 65535: exact
     sampling of more clouds than that (it has no limit on them) goes through the grid kernel."""
-    assert kernel(65535, 8193, 4097) == fb.FFPS_KERNEL_LOCAL
-    assert kernel(65536, 8193, 4097) == fb.FFPS_KERNEL_GRID
-    assert kernel(65536, 30000, 30000) == fb.FFPS_KERNEL_GRID
+    assert kernel(65535, 30000, 20000) == fb.FFPS_KERNEL_LOCAL
+    assert kernel(65536, 30000, 20000) == fb.FFPS_KERNEL_GRID
+    assert kernel(65536, 8193, 8193) == fb.FFPS_KERNEL_GRID
+
+
+def test_few_samples_and_many_clouds_stay_with_rounds_of_candidates():
+    """Where picks by local maxima were measured to be slower than the kernel they replaced: few
+    samples of many points, and many clouds, each of which has only few workgroups then."""
+    local, grid = fb.FFPS_KERNEL_LOCAL, fb.FFPS_KERNEL_GRID
+    assert [kernel(1, n, m) for n, m in ((65536, 512), (65537, 512), (100000, 336), (100000, 672), (200000, 335), (200000, 336))] == \
+        [local, grid, grid, local, grid, local]
+    assert kernel(1, 3145729, 80) == local and kernel(1, 3145729, 79) == fb.FFPS_KERNEL_STREAM
+    assert [kernel(b, 30000, 7500) for b in (1, 8, 15, 16, 64)] == [local, local, local, grid, grid]
+    assert [kernel(b, 16384, 4096) for b in (16, 17, 256)] == [local, grid, grid]
+    assert [kernel(b, 30000, 15000) for b in (16, 128)] == [local, local]
+    assert [kernel(b, 8192, 4096) for b in (1, 16, 17, 79)] == [local, local, grid, grid]
+    # a device with fewer CUs
+    assert kernel(8, 30000, 7500, num_cu=64) == grid and kernel(4, 16384, 4096, num_cu=64) == local
 
 
 def test_a_workspace_sized_for_other_clouds():
