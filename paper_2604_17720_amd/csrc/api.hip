@@ -199,8 +199,9 @@ bool takes_block(int B, int N) {
 // beyond 65,536 points is 2^26.  Beyond the registers' 3.1 million points, where k_fps_grid gives way to
 // k_fps_stream, the two meet near 80 samples (four million uniform points to 80: 673 against 738 us, five million to
 // 64: 886 against 769, to 128: 972 against 1086; a room of five million to 64: 747 against 1168).
-// Clouds of long tails are the ones that lose: normally distributed points need four to ten times the
-// samples (200,000 to 2048 707 against 527 us, a million to 2048 742 against 887).
+// Clouds of long tails are the ones that lose, whose far points are most of the samples and lie in few units:
+// 200,000 normally distributed points to 2048 take 575 against 527 us (a million to 2048 748 against 891), 300,000
+// points of which five in a hundred lie around the others at up to 100 times the extent, to 16,384, 3150 against 2210.
 //
 // Many clouds leave each few workgroups, and what is gained shrinks, for LiDAR stretches first: 12 clouds of
 // 30,000 to 7500 812, 890, 1591 against 1310, 1405, 1687; 16 clouds (16 workgroups each) of 16,384 to 4096 668, 717,

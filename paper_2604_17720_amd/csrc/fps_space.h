@@ -98,7 +98,10 @@ struct Frame {
 };
 constexpr int kFramePoints = 64;  // points that are looked at, one per lane
 constexpr int kFrameCells = 16;   // cells of the longest side of the box, per axis ...
-constexpr int kFrameFilled = 9;   // ... and how many of them these points fill, on the best axis, where a grid will do
+// ... and how many of them these points fill, on the best axis, where a grid will do.  Cubes, rooms, planes and
+// surfaces fill 14 to 16; with 9 here instead, normally distributed points and some LiDAR frames still had the
+// grid: 300,000 points to 16,384 took 1642 and 1554 us, 1061 and 918 with 13.
+constexpr int kFrameFilled = 13;
 
 // Whether a grid over the box (lowest corner, longest side) will do, judged by 64 points, one per lane.
 __device__ __forceinline__ bool fills_box(float x, float y, float z, const float (&low)[3], float side) {
