@@ -4,8 +4,9 @@
 // What bounds a cloud this small is the number of instructions of a round (with two waves on a
 // SIMD an instruction costs about eight cycles).  k_fps_wgm takes 20 to 30 picks a round but
 // needs about 12,000 cycles for it: pairwise masks of 64 candidates, one wave that settles them,
-// and every pick applied to every point.  Here a round has ten picks and 2700 cycles (1024 points):
-//   - The points are put along a space-filling curve (two stable radix passes in LDS); a UNIT
+// and every pick applied to every point.  Here a round has ten picks and takes 1.2 us (1024 points):
+//   - The points are put along a space-filling curve (two stable radix passes in LDS, by cells of a
+//     grid over the cloud or, where that would not do, by splitters: fps_space.h); a UNIT
 //     is a row of 16 lanes with P points each, 32 units in eight waves, so that everything a
 //     unit does is done for the four units of a wave by the same instructions and a
 //     reduction is four DPP steps.  (64 units in sixteen waves make 0.7 times the rounds, but
@@ -16,8 +17,8 @@
 //     Picks near the unit's box are applied, two at a time.
 //   - Once there are as many picks as samples, a round counts the picks above the largest
 //     value that is left; when these are enough it is the last.
-// Measured against k_fps_wgm, one cloud: 1024 points to 512 in 74 us (56 rounds), 110 before;
-// 4096 to 1024 in 209 us (113 rounds), 342 before; 4608 to 2304 in 400 us, 638 before.
+// Measured against k_fps_wgm, one cloud of planes and clusters: 1024 points to 512 in 70 us (54 rounds),
+// 119 there; 4096 to 1024 in 230 us (119 rounds), 364 there; 4608 to 2304 in 400 us (198 rounds), 646 there.
 #include "fps_exchange.h"
 #include "fps_block.h"
 #include "fps_space.h"
@@ -280,7 +281,7 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_fps_block(BlockArgs a) {
     const int base = (wave * 4 + kBlockUnits - 6) & (kBlockUnits - 1);
     const int u0 = (base + l16) & (kBlockUnits - 1), u1 = u0 ^ 16;
     const Box b0 = ubox[u0], b1 = ubox[u1];
-    const uint32_t g0 = f2u(box_box(box, b0)), g1 = f2u(box_box(box, b1));  // not above the distance of any two of their points
+    const uint32_t g1 = f2u(box_box(box, b1));  // not above the distance of any two of their points
     report();
 
     // ---- rounds ----
@@ -373,7 +374,7 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_fps_block(BlockArgs a) {
     // ---- the picks in their order ----
     // Into bins over the range of their values, largest first; a pick's place is that of its bin
     // plus the picks of the bin before it.  (The bitonic sort below, for many picks of nearly one
-    // value, takes 14 of the 87 us of a cloud of 1024 points by itself.)
+    // value, takes 14 us of a cloud of 1024 points by itself.)
     __syncthreads();
     uint64_t *binned = keys + kCap;
     uint32_t vlo = 0xffffffffu, vhi = 0u;

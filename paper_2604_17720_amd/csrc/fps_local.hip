@@ -14,15 +14,16 @@
 //
 // Where the time of the loop in fps_grid.hip goes into rounds of about a hundred picks each
 // (462 for 50,000 of 200,000 points) and into applying every pick to every point, here a
-// round makes as many picks as there are separate maxima (360 on average, 167 rounds)
+// round makes as many picks as there are separate maxima (348 on average, 169 rounds)
 // and a pick is applied where it can matter: about 130 distances per point, not 50,000.
 // What is left is the latency of a round, which is what everything below is about.
 //
 //   - Points are sorted along a space-filling curve first (spatial.hip); a UNIT, one
 //     wave, holds a stretch of it in registers (up to 40 rows of 64 points), eight units
-//     make a workgroup.  From 24 rows on some values of the slots below are spilled (40 rows: about
-//     250 registers); with the boxes in LDS, records gathered two slots at a time and the rows
-//     kept in their order (few_rows) a round of five million points takes 10 us, 21 without.
+//     make a workgroup.  From 12 rows on registers are spilled: 6 there, 32 at 16 rows, 52 at 24,
+//     149 at 32 and 228 at 40 (compiled with the build's flags).  With the boxes in LDS, records gathered two
+//     slots at a time and the rows kept in their order (few_rows), all beyond 16 rows, a round of
+//     five million points takes 10 us, 21 without.
 //   - Per round a unit publishes its best point (value, index, coordinates), the value of
 //     its second best, and whether the candidate it published the round before was picked:
 //     32 bytes.  Every lane reads the records of up to four units, eight lanes for a
@@ -36,11 +37,12 @@
 //     small and its best lies outside.
 //   - A workgroup stops when as many picks as samples have values in bins above that
 //     of its largest value: nothing it holds can belong to the samples any more.  Picks
-//     beyond the samples (10 to 15 % of them) are left out by the final sort (spatial.hip).
+//     beyond the samples are left out by the final sort (spatial.hip): 18 % more than the 50,000 of a
+//     room, 45 % more than 5001 of 45,678, 37 % more than 16,384 of a LiDAR frame.
 //
 // Measured, exact FPS of a room of 200,000 points to 50,000 samples, sorts included:
 // 0.82 ms against 4.44 ms with k_fps_grid; 45,678 points to 5,001: 0.42 against 0.84 ms;
-// five million to 1024: 1.22 ms against 4.71 ms with k_fps_stream.
+// five million to 1024: 1.2 ms against 4.7 ms with k_fps_stream.
 //
 // Every wait is bounded as in fps_exchange.h.  A point that is picked twice (coordinates that are not
 // finite) ends the workgroup with the status of inconsistent results; those that wait for it look at the
@@ -230,7 +232,7 @@ __device__ __forceinline__ Best unit_best(const float (&x)[P], const float (&y)[
 }
 
 // Rows up to which the records of four slots are gathered at once; beyond, the registers that
-// takes are dearer than a second wait.
+// takes are dearer than a second wait (at 24 to 40 rows; 12 and 16 rows, which spill a few, were not tried).
 constexpr int kGatherRows = 16;
 
 template <int P>

@@ -423,10 +423,6 @@ hipError_t launch_fps_wg(const float *xyz, int B, int N, int M, int start, const
 #define FFPS_WG_CASE(NT, P) \
     if (N <= (NT) * (P))    \
         return launch_wg_t<NT, P>(xyz, B, N, M, start, start_dev, idx, idx_stride, md, md_stride, s);
-    if (N <= kWaveCapacity) {
-        const BlockArgs a = {xyz, N, nullptr, 0, N, M, start, start_dev, idx, idx_stride, md, md_stride, status, false};
-        return launch_fps_wave(a, B, s);
-    }
     if (N <= wgm_capacity()) {
         WgmArgs a;
         a.xyz = xyz; a.N = N; a.M = M; a.start = start; a.start_dev = start_dev;
