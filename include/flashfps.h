@@ -128,7 +128,9 @@ int ffps_exact(const float *d_xyz, int B, int N, int M, int start_idx, int varia
  * no workspace and allocates nothing.  What the kernels need besides inputs and
  * outputs (the status block and the exchange areas of one launch, 12 MiB + 256
  * bytes) lives in an array inside the library's device image; every GPU the
- * library runs on holds its copy until the process ends.
+ * library runs on holds its copy until the process ends.  AUTO takes the
+ * local-maximum kernel where its area fits there, too (one cloud of up to about
+ * 350,000 points), and the GRID kernel otherwise.
  *   arguments   as ffps_exact, without d_ws / ws_bytes
  *   d_status    out  int32[2] on the device, or NULL: {status word, rounds} of
  *                    this call, readable through ffps_last_status(d_status, stream)

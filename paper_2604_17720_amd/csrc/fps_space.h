@@ -103,7 +103,7 @@ constexpr int kFrameCells = 16;   // cells of the longest side of the box, per a
 // grid: 300,000 points to 16,384 took 1642 and 1554 us, 1061 and 918 with 13.
 constexpr int kFrameFilled = 13;
 
-// Whether a grid over the box (lowest corner, longest side) will do, judged by 64 points, one per lane.
+// Whether a grid over the box (lowest corner, longest side) will do, decided by 64 points, one per lane.
 __device__ __forceinline__ bool fills_box(float x, float y, float z, const float (&low)[3], float side) {
     const float per = side > 0.f ? (float)kFrameCells / side : 0.f;
     auto bit = [&](float v, int k) { return 1u << (uint32_t)fmaxf(0.f, fminf((float)(kFrameCells - 1), (v - low[k]) * per)); };
