@@ -11,14 +11,19 @@
 //     unit does is done for the four units of a wave by the same instructions and a
 //     reduction is four DPP steps.  (64 units in sixteen waves make 0.7 times the rounds, but
 //     the pairwise tests are four times as many.)
-//   - Every unit puts its best point and the value of its second best into LDS; a lane tests
-//     the unit's candidate against two units, a row against all of them.
+//   - Every unit puts its two best points and a bound of the values of all others into LDS; a lane tests
+//     the unit's candidate against two units, a row against all of them.  (With the value of the second
+//     alone, 57 rounds in place of 48 for 1024 points to 512, 126 in place of 100 for 4096 to 1024, each 12 to 17 %
+//     shorter: 76 us against 73, 239 against 214.  With one point per lane it is still that way: the second
+//     made no fewer rounds of 300 and 512 points, and 2 % of the time.)
 //   - Every unit has a slot for its pick (value 0: none), so a round needs two barriers.
-//     Picks near the unit's box are applied, two at a time.
+//     Picks near the unit's box are applied, two at a time.  All waves see all slots, so each counts
+//     the picks for itself (an atomic in LDS, and looking at half of the units only where the boxes
+//     of the others are near, which one of a wave's lanes always was: 75 us in place of 73).
 //   - Once there are as many picks as samples, a round counts the picks above the largest
 //     value that is left; when these are enough it is the last.
-// Measured against k_fps_wgm, one cloud of planes and clusters: 1024 points to 512 in 70 us (54 rounds),
-// 119 there; 4096 to 1024 in 230 us (119 rounds), 364 there; 4608 to 2304 in 400 us (198 rounds), 646 there.
+// Measured against k_fps_wgm, one cloud of planes and clusters (before the second points): 1024 points to 512 in 70 us
+// (54 rounds), 119 there; 4096 to 1024 in 230 us (119 rounds), 364 there; 4608 to 2304 in 400 us (198 rounds), 646 there.
 #include "fps_exchange.h"
 #include "fps_block.h"
 #include "fps_space.h"
@@ -58,6 +63,7 @@ __device__ __forceinline__ uint64_t key_of(const u32x4 &rec) { return ((uint64_t
 template <int P>
 __global__ __launch_bounds__(kBlockThreads, 2) void k_fps_block(BlockArgs a) {
     constexpr int kCap = kBlockThreads * P;
+    constexpr bool kTwo = P > 1;  // units report their second points
     // coordinates by index and the order, later the keys of the picks
     __shared__ __attribute__((aligned(16))) float sx[4 * kCap];
     uint32_t *order = reinterpret_cast<uint32_t *>(sx + 3 * kCap);
@@ -70,9 +76,10 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_fps_block(BlockArgs a) {
     __shared__ uint32_t wsum[kBlockWaves], wtop[kBlockWaves];
     __shared__ __attribute__((aligned(16))) u32x4 recA[kBlockUnits];  // {~index, value, second value, x}
     __shared__ __attribute__((aligned(8))) u32x2 recB[kBlockUnits];   // {y, z}
+    __shared__ __attribute__((aligned(16))) u32x4 recC[kBlockUnits];  // {x, y, z} of the second, a bound of all others
     __shared__ __attribute__((aligned(16))) u32x4 pick_of[kBlockUnits + 1];  // {x, y, z, value}, the last one never a pick
     __shared__ Box ubox[kBlockUnits];
-    __shared__ uint32_t s_above[2], s_np;  // picks above what is left, picks
+    __shared__ uint32_t s_above[2];  // picks above what is left
     static_assert(sizeof(sx) >= pow2_above(kCap) * sizeof(uint64_t), "keys take the coordinates' place");
     uint64_t *keys = reinterpret_cast<uint64_t *>(sx);
 
@@ -231,7 +238,6 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_fps_block(BlockArgs a) {
     }
     if (l16 == 0) ubox[unit] = box;
     if (tid < 2) s_above[tid] = 0;
-    if (tid == 0) s_np = 0;
     if (tid == 0) pick_of[kBlockUnits] = u32x4{0u, 0u, 0u, 0u};
     uint32_t pvb = 0;  // the row's largest value
     // Best point of each row, into its record.
@@ -268,7 +274,20 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_fps_block(BlockArgs a) {
             const uint32_t same = row_bits(__builtin_amdgcn_ballot_w64(bi == low), lane);
             win = l16 == __builtin_ctz(same | 0x10000u);
         }
-        const uint32_t second = row_max_all(win ? f2u(t2) : f2u(t1));
+        const uint32_t rest = f2u(win ? t2 : t1), second = row_max_all(rest);
+        if constexpr (kTwo) {
+            // Of equal seconds any will do: the third value is the same then.  So it is taken to be where a lane
+            // holds the two best: its own third value is not known.
+            const bool win2 = l16 == __builtin_ctz(row_bits(__builtin_amdgcn_ballot_w64(rest == second), lane) | 0x10000u);
+            const uint32_t third = row_max_all(win2 ? f2u(t2) : rest);
+            float cx = x[0], cy = y[0], cz = z[0];
+#pragma unroll
+            for (int j = 1; j < P; ++j) {
+                const bool e = f2u(m[j]) == second;
+                cx = e ? x[j] : cx; cy = e ? y[j] : cy; cz = e ? z[j] : cz;
+            }
+            if (win2) recC[unit] = u32x4{f2u(cx), f2u(cy), f2u(cz), third};
+        }
         pvb = top;
         if (win) {
             recA[unit] = u32x4{~bi, top, second, f2u(bx)};
@@ -276,12 +295,10 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_fps_block(BlockArgs a) {
         }
     };
     __syncthreads();  // boxes; the coordinates are done with
-    // A lane looks after two units, of the half of the curve around its wave and of the other
-    // half: the other half is passed over where the boxes are too far apart for every lane.
+    // A lane looks after two units, of the half of the curve around its wave and of the other half.
     const int base = (wave * 4 + kBlockUnits - 6) & (kBlockUnits - 1);
     const int u0 = (base + l16) & (kBlockUnits - 1), u1 = u0 ^ 16;
     const Box b0 = ubox[u0], b1 = ubox[u1];
-    const uint32_t g1 = f2u(box_box(box, b1));  // not above the distance of any two of their points
     report();
 
     // ---- rounds ----
@@ -294,30 +311,23 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_fps_block(BlockArgs a) {
         ++round;
         const uint32_t par = round & 1;
         wg_barrier();  // records
-        const uint64_t far = __builtin_amdgcn_ballot_w64(g1 < pvb);  // a unit of the other half may matter
-        const u32x4 rA = recA[unit], a0 = recA[u0];
-        const u32x2 rB = recB[unit], c0 = recB[u0];
+        const u32x4 rA = recA[unit], a0 = recA[u0], a1 = recA[u1], d0 = recC[u0], d1 = recC[u1];
+        const u32x2 rB = recB[unit], c0 = recB[u0], c1 = recB[u1];
         const float pv = u2f(pvb), px = u2f(rA.w), py = u2f(rB.x), pz = u2f(rB.y);
         const uint64_t kp = key_of(rA);
-        auto holds = [&](const u32x4 &A, const u32x2 &B, const Box &b) {
-            return (key_of(A) > kp) & (box_dist(b, px, py, pz) < pv) &
-                   ((A.z >= pvb) | (sqdist(u2f(A.w), u2f(B.x), u2f(B.y), px, py, pz) < pv));
+        auto holds = [&](const u32x4 &A, const u32x2 &B, const u32x4 &C, const Box &b) {
+            const bool first = sqdist(u2f(A.w), u2f(B.x), u2f(B.y), px, py, pz) < pv, near = box_dist(b, px, py, pz) < pv;
+            if constexpr (kTwo)
+                return (key_of(A) > kp) & (first | ((A.z >= pvb) & (sqdist(u2f(C.x), u2f(C.y), u2f(C.z), px, py, pz) < pv)) |
+                                           ((C.w >= pvb) & near));
+            else
+                return (key_of(A) > kp) & (first | ((A.z >= pvb) & near));
         };
-        bool held;
-        if (far) {
-            const u32x4 a1 = recA[u1];
-            const u32x2 c1 = recB[u1];
-            held = holds(a0, c0, b0) | holds(a1, c1, b1);
-        } else {
-            held = holds(a0, c0, b0);
-        }
+        const bool held = holds(a0, c0, d0, b0) | holds(a1, c1, d1, b1);
         const bool pick = (pvb != 0u) & (n_list < n_mine) & (row_bits(__builtin_amdgcn_ballot_w64(held), lane) == 0u);
         if (l16 == 0) {
             pick_of[unit] = u32x4{f2u(px), f2u(py), f2u(pz), pick ? pvb : 0u};
-            if (pick) {
-                mine[n_list] = kp;
-                atomicAdd(&s_np, 1u);
-            }
+            if (pick) mine[n_list] = kp;
         }
         const bool counting = np >= want;
         if (counting) {
@@ -331,27 +341,27 @@ __global__ __launch_bounds__(kBlockThreads, 2) void k_fps_block(BlockArgs a) {
         }
         n_list += pick ? 1 : 0;
         wg_barrier();  // picks
-        const u32x4 q0 = pick_of[u0];
-        u32x4 q1 = {0u, 0u, 0u, 0u};
-        if (far) q1 = pick_of[u1];
-        const int np_now = (int)s_np;
+        const u32x4 q0 = pick_of[u0], q1 = pick_of[u1];
+        // a row looks at all units
+        const int made = __builtin_popcount((uint32_t)__builtin_amdgcn_ballot_w64(q0.w != 0u) & 0xffffu) +
+                         __builtin_popcount((uint32_t)__builtin_amdgcn_ballot_w64(q1.w != 0u) & 0xffffu);
         if (counting && s_above[par] >= (uint32_t)want) {
             n_list -= pick ? 1 : 0;  // the picks of this round are not needed
             break;
         }
-        if (np_now == np) {
+        if (made == 0) {
             // no value is left, or (coordinates that are not finite) a point was picked twice
             bad = pvb != 0u;
             break;
         }
-        np = np_now;
+        np += made;
         if (tid == 0) s_above[par ^ 1] = 0;
         // ---- apply what reaches the unit's box ----
         auto reaches = [&](const u32x4 &q) {
             return box_dist(box, u2f(q.x), u2f(q.y), u2f(q.z)) < u2f(umin(pvb, q.w));
         };
         uint32_t hits = row_bits(__builtin_amdgcn_ballot_w64(reaches(q0)), lane);
-        if (far) hits |= row_bits(__builtin_amdgcn_ballot_w64(reaches(q1)), lane) << 16;
+        hits |= row_bits(__builtin_amdgcn_ballot_w64(reaches(q1)), lane) << 16;
         if (__builtin_amdgcn_ballot_w64(hits != 0) == 0) continue;
         do {
             const int h0 = hits ? (base + __builtin_ctz(hits)) & (kBlockUnits - 1) : kBlockUnits;
