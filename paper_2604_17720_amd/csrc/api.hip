@@ -270,7 +270,7 @@ int run_exact(const float *xyz, int B, int N, int M, int start, const int *start
                              idx, idx_stride, md, md_stride, (int *)(ws + w.status), clear && own};
         return hip_rc(kernel == FFPS_KERNEL_WAVE ? launch_fps_wave(a, B, s) : launch_fps_block(a, B, s));
     }
-    if (clear) {
+    if (clear && kernel != FFPS_KERNEL_LOCAL) {
         int rc = clear_status(ws, w, s);
         if (rc) return rc;
     }
@@ -281,7 +281,7 @@ int run_exact(const float *xyz, int B, int N, int M, int start, const int *start
         const LocalPlan plan = plan_fps_local(B, N, dev.num_cu);
         const LocalBuffers l = carve_local(ws + w.local, B, N, plan, nullptr);
         int *status = (int *)(ws + w.status);
-        int rc = hip_rc(launch_order(xyz, B, N, l, s));
+        int rc = hip_rc(launch_order(xyz, B, N, l, clear ? status : nullptr, s));
         if (rc == FFPS_OK)
             rc = hip_rc(launch_local(xyz, l, B, N, M, start, start_dev, plan, status,
                                      (variant & FFPS_VARIANT_TEST_NO_WAIT) ? 0 : -1, s));

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "fps_launch.h"
+
 namespace ffps {
 
 struct BlockArgs {
@@ -19,7 +21,6 @@ struct BlockArgs {
     int *status;          // as for the other kernels
     bool clear;           // the kernel clears the status block itself
 };
-constexpr int kStatusWords = 64;
 constexpr int kWaveCapacity = 256;  // largest N of one wave
 
 // fps_wg.hip: one wave per cloud, one pick per pass; N <= kWaveCapacity

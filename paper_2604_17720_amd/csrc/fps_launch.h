@@ -6,6 +6,8 @@
 
 namespace ffps {
 
+constexpr int kStatusWords = 64;  // of the status block
+
 #ifndef FFPS_MAX_PICKS
 #define FFPS_MAX_PICKS 192
 #endif

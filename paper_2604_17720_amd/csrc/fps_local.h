@@ -44,7 +44,8 @@ LocalBuffers carve_local(char *base, int B, int N, const LocalPlan &p, size_t *b
 int local_capacity();  // largest N on any device
 size_t local_workspace_bound(int B, int N);  // over all devices
 
-hipError_t launch_order(const float *xyz, int B, int N, const LocalBuffers &l, hipStream_t s);
+// `clear_status`: the call's status block, cleared as well, or null.
+hipError_t launch_order(const float *xyz, int B, int N, const LocalBuffers &l, int *clear_status, hipStream_t s);
 hipError_t launch_local(const float *xyz, const LocalBuffers &l, int B, int N, int M, int start, const int *start_dev, const LocalPlan &p,
                         int *status, int spin_limit, hipStream_t s);
 hipError_t launch_finish(const LocalBuffers &l, int B, int N, int M, int units, int start, const int *start_dev, int32_t *idx,

@@ -12,7 +12,7 @@
 // five million points; the pass and the counts by themselves take 60 and 18 us.)
 //
 // Picks: k_fps_local counts them in 8192 bins by value (32 bins to a factor of two), so a pick's
-// bin is known at once; bins are sorted in LDS.
+// bin is known at once; bins are sorted in LDS, by 1024 sub-bins first.
 #include "fps_device.h"
 #include "fps_launch.h"
 #include "fps_local.h"
@@ -66,11 +66,12 @@ __device__ __forceinline__ void block_box(Ext &e, float (*sh)[6], int tid) {
 
 // Box of each tile; clears the words the later kernels count and poll in.
 __global__ __launch_bounds__(kOT) void k_order_box(const float *__restrict__ xyz, int N, int tiles, float *__restrict__ boxes,
-                                                   uint32_t *__restrict__ zero, long zero_words) {
+                                                   uint32_t *__restrict__ zero, long zero_words, int *__restrict__ status) {
     __shared__ float sh[kOW][6];
     const int tid = threadIdx.x, t = blockIdx.x, b = blockIdx.y;
     const long nthr = (long)gridDim.x * gridDim.y * kOT, me = ((long)b * gridDim.x + t) * kOT + tid;
     for (long i = me; i < zero_words; i += nthr) zero[i] = 0u;
+    if (status && me < kStatusWords) status[me] = 0;
     int lo, hi;
     tile_range(N, tiles, t, lo, hi);
     const float *p = xyz + (size_t)b * N * 3;
@@ -305,7 +306,9 @@ __global__ __launch_bounds__(kOT) void k_order_high(const float *__restrict__ xy
 
 // ---- the picks in their order ----------------------------------------------------
 constexpr int kFT = 1024;
-constexpr int kSortMax = 2048;  // picks of a bin that are sorted in LDS
+constexpr int kSortMax = 2048;  // picks of a bin that are sorted in LDS: those of a room of 50,000 samples are 900 to 1800
+constexpr int kSubBits = 10, kSubBins = 1 << kSubBits;  // next bits of a value
+constexpr uint32_t kSubMax = 64;                        // picks that share them and are compared with one another
 
 struct FinishArgs {
     int N, M, U;                // points, samples, units of a cloud
@@ -326,52 +329,73 @@ struct FinishArgs {
     int *status;
 };
 
-// Places of the bins (largest values first), then every pick into its bin.
+// Sum over the lanes up to this one, and over the waves of the block before it: an exclusive prefix; `total` receives the sum.
+template <int WAVES>
+__device__ __forceinline__ uint32_t block_before(uint32_t v, uint32_t *part, int tid, uint32_t *total) {
+    const int lane = tid & 63, wave = tid >> 6;
+    uint32_t s = v;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t u = __shfl_up(s, o);
+        s += lane >= o ? u : 0u;
+    }
+    if (lane == 63) part[wave] = s;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        const uint32_t c = part[w];
+        before += w < wave ? c : 0u;
+        all += c;
+    }
+    *total = all;
+    return before + s - v;
+}
+// Place of a bin in LDS, where neighbours and every 64th bin lie in different banks.
+__device__ __forceinline__ uint32_t bank_place(uint32_t bin) { return bin ^ ((bin >> 6) & 31u); }
+
+// Places of the bins (largest values first), then every pick into its bin.  What bounds it is latency: of the counts, which
+// are read as they lie, of two scans and of two passes over lists of a few picks, a row of 16 lanes for each of 64 units at once.
 __global__ __launch_bounds__(kFT) void k_finish_bins(FinishArgs a) {
-    __shared__ uint32_t base[kLocalBins], cnt[kLocalBins], part[kFT];
+    __shared__ uint32_t base[kLocalBins], cnt[kLocalBins], part[2 * (kFT / kWave)];
     const int tid = threadIdx.x, b = blockIdx.y;
     const uint32_t *hist = a.hist + (size_t)b * kLocalWords;
     constexpr int per = kLocalBins / kFT;
+    {
+        uint32_t h[per];
+#pragma unroll
+        for (int k = 0; k < per; ++k) h[k] = hist[k * kFT + tid];
+#pragma unroll
+        for (int k = 0; k < per; ++k) {
+            const uint32_t w = (uint32_t)(k * kFT + tid), bin = (w & 127u) << 6 | w >> 7;
+            cnt[bank_place(bin)] = h[k];
+        }
+        static_assert(kLocalBins == 64 * 128, "the inverse of local_bin_place");
+    }
+    __syncthreads();
     // thread t: bins kLocalBins - 1 - t * per downwards
     uint32_t h[per], sum = 0, used = 0;
 #pragma unroll
     for (int k = 0; k < per; ++k) {
-        h[k] = hist[local_bin_place(kLocalBins - 1 - (tid * per + k))];
+        h[k] = cnt[bank_place(kLocalBins - 1 - (tid * per + k))];
         sum += h[k];
         used += h[k] ? 1u : 0u;
     }
-    part[tid] = sum;
-    __syncthreads();
-    for (int o = 1; o < kFT; o <<= 1) {
-        const uint32_t v = tid >= o ? part[tid - o] : 0u;
-        __syncthreads();
-        part[tid] += v;
-        __syncthreads();
-    }
-    uint32_t at = part[tid] - sum;
-    const uint32_t first = at;
+    uint32_t total;
+    const uint32_t first = block_before<kFT / kWave>(sum, part, tid, &total);
+    uint32_t at = first;
 #pragma unroll
     for (int k = 0; k < per; ++k) {
-        const int bin = kLocalBins - 1 - (tid * per + k);
-        base[bin] = at;
-        cnt[bin] = 0;
+        const uint32_t place = bank_place(kLocalBins - 1 - (tid * per + k));
+        base[place] = at;
+        cnt[place] = 0;
         at += h[k];
     }
-    const uint32_t total = part[kFT - 1];
-    __syncthreads();
     if (blockIdx.x == 0) {
         // the bins that hold samples, for the next kernel; samples beyond the picks repeat point 0
-        uint32_t n = 0;
-        if (first < (uint32_t)(a.M - 1)) n = used;
-        part[tid] = n;
-        __syncthreads();
-        for (int o = 1; o < kFT; o <<= 1) {
-            const uint32_t v = tid >= o ? part[tid - o] : 0u;
-            __syncthreads();
-            part[tid] += v;
-            __syncthreads();
-        }
-        uint32_t r = part[tid] - n;
+        const uint32_t n = first < (uint32_t)(a.M - 1) ? used : 0u;
+        uint32_t runs;
+        uint32_t r = block_before<kFT / kWave>(n, part + kFT / kWave, tid, &runs);
         if (n) {
             uint32_t p = first;
 #pragma unroll
@@ -381,7 +405,7 @@ __global__ __launch_bounds__(kFT) void k_finish_bins(FinishArgs a) {
             }
         }
         if (tid == 0) {
-            a.nruns[b] = (int)part[kFT - 1];
+            a.nruns[b] = (int)runs;
             a.idx[b * a.idx_stride] = a.start_dev ? a.start_dev[b] : a.start;
             if (a.md) a.md[b * a.md_stride] = __builtin_inff();
         }
@@ -390,41 +414,47 @@ __global__ __launch_bounds__(kFT) void k_finish_bins(FinishArgs a) {
             if (a.md) a.md[b * a.md_stride + 1 + k] = 0.f;
         }
     }
-    // units of this block
+    __syncthreads();
+    // units of this block, a row of lanes each
     const int u0 = (int)((long)blockIdx.x * a.U / gridDim.x), u1 = (int)((long)(blockIdx.x + 1) * a.U / gridDim.x);
-    const int lane = tid & 63, wave = tid >> 6;
+    const int row = tid >> 4, l16 = tid & 15;
     const u32x4 *picks = a.picks + (size_t)b * a.N;
-    for (int u = u0 + wave; u < u1; u += kFT / kWave) {
+    auto bin_of = [](uint32_t v) { return bank_place((v >> kLocalBinShift) & (kLocalBins - 1)); };
+    for (int u = u0 + row; u < u1; u += kFT / 16) {
         const u32x4 *l = picks + (int)((long)u * a.N / a.U);
         const int n = a.npicks[(size_t)b * a.U + u];
-        for (int k = lane; k < n; k += kWave) atomicAdd(&cnt[(l[k].x >> kLocalBinShift) & (kLocalBins - 1)], 1u);
+        for (int k = l16; k < n; k += 16) atomicAdd(&cnt[bin_of(l[k].x)], 1u);
     }
     __syncthreads();
-    for (int i = tid; i < kLocalBins; i += kFT) {
-        const uint32_t c = cnt[i];
-        if (c) cnt[i] = base[i] + atomicAdd(&a.cursor[(size_t)b * kLocalBins + i], c);
+#pragma unroll
+    for (int k = 0; k < per; ++k) {
+        const uint32_t bin = (uint32_t)(k * kFT + tid), place = bank_place(bin), c = cnt[place];
+        if (c) cnt[place] = base[place] + atomicAdd(&a.cursor[(size_t)b * kLocalBins + bin], c);
     }
     __syncthreads();
     uint32_t rounds = 0;
-    for (int u = u0 + wave; u < u1; u += kFT / kWave) {
+    for (int u = u0 + row; u < u1; u += kFT / 16) {
         const u32x4 *l = picks + (int)((long)u * a.N / a.U);
         const int n = a.npicks[(size_t)b * a.U + u];
-        for (int k = lane; k < n; k += kWave) {
+        for (int k = l16; k < n; k += 16) {
             const u32x4 p = l[k];
-            const uint32_t bin = (p.x >> kLocalBinShift) & (kLocalBins - 1);
-            if (base[bin] < (uint32_t)(a.M - 1)) rounds = umax(rounds, p.z);
-            const uint32_t pos = atomicAdd(&cnt[bin], 1u);
+            const uint32_t place = bin_of(p.x);
+            if (base[place] < (uint32_t)(a.M - 1)) rounds = umax(rounds, p.z);
+            const uint32_t pos = atomicAdd(&cnt[place], 1u);
             a.keys[(size_t)b * a.N + pos] = ((uint64_t)p.x << 32) | (uint32_t)~p.y;
         }
     }
     rounds = wave_max_u32(rounds);
-    if (lane == 0 && rounds) __hip_atomic_fetch_max(a.status + 1, (int)rounds, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((tid & 63) == 0 && rounds) __hip_atomic_fetch_max(a.status + 1, (int)rounds, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Sorts each bin (descending keys) and writes the samples.
+// Sorts each bin (descending keys) and writes the samples.  A bitonic sort of each bin in LDS took 39 us of 50,000 samples of
+// 200,000 points; by sub-bins 7.  (The kernel above: 30 us of eight clouds of 4096 samples with each bin read where it
+// lies, a wave per unit and 32 blocks per cloud; 12.)
 __global__ __launch_bounds__(256) void k_finish_sort(FinishArgs a) {
     __shared__ uint64_t s[kSortMax];
-    __shared__ uint32_t cnt[256];
+    __shared__ uint32_t sub[kSubBins];
+    __shared__ uint32_t cnt[256], part[4], most[4];
     const int tid = threadIdx.x, b = blockIdx.y, wave = tid >> 6;
     const int n_runs = a.nruns[b];
     auto put = [&](uint32_t place, uint64_t key) {
@@ -438,9 +468,58 @@ __global__ __launch_bounds__(256) void k_finish_sort(FinishArgs a) {
         uint64_t *keys = a.keys + (size_t)b * a.N + run.x;
         const int n = (int)run.y;
         if (n <= kSortMax) {
+            // by the next bits of the value, then among those that share them
+            uint64_t key[kSortMax / 256];
+            uint32_t at[kSortMax / 256];
+#pragma unroll
+            for (int k = 0; k < kSubBins / 256; ++k) sub[tid + k * 256] = 0;
+#pragma unroll
+            for (int k = 0; k < kSortMax / 256; ++k) {
+                const int i = tid + k * 256;
+                key[k] = i < n ? keys[i] : 0ull;
+            }
+            __syncthreads();
+            auto sub_of = [](uint64_t x) { return kSubBins - 1 - (((uint32_t)(x >> 32) >> (kLocalBinShift - kSubBits)) & (kSubBins - 1)); };
+#pragma unroll
+            for (int k = 0; k < kSortMax / 256; ++k) at[k] = tid + k * 256 < n ? atomicAdd(&sub[sub_of(key[k])], 1u) : 0u;
+            __syncthreads();
+            uint32_t c[kSubBins / 256], sum = 0, top = 0;
+#pragma unroll
+            for (int k = 0; k < kSubBins / 256; ++k) {
+                c[k] = sub[tid * (kSubBins / 256) + k];
+                sum += c[k];
+                top = umax(top, c[k]);
+            }
+            top = wave_max_u32(top);
+            if ((tid & 63) == 0) most[wave] = top;
+            uint32_t all;
+            uint32_t p = block_before<4>(sum, part, tid, &all);
+            top = umax(umax(most[0], most[1]), umax(most[2], most[3]));
+#pragma unroll
+            for (int k = 0; k < kSubBins / 256; ++k) {
+                sub[tid * (kSubBins / 256) + k] = p;
+                p += c[k];
+            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < kSortMax / 256; ++k)
+                if (tid + k * 256 < n) s[sub[sub_of(key[k])] + at[k]] = key[k];
+            __syncthreads();
+            if (top <= kSubMax) {
+                for (int i = tid; i < n; i += 256) {
+                    const uint64_t x = s[i];
+                    const uint32_t d = sub_of(x), e0 = sub[d], e1 = d + 1 < kSubBins ? sub[d + 1] : (uint32_t)n;
+                    uint32_t place = e0;
+                    for (uint32_t e = e0; e < e1; ++e) place += s[e] > x ? 1u : 0u;
+                    put(run.x + place, x);
+                }
+                __syncthreads();
+                continue;
+            }
+            // many of nearly one value
             int size = 2;
             while (size < n) size <<= 1;
-            for (int i = tid; i < size; i += 256) s[i] = i < n ? keys[i] : 0ull;
+            for (int i = n + tid; i < size; i += 256) s[i] = 0ull;
             __syncthreads();
             for (int k = 2; k <= size; k <<= 1) {
                 for (int o = k >> 1; o > 0; o >>= 1) {
@@ -509,12 +588,12 @@ int order_tiles(int N) {
     return t < 1 ? 1 : t > 256 ? 256 : t;
 }
 
-hipError_t launch_order(const float *xyz, int B, int N, const LocalBuffers &l, hipStream_t s) {
+hipError_t launch_order(const float *xyz, int B, int N, const LocalBuffers &l, int *clear_status, hipStream_t s) {
     if (N > 1 << kIndexBits) return hipErrorInvalidValue;
     const int tiles = order_tiles(N);
     const dim3 grid(tiles, B);
     uint32_t *elems = (uint32_t *)l.picks;  // the picks come later
-    k_order_box<<<grid, dim3(kOT), 0, s>>>(xyz, N, tiles, l.boxes, (uint32_t *)l.zeroed, (long)(l.zero_bytes / 4));
+    k_order_box<<<grid, dim3(kOT), 0, s>>>(xyz, N, tiles, l.boxes, (uint32_t *)l.zeroed, (long)(l.zero_bytes / 4), clear_status);
     k_order_code<<<grid, dim3(kOT), 0, s>>>(xyz, N, tiles, l.boxes, l.codes, l.hist1);
     k_order_low<<<grid, dim3(kOT), 0, s>>>(N, tiles, l.codes, l.hist1, elems);
     k_order_count<<<grid, dim3(kOT), 0, s>>>(N, tiles, elems, l.hist2);
@@ -529,7 +608,9 @@ hipError_t launch_finish(const LocalBuffers &l, int B, int N, int M, int units, 
     a.picks = (const u32x4 *)l.picks; a.npicks = l.npicks; a.hist = l.hist; a.cursor = l.cursor;
     a.runs = (u32x2 *)l.runs; a.nruns = l.nruns; a.keys = (uint64_t *)l.pts; a.spare = (uint64_t *)l.picks;
     a.idx = idx; a.idx_stride = idx_stride; a.md = md; a.md_stride = md_stride; a.status = status;
-    const int gb = B >= 32 ? 1 : units < 256 ? 4 : 32;
+    // a unit per row of lanes; with many clouds no more blocks than CUs, since all of a cloud scan its 8192 bins
+    const int rows = kFT / 16, full = (units + rows - 1) / rows, share = 256 / B > 1 ? 256 / B : 1;
+    const int gb = full < share ? full : share;
     k_finish_bins<<<dim3(gb, B), dim3(kFT), 0, s>>>(a);
     k_finish_sort<<<dim3(B >= 8 ? 64 : 256, B), dim3(256), 0, s>>>(a);
     return hipGetLastError();

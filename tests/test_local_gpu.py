@@ -52,6 +52,7 @@ CASES = {
     "largest": (lambda: inputs.uniform_cube(3145728, 5)[None], 60, 9, "GRID"),
     "many clouds of few samples": (lambda: np.stack([inputs.uniform_cube(4700, i) for i in range(270)]), 90, 3, "BLOCK"),
     "clusters in many clouds": (lambda: np.stack([inputs.planes_and_clusters(5003, i) for i in range(37)]), 600, 1, "GRID"),
+    "equal values, bins sorted in LDS": (lambda: inputs.lattice_grid(40, 40, 8)[None], 3000, 0),
     "equal values in sixteen rows": (lambda: inputs.lattice_grid(160, 128, 102)[None], 200, 0),
     "equal values in rows that are read again": (lambda: inputs.lattice_grid(160, 128, 108)[None], 200, 0),
     "clusters": (lambda: np.stack([inputs.planes_and_clusters(9001, 50 + i) for i in range(4)]), 4000, 1),
