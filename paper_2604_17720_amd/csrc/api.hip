@@ -321,42 +321,53 @@ int run_exact(const float *xyz, int B, int N, int M, int start, const int *start
     return FFPS_OK;
 }
 
+// `stages`: prefixes of the result that are wanted as well; n is 0 afterwards where they are written already.
 int run_prune(const float *xyz, int B, int N, int M, int start, int keep_num, int keep_den,
               unsigned flags, uint64_t seed, int variant, int32_t *idx, long idx_stride, char *ws,
-              const Workspace &w, const Device &dev, hipStream_t s) {
+              const Workspace &w, const Device &dev, hipStream_t s, Prefixes *stages = nullptr) {
     int Nc, k, R;
     int rc = ffps_prune_sizes(N, M, keep_num, keep_den, flags, &Nc, &k, &R);
     if (rc) return rc;
     const bool perm = (flags & FFPS_FLAG_PERM) != 0;
     uint32_t *bitmap = (uint32_t *)(ws + w.bitmap);
+    int *status = (int *)(ws + w.status);
+    const size_t words = R > 0 ? bitmap_words(B, N) : 0;
+    const Prefixes none = {};
+    const bool along = stages && stages->n > 0 && Nc < N && stages->len[0] <= k;  // no stage reaches into the fill
+    const Prefixes &put = along ? *stages : none;
+    bool ready = false;  // the bitmap is as the fill wants it: picks marked, or cleared before drawn ones
     if (Nc < N) {
         float *cxyz = (float *)(ws + w.cxyz);
         int32_t *loc = (int32_t *)(ws + w.loc);
+        ready = perm || !fill_marks_itself(N);
         if (perm) {
             int32_t *cand = (int32_t *)(ws + w.cand);
             int *spos = (int *)(ws + w.spos);
-            rc = hip_rc(launch_perm_candidates(xyz, B, N, Nc, start, seed, bitmap, cand, cxyz, spos, s));
+            rc = hip_rc(launch_perm_candidates(xyz, B, N, Nc, start, seed, bitmap, cand, cxyz, spos, Cleared{status, nullptr, 0}, s));
             if (rc) return rc;
-            rc = run_exact(cxyz, B, Nc, k, 0, spos, variant, loc, k, nullptr, 0, ws, w, dev, s, true);
+            rc = run_exact(cxyz, B, Nc, k, 0, spos, variant, loc, k, nullptr, 0, ws, w, dev, s, false);
             if (rc) return rc;
-            rc = hip_rc(launch_compose(cand, Nc, loc, k, B, k, idx, idx_stride, s));
+            rc = hip_rc(launch_compose(cand, Nc, loc, k, B, k, idx, idx_stride, Cleared{nullptr, bitmap, words}, put, s));
         } else {
-            rc = hip_rc(launch_gather_candidates(xyz, B, N, Nc, start, cxyz, s));
+            rc = hip_rc(launch_gather_candidates(xyz, B, N, Nc, start, cxyz, Cleared{status, bitmap, ready ? words : 0}, s));
             if (rc) return rc;
             long j0 = (((long)N - start) * Nc + N - 1) / N;  // where the strided list wraps
             if (j0 > Nc) j0 = Nc;
             int spos = (int)((Nc - j0) % Nc);  // position of start_idx in the sorted list
-            rc = run_exact(cxyz, B, Nc, k, spos, nullptr, variant, loc, k, nullptr, 0, ws, w, dev, s, true);
+            rc = run_exact(cxyz, B, Nc, k, spos, nullptr, variant, loc, k, nullptr, 0, ws, w, dev, s, false);
             if (rc) return rc;
-            rc = hip_rc(launch_map_candidates(loc, k, B, N, Nc, start, k, idx, idx_stride, s));
+            rc = hip_rc(launch_map_candidates(loc, k, B, N, Nc, start, k, idx, idx_stride, ready && words ? bitmap : nullptr, put, s));
         }
         if (rc) return rc;
+        if (along) stages->n = 0;
     } else {
         rc = run_exact(xyz, B, N, k, start, nullptr, variant, idx, idx_stride, nullptr, 0, ws, w, dev, s, true);
         if (rc) return rc;
     }
-    if (perm) return hip_rc(launch_fill_perm(B, N, k, R, seed, idx, idx_stride, bitmap, (int *)(ws + w.cand), s));  // the list is done with
-    return hip_rc(launch_fill(B, N, k, R, idx, idx_stride, bitmap, s));
+    // the list of candidates is done with, and no kernel needs its distances any more
+    if (perm)
+        return hip_rc(launch_fill_perm(B, N, k, R, seed, idx, idx_stride, bitmap, ready, (int32_t *)(ws + w.mind), (int *)(ws + w.cand), s));
+    return hip_rc(launch_fill(B, N, k, R, idx, idx_stride, bitmap, ready, s));
 }
 
 }  // namespace
@@ -490,21 +501,26 @@ int ffps_cached_stages(const float *d_xyz, int B, int N, int L, const int *M_sta
     hipStream_t s = (hipStream_t)stream;
     char *ws = (char *)d_ws;
 
-    rc = run_prune(d_xyz, B, N, M_stages[0], start_idx, keep_num, keep_den, flags, seed, variant,
-                   d_idx, S, ws, w, dev, s);
-    if (rc) return rc;
     long off = M_stages[0];
+    int next = 1;  // first stage that is not among the prefixes
+    auto some_stages = [&]() {
+        Prefixes p = {};
+        for (; p.n < kMaxPrefixes && next < L; ++p.n, ++next) {
+            p.at[p.n] = off;
+            p.len[p.n] = M_stages[next];
+            off += M_stages[next];
+        }
+        return p;
+    };
+    Prefixes stages = {};
+    if (mode == FFPS_MODE_CACHED) stages = some_stages();
+    rc = run_prune(d_xyz, B, N, M_stages[0], start_idx, keep_num, keep_den, flags, seed, variant,
+                   d_idx, S, ws, w, dev, s, &stages);
+    if (rc) return rc;
     if (mode == FFPS_MODE_CACHED) {
-        for (int l = 1; l < L;) {
-            long at[kMaxPrefixes];
-            int n = 0;
-            for (; n < kMaxPrefixes && l + n < L; ++n) {
-                at[n] = off;
-                off += M_stages[l + n];
-            }
-            rc = hip_rc(launch_copy_prefixes(d_idx, S, B, n, at, M_stages + l, s));
-            if (rc) return rc;
-            l += n;
+        while (stages.n > 0 || next < L) {
+            if (stages.n > 0 && (rc = hip_rc(launch_copy_prefixes(d_idx, S, B, stages, s)))) return rc;
+            stages = some_stages();
         }
         return FFPS_OK;
     }
@@ -522,7 +538,7 @@ int ffps_cached_stages(const float *d_xyz, int B, int N, int L, const int *M_sta
             if (rc) return rc;
             rc = run_exact(pxyz, B, n, m, 0, nullptr, variant, loc, m, nullptr, 0, ws, w, dev, s, false);
             if (rc) return rc;
-            rc = hip_rc(launch_compose(prev, S, loc, m, B, m, cur, S, s));
+            rc = hip_rc(launch_compose(prev, S, loc, m, B, m, cur, S, kClearNothing, Prefixes{}, s));
         }
         if (rc) return rc;
         prev = cur;

@@ -32,8 +32,17 @@ __device__ __forceinline__ int cand_at(int i, int N, int Nc, int start, int j0) 
     return (int)(((long)start + (j * (long)N) / Nc) % N);
 }
 
+// What a later launch of the call needs cleared, by the threads of this one: a launch for it alone takes 4.5 us.
+__device__ __forceinline__ void also_clear(const Cleared &c) {
+    const size_t me = (blockIdx.y * (size_t)gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x;
+    const size_t all = (size_t)gridDim.x * gridDim.y * blockDim.x;
+    if (c.status && me < (size_t)kStatusWords) c.status[me] = 0;
+    for (size_t i = me; i < c.words; i += all) c.bitmap[i] = 0u;
+}
+
 __global__ void k_gather_candidates(const float *__restrict__ xyz, int N, int Nc, int start, int j0,
-                                    float *__restrict__ cxyz) {
+                                    float *__restrict__ cxyz, Cleared clear) {
+    also_clear(clear);
     const int b = blockIdx.y;
     const float *src = xyz + (size_t)b * N * 3;
     float *dst = cxyz + (size_t)b * Nc * 3;
@@ -45,12 +54,21 @@ __global__ void k_gather_candidates(const float *__restrict__ xyz, int N, int Nc
     }
 }
 
+// Sample j of the first stage into the prefixes of it that are the deeper ones.
+__device__ __forceinline__ void put_prefixes(int32_t *row, int j, int32_t v, const Prefixes &p) {
+    for (int l = 0; l < p.n && j < p.len[l]; ++l) row[p.at[l] + j] = v;
+}
+
 __global__ void k_map_candidates(const int32_t *__restrict__ loc, long loc_stride, int N, int Nc,
                                  int start, int j0, int k, int32_t *__restrict__ idx,
-                                 long idx_stride) {
+                                 long idx_stride, uint32_t *__restrict__ marked, Prefixes stages) {
     const int b = blockIdx.y;
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < k; j += gridDim.x * blockDim.x)
-        idx[b * idx_stride + j] = cand_at(loc[b * loc_stride + j], N, Nc, start, j0);
+    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < k; j += gridDim.x * blockDim.x) {
+        const int c = cand_at(loc[b * loc_stride + j], N, Nc, start, j0);
+        idx[b * idx_stride + j] = c;
+        put_prefixes(idx + b * idx_stride, j, c, stages);
+        if (marked) atomicOr(&marked[(size_t)b * ((N + 31) / 32) + (c >> 5)], 1u << (c & 31));
+    }
 }
 
 // bm[b] |= the k picks of cloud b (bitmap cleared beforehand)
@@ -64,23 +82,29 @@ __global__ void k_mark_picks(int N, int k, const int32_t *__restrict__ idx_all, 
     }
 }
 
-constexpr int kTileWords = 1024;  // bitmap words of a tile, one per thread: 32,768 points
 constexpr int kTileBlocks = 256;  // blocks of a cloud at most: each counts the words before its own tiles again
 
-// Exclusive prefix over the block of one count per thread; `total` receives the sum.
+// Exclusive prefix over a block of 1024 of one count per thread; `total` receives the sum.
 __device__ __forceinline__ int block_prefix(int cnt, int *part, int tid, int *total) {
-    part[tid] = cnt;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {  // inclusive scan
-        const int v = tid >= off ? part[tid - off] : 0;
-        __syncthreads();
-        part[tid] += v;
-        __syncthreads();
+    const int lane = tid & 63, wave = tid >> 6;
+    int s = cnt;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const int v = __shfl_up(s, off);
+        s += lane >= off ? v : 0;
     }
-    if (total) *total = part[1023];
-    const int r = part[tid] - cnt;
+    if (lane == 63) part[wave] = s;
     __syncthreads();
-    return r;
+    int before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+        const int c = part[w];
+        before += w < wave ? c : 0;
+        all += c;
+    }
+    __syncthreads();
+    if (total) *total = all;
+    return before + s - cnt;
 }
 
 // First tile of a block.
@@ -93,18 +117,21 @@ __device__ __forceinline__ int first_tile(int tiles, int block, int blocks) { re
 // some j maps to its rank: fill[j] = free[floor(j*F/R)], F = N - k.  Since
 // F >= R the ranks floor(j*F/R) are distinct, and rank r is hit exactly by
 // j = ceil(r*R/F) when floor(j*F/R) == r.
-// Clouds of one tile are marked here as well, in the same launch.  One block did clouds of all
-// sizes before: 51 us for 200,000 points, with tiles 14 us in three launches.
+// Clouds of one block are marked here as well, in the same launch: their threads take a word each.  Beyond, a thread
+// takes a byte, so that there are enough blocks: 200,000 points are 25 of them.  (Seven blocks of 1024 words took
+// 10.8 us; one block for clouds of all sizes 51 us.)
+template <int BITS>
 __global__ __launch_bounds__(1024) void k_fill(int N, int tiles, int k, int R, int32_t *__restrict__ idx_all,
                                                long idx_stride, uint32_t *__restrict__ bitmap_all) {
-    __shared__ int part[1024];
+    __shared__ int part[16];
+    constexpr int kTileWords = 1024 * BITS / 32;
     const int b = blockIdx.y;
     const int tid = threadIdx.x;
     const int words = (N + 31) / 32;
     uint32_t *bm = bitmap_all + (size_t)b * words;
     int32_t *idx = idx_all + b * idx_stride;
 
-    if (tiles == 1) {
+    if constexpr (BITS == 32) {
         for (int i = tid; i < words; i += 1024) bm[i] = 0u;
         __syncthreads();
         for (int j = tid; j < k; j += 1024) {
@@ -119,9 +146,10 @@ __global__ __launch_bounds__(1024) void k_fill(int N, int tiles, int k, int R, i
     if (t0 > 0) (void)block_prefix(before, part, tid, &before);
     const long F = (long)N - k;
     for (int tile = t0; tile < t1; ++tile) {
-        const int wd = tile * kTileWords + tid;
+        const int wd = tile * kTileWords + tid / (32 / BITS), bit0 = tid % (32 / BITS) * BITS;
         uint32_t free_bits = 0u;
         if (wd < words) free_bits = ~bm[wd] & ((wd == words - 1 && (N & 31)) ? ((1u << (N & 31)) - 1u) : 0xffffffffu);
+        if constexpr (BITS < 32) free_bits &= ((1u << BITS) - 1u) << bit0;
         // Rank r is taken by fill slot j = ceil(r*R/F) iff floor(j*F/R) == r, i.e. iff
         // acc = j*F - r*R lies in [0, R).  One division finds j for the thread's first
         // rank; from rank to rank acc drops by R and, when it goes negative, j steps up.
@@ -175,10 +203,14 @@ __global__ void k_gather_rows(const float *__restrict__ rows, int N, int C,
 
 __global__ void k_compose(const int32_t *__restrict__ prev, long prev_stride,
                           const int32_t *__restrict__ loc, long loc_stride, int S,
-                          int32_t *__restrict__ out, long out_stride) {
+                          int32_t *__restrict__ out, long out_stride, Cleared clear, Prefixes stages) {
+    also_clear(clear);
     const int b = blockIdx.y;
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < S; j += gridDim.x * blockDim.x)
-        out[b * out_stride + j] = prev[b * prev_stride + loc[b * loc_stride + j]];
+    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < S; j += gridDim.x * blockDim.x) {
+        const int32_t c = prev[b * prev_stride + loc[b * loc_stride + j]];
+        out[b * out_stride + j] = c;
+        put_prefixes(out + b * out_stride, j, c, stages);
+    }
 }
 
 __global__ void k_copy_prefix(const int32_t *__restrict__ src, long src_stride, int S,
@@ -188,13 +220,6 @@ __global__ void k_copy_prefix(const int32_t *__restrict__ src, long src_stride, 
         out[b * out_stride + j] = src[b * src_stride + j];
 }
 
-// The prefixes of several stages, behind one another in the output: a launch costs more than
-// what it copies (three stages of a room: 14 us in three launches).
-struct Prefixes {
-    int n;
-    long at[kMaxPrefixes];  // first word of the stage in a cloud's row
-    int len[kMaxPrefixes];
-};
 __global__ void k_copy_prefixes(int32_t *__restrict__ idx, long stride, Prefixes p) {
     int32_t *row = idx + blockIdx.y * stride;
     for (int l = 0; l < p.n; ++l)
@@ -245,7 +270,8 @@ __device__ __forceinline__ uint32_t perm_at(const Perm &p, uint32_t j) {
 constexpr uint64_t kFillSeedXor = 0xD1B54A32D192ED03ull;
 
 // bitmap[b] |= { perm_{seed+b}(j) : j < Nc }   (bitmap cleared beforehand)
-__global__ void k_perm_mark(int N, int Nc, uint64_t seed, uint32_t *__restrict__ bitmap_all) {
+__global__ void k_perm_mark(int N, int Nc, uint64_t seed, uint32_t *__restrict__ bitmap_all, Cleared clear) {
+    also_clear(clear);
     const int b = blockIdx.y;
     uint32_t *bm = bitmap_all + (size_t)b * ((N + 31) / 32);
     const Perm p = make_perm(N, seed + (uint64_t)b);
@@ -258,16 +284,18 @@ __global__ void k_perm_mark(int N, int Nc, uint64_t seed, uint32_t *__restrict__
 // The candidate set in ascending order with the candidates' coordinates, a tile of the bitmap per
 // block; `start` takes the place of the last drawn candidate when it was not drawn.  A wave takes
 // two words at a time, a lane per bit, so that list and coordinates are written side by side.
-// (One block with a stretch of words per thread took 429 us for 300,000 points.)
+// 4096 points are a tile, 73 blocks for 300,000 points.  (Ten blocks of 32,768 points took 20 us, one
+// block 429 us.)
+constexpr int kCompactWords = 128;
 __global__ __launch_bounds__(1024) void k_perm_compact(const float *__restrict__ xyz_all, int N, int tiles, int Nc,
                                                        int start, uint64_t seed,
                                                        const uint32_t *__restrict__ bitmap_all,
                                                        int32_t *__restrict__ cand_all,
                                                        float *__restrict__ cxyz_all,
                                                        int *__restrict__ spos_all) {
-    __shared__ int part[1024];
-    __shared__ uint32_t bits_of[kTileWords];
-    __shared__ int rank_of[kTileWords];
+    __shared__ int part[16];
+    __shared__ uint32_t bits_of[kCompactWords];
+    __shared__ int rank_of[kCompactWords];
     const int b = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int words = (N + 31) / 32;
@@ -287,18 +315,20 @@ __global__ __launch_bounds__(1024) void k_perm_compact(const float *__restrict__
     };
     int before = 0;
     const int t0 = first_tile(tiles, blockIdx.x, gridDim.x), t1 = first_tile(tiles, blockIdx.x + 1, gridDim.x);
-    for (int wd = tid; wd < t0 * kTileWords; wd += 1024) before += __popc(word(wd));
+    for (int wd = tid; wd < t0 * kCompactWords; wd += 1024) before += __popc(word(wd));
     if (t0 > 0) (void)block_prefix(before, part, tid, &before);
     for (int tile = t0; tile < t1; ++tile) {
-        const int wd0 = tile * kTileWords;
-        const uint32_t own = wd0 + tid < words ? word(wd0 + tid) : 0u;
+        const int wd0 = tile * kCompactWords;
+        const uint32_t own = tid < kCompactWords && wd0 + tid < words ? word(wd0 + tid) : 0u;
         int total = 0;
         const int r = before + block_prefix(__popc(own), part, tid, &total);
         before += total;
-        bits_of[tid] = own;
-        rank_of[tid] = r;
+        if (tid < kCompactWords) {
+            bits_of[tid] = own;
+            rank_of[tid] = r;
+        }
         __syncthreads();
-        for (int p = wave; p < kTileWords / 2; p += 16) {
+        for (int p = wave; p < kCompactWords / 2; p += 16) {
             const int t = 2 * p + (lane >> 5);
             const uint32_t v = bits_of[t];
             if ((v >> (lane & 31)) & 1u) {
@@ -311,54 +341,42 @@ __global__ __launch_bounds__(1024) void k_perm_compact(const float *__restrict__
                 if (i == start) spos_all[b] = at;
             }
         }
+        __syncthreads();
     }
 }
 
 // The seeded fill: idx[k + r] = r-th index, in the order of a second permutation of [0, N), that
-// is not among the picks (marked in the bitmap); r < R.  A tile of 4096 places of the permutation
-// per block, twice: the first launch counts the free ones of each tile, the second places them.
-// (One block walking through all places took 1560 us for 300,000 points.)
-constexpr int kPermTile = 4096;
-template <bool COUNT>
-__global__ __launch_bounds__(1024) void k_fill_perm(int N, int k, int R, uint64_t seed,
-                                                    int32_t *__restrict__ idx_all, long idx_stride,
-                                                    const uint32_t *__restrict__ bitmap_all, int *__restrict__ free_all) {
-    __shared__ int part[1024];
-    const int b = blockIdx.y, tile = blockIdx.x;
-    const int tid = threadIdx.x;
+// is not among the picks (marked in the bitmap); r < R.  The first k + R places hold R such indices.  A tile of
+// 1024 places per block, twice: the first launch finds the index at each place (-1: a pick) and counts the others, the
+// second puts them where they belong.  What bounds the first is the longest walk of a wave's lanes until the permutation
+// falls below N.  16,384 samples of 300,000 points: 22 and 23 us with all places and tiles of 4096, found in both launches.
+constexpr int kPermTile = 1024;
+__global__ __launch_bounds__(kPermTile) void k_fill_perm_find(int N, int places, uint64_t seed, const uint32_t *__restrict__ bitmap_all,
+                                                              int32_t *__restrict__ at_all, int *__restrict__ free_all) {
+    __shared__ int part[16];
+    const int b = blockIdx.y, tile = blockIdx.x, tid = threadIdx.x, j = tile * kPermTile + tid;
     const uint32_t *bm = bitmap_all + (size_t)b * ((N + 31) / 32);
-    int32_t *idx = idx_all + b * idx_stride;
-    int *nfree = free_all + (size_t)b * gridDim.x;
-    int before = 0;
-    if constexpr (!COUNT) {
-        for (int t = tid; t < tile; t += 1024) before += nfree[t];
-        (void)block_prefix(before, part, tid, &before);
-        if (before >= R) return;
-    }
-    const Perm p = make_perm(N, (seed + (uint64_t)b) ^ kFillSeedXor);
-    constexpr int per = kPermTile / 1024;
-    uint32_t at[per];
-    int cnt = 0;
-    bool is_free[per];
-#pragma unroll
-    for (int e = 0; e < per; ++e) {
-        const long j = (long)tile * kPermTile + tid * per + e;
-        is_free[e] = false;
-        if (j < N) {
-            at[e] = perm_at(p, (uint32_t)j);
-            is_free[e] = !((bm[at[e] >> 5] >> (at[e] & 31)) & 1u);
-        }
-        cnt += is_free[e] ? 1 : 0;
+    int at = -1;
+    if (j < places) {
+        at = (int)perm_at(make_perm(N, (seed + (uint64_t)b) ^ kFillSeedXor), (uint32_t)j);
+        if ((bm[at >> 5] >> (at & 31)) & 1u) at = -1;
+        at_all[(size_t)b * places + j] = at;
     }
     int total = 0;
-    int r = before + block_prefix(cnt, part, tid, &total);
-    if constexpr (COUNT) {
-        if (tid == 0) nfree[tile] = total;
-    } else {
-#pragma unroll
-        for (int e = 0; e < per; ++e)
-            if (is_free[e] && r < R) idx[k + r++] = (int32_t)at[e];
-    }
+    (void)block_prefix(at >= 0 ? 1 : 0, part, tid, &total);
+    if (tid == 0) free_all[(size_t)b * gridDim.x + tile] = total;
+}
+__global__ __launch_bounds__(kPermTile) void k_fill_perm_put(int places, int k, int R, int32_t *__restrict__ idx_all, long idx_stride,
+                                                             const int32_t *__restrict__ at_all, const int *__restrict__ free_all) {
+    __shared__ int part[16];
+    const int b = blockIdx.y, tile = blockIdx.x, tid = threadIdx.x, j = tile * kPermTile + tid;
+    const int *nfree = free_all + (size_t)b * gridDim.x;
+    const int at = j < places ? at_all[(size_t)b * places + j] : -1;
+    int before = 0;
+    for (int t = tid; t < tile; t += kPermTile) before += nfree[t];
+    (void)block_prefix(before, part, tid, &before);
+    const int r = before + block_prefix(at >= 0 ? 1 : 0, part, tid, nullptr);
+    if (at >= 0 && r < R) idx_all[b * idx_stride + k + r] = at;
 }
 
 // Reference point for the multi-workgroup kernels: `iters` plain grid barriers
@@ -434,49 +452,58 @@ hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s) {
 }
 
 hipError_t launch_gather_candidates(const float *xyz, int B, int N, int Nc, int start, float *cxyz,
-                                    hipStream_t s) {
+                                    const Cleared &clear, hipStream_t s) {
     hipLaunchKernelGGL(k_gather_candidates, dim3(blocks_for(Nc), B), dim3(kT), 0, s, xyz, N, Nc,
-                       start, wrap_point(N, Nc, start), cxyz);
+                       start, wrap_point(N, Nc, start), cxyz, clear);
     return hipGetLastError();
 }
 
 hipError_t launch_map_candidates(const int32_t *loc, long loc_stride, int B, int N, int Nc,
-                                 int start, int k, int32_t *idx, long idx_stride, hipStream_t s) {
+                                 int start, int k, int32_t *idx, long idx_stride, uint32_t *marked, const Prefixes &stages,
+                                 hipStream_t s) {
     hipLaunchKernelGGL(k_map_candidates, dim3(blocks_for(k), B), dim3(kT), 0, s, loc, loc_stride, N,
-                       Nc, start, wrap_point(N, Nc, start), k, idx, idx_stride);
+                       Nc, start, wrap_point(N, Nc, start), k, idx, idx_stride, marked, stages);
     return hipGetLastError();
 }
 
-// Clears the bitmap and marks the picks in it.
-static hipError_t mark_picks(int B, int N, int k, const int32_t *idx, long idx_stride, uint32_t *bitmap, hipStream_t s) {
-    const size_t words = (size_t)B * ((N + 31) / 32);
-    hipLaunchKernelGGL(k_fill_zero, dim3(blocks_for(words)), dim3(kT), 0, s, bitmap, words);
+size_t bitmap_words(int B, int N) { return (size_t)B * ((N + 31) / 32); }
+
+// Clears the bitmap, where it is not, and marks the picks in it.
+static hipError_t mark_picks(int B, int N, int k, const int32_t *idx, long idx_stride, uint32_t *bitmap, bool cleared, hipStream_t s) {
+    const size_t words = bitmap_words(B, N);
+    if (!cleared) hipLaunchKernelGGL(k_fill_zero, dim3(blocks_for(words)), dim3(kT), 0, s, bitmap, words);
     hipLaunchKernelGGL(k_mark_picks, dim3(blocks_for(k), B), dim3(kT), 0, s, N, k, idx, idx_stride, bitmap);
     return hipGetLastError();
 }
 
+static int tiles_of(int N, int tile_words) { return ((N + 31) / 32 + tile_words - 1) / tile_words; }
 static int tile_blocks(int tiles) { return tiles < kTileBlocks ? tiles : kTileBlocks; }
-static int bitmap_tiles(int N) { return ((N + 31) / 32 + kTileWords - 1) / kTileWords; }
 
-hipError_t launch_fill(int B, int N, int k, int R, int32_t *idx, long idx_stride, uint32_t *bitmap,
+bool fill_marks_itself(int N) { return tiles_of(N, 1024) == 1; }
+
+hipError_t launch_fill(int B, int N, int k, int R, int32_t *idx, long idx_stride, uint32_t *bitmap, bool marked,
                        hipStream_t s) {
     if (R <= 0) return hipSuccess;
-    const int tiles = bitmap_tiles(N);
-    if (tiles > 1) {
-        hipError_t e = mark_picks(B, N, k, idx, idx_stride, bitmap, s);
+    if (fill_marks_itself(N)) {
+        hipLaunchKernelGGL(k_fill<32>, dim3(1, B), dim3(1024), 0, s, N, 1, k, R, idx, idx_stride, bitmap);
+        return hipGetLastError();
+    }
+    if (!marked) {
+        hipError_t e = mark_picks(B, N, k, idx, idx_stride, bitmap, false, s);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_fill, dim3(tile_blocks(tiles), B), dim3(1024), 0, s, N, tiles, k, R, idx, idx_stride, bitmap);
+    const int tiles = tiles_of(N, 256);
+    hipLaunchKernelGGL(k_fill<8>, dim3(tile_blocks(tiles), B), dim3(1024), 0, s, N, tiles, k, R, idx, idx_stride, bitmap);
     return hipGetLastError();
 }
 
 hipError_t launch_perm_candidates(const float *xyz, int B, int N, int Nc, int start, uint64_t seed,
                                   uint32_t *bitmap, int32_t *cand, float *cxyz, int *spos,
-                                  hipStream_t s) {
-    const size_t words = (size_t)B * ((N + 31) / 32);
+                                  const Cleared &clear, hipStream_t s) {
+    const size_t words = bitmap_words(B, N);
     hipLaunchKernelGGL(k_fill_zero, dim3(blocks_for(words)), dim3(kT), 0, s, bitmap, words);
-    hipLaunchKernelGGL(k_perm_mark, dim3(blocks_for(Nc), B), dim3(kT), 0, s, N, Nc, seed, bitmap);
-    const int tiles = bitmap_tiles(N);
+    hipLaunchKernelGGL(k_perm_mark, dim3(blocks_for(Nc), B), dim3(kT), 0, s, N, Nc, seed, bitmap, clear);
+    const int tiles = tiles_of(N, kCompactWords);
     hipLaunchKernelGGL(k_perm_compact, dim3(tile_blocks(tiles), B), dim3(1024), 0, s, xyz, N, tiles, Nc, start, seed, bitmap, cand,
                        cxyz, spos);
     return hipGetLastError();
@@ -485,13 +512,14 @@ hipError_t launch_perm_candidates(const float *xyz, int B, int N, int Nc, int st
 size_t fill_perm_count_words(int N) { return (size_t)(N + kPermTile - 1) / kPermTile; }
 
 hipError_t launch_fill_perm(int B, int N, int k, int R, uint64_t seed, int32_t *idx, long idx_stride,
-                            uint32_t *bitmap, int *counts, hipStream_t s) {
+                            uint32_t *bitmap, bool cleared, int32_t *at, int *counts, hipStream_t s) {
     if (R <= 0) return hipSuccess;
-    hipError_t e = mark_picks(B, N, k, idx, idx_stride, bitmap, s);
+    hipError_t e = mark_picks(B, N, k, idx, idx_stride, bitmap, cleared, s);
     if (e != hipSuccess) return e;
-    const dim3 grid((unsigned)fill_perm_count_words(N), B);
-    hipLaunchKernelGGL(k_fill_perm<true>, grid, dim3(1024), 0, s, N, k, R, seed, idx, idx_stride, bitmap, counts);
-    hipLaunchKernelGGL(k_fill_perm<false>, grid, dim3(1024), 0, s, N, k, R, seed, idx, idx_stride, bitmap, counts);
+    const int places = k + R;
+    const dim3 grid((unsigned)fill_perm_count_words(places), B);
+    hipLaunchKernelGGL(k_fill_perm_find, grid, dim3(kPermTile), 0, s, N, places, seed, bitmap, at, counts);
+    hipLaunchKernelGGL(k_fill_perm_put, grid, dim3(kPermTile), 0, s, places, k, R, idx, idx_stride, at, counts);
     return hipGetLastError();
 }
 
@@ -510,9 +538,9 @@ hipError_t launch_gather_rows(const float *rows, int B, int N, int C, const int3
 }
 
 hipError_t launch_compose(const int32_t *prev, long prev_stride, const int32_t *loc, long loc_stride,
-                          int B, int S, int32_t *out, long out_stride, hipStream_t s) {
+                          int B, int S, int32_t *out, long out_stride, const Cleared &clear, const Prefixes &stages, hipStream_t s) {
     hipLaunchKernelGGL(k_compose, dim3(blocks_for(S), B), dim3(kT), 0, s, prev, prev_stride, loc,
-                       loc_stride, S, out, out_stride);
+                       loc_stride, S, out, out_stride, clear, stages);
     return hipGetLastError();
 }
 
@@ -523,11 +551,8 @@ hipError_t launch_copy_prefix(const int32_t *src, long src_stride, int B, int S,
     return hipGetLastError();
 }
 
-hipError_t launch_copy_prefixes(int32_t *idx, long stride, int B, int n, const long *at, const int *len, hipStream_t s) {
-    if (n < 1 || n > kMaxPrefixes) return hipErrorInvalidValue;
-    Prefixes p;
-    p.n = n;
-    for (int k = 0; k < n; ++k) { p.at[k] = at[k]; p.len[k] = len[k]; }
+hipError_t launch_copy_prefixes(int32_t *idx, long stride, int B, const Prefixes &p, hipStream_t s) {
+    if (p.n < 1 || p.n > kMaxPrefixes) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_copy_prefixes, dim3(blocks_for(p.len[0]), B), dim3(kT), 0, s, idx, stride, p);
     return hipGetLastError();
 }

@@ -66,25 +66,45 @@ hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s);
 // `iters` grid barriers over num_wg co-resident workgroups; *counter must be zero
 hipError_t launch_barrier_probe(unsigned *counter, int *status, int num_wg, int iters, hipStream_t s);
 hipError_t launch_alu_probe(float *sink, int num_wg, int waves_per_wg, int iters, hipStream_t s);
+// What a helper kernel clears besides its own work, for a later launch of the call: the status block (or null), words of a bitmap.
+struct Cleared {
+    int *status;
+    uint32_t *bitmap;
+    size_t words;
+};
+constexpr Cleared kClearNothing = {nullptr, nullptr, 0};
+// Prefixes of a cloud's first stage, its deeper stages, behind it in the row; they do not grow.  A launch costs more than
+// what it copies (three stages of a room: 14 us in three launches, 4 in one), so where the first stage's
+// samples are put down they are put into the prefixes as well, if no prefix is longer.
+constexpr int kMaxPrefixes = 16;
+struct Prefixes {
+    int n;
+    long at[kMaxPrefixes];  // first word of the stage in a cloud's row
+    int len[kMaxPrefixes];
+};
+size_t bitmap_words(int B, int N);  // a bit per point
 // cxyz[b][i] = xyz[b][cand(i)], cand = the sorted strided candidate list (see flashfps.h)
 hipError_t launch_gather_candidates(const float *xyz, int B, int N, int Nc, int start,
-                                    float *cxyz, hipStream_t s);
-// idx[b][j] = cand(loc[b][j]) for j < k
+                                    float *cxyz, const Cleared &clear, hipStream_t s);
+// idx[b][j] = cand(loc[b][j]) for j < k; `marked`: a cleared bitmap in which they are marked, or null
 hipError_t launch_map_candidates(const int32_t *loc, long loc_stride, int B, int N, int Nc,
-                                 int start, int k, int32_t *idx, long idx_stride, hipStream_t s);
-// idx[b][k + j] = j-th strided rank of the indices not in idx[b][0..k)
+                                 int start, int k, int32_t *idx, long idx_stride, uint32_t *marked, const Prefixes &stages,
+                                 hipStream_t s);
+// idx[b][k + j] = j-th strided rank of the indices not in idx[b][0..k), which are marked in the bitmap already where
+// `marked` says so
 hipError_t launch_fill(int B, int N, int k, int R, int32_t *idx, long idx_stride,
-                       uint32_t *bitmap, hipStream_t s);
+                       uint32_t *bitmap, bool marked, hipStream_t s);
+bool fill_marks_itself(int N);  // nobody else has to clear or mark the bitmap then
 // Seeded random candidate set of cloud b (seed + b): ascending list cand[b][0..Nc),
 // its coordinates cxyz[b][0..Nc), and spos[b] = position of `start` in the list.
 hipError_t launch_perm_candidates(const float *xyz, int B, int N, int Nc, int start, uint64_t seed,
                                   uint32_t *bitmap, int32_t *cand, float *cxyz, int *spos,
-                                  hipStream_t s);
+                                  const Cleared &clear, hipStream_t s);
 // idx[b][k + r], r < R = first R indices, in the order of a second seeded permutation,
-// that are not in idx[b][0..k)
+// that are not in idx[b][0..k); the bitmap has to be cleared first unless `cleared`; `at`: k + R words per cloud
 hipError_t launch_fill_perm(int B, int N, int k, int R, uint64_t seed, int32_t *idx, long idx_stride,
-                            uint32_t *bitmap, int *counts, hipStream_t s);
-size_t fill_perm_count_words(int N);  // words of `counts` per cloud
+                            uint32_t *bitmap, bool cleared, int32_t *at, int *counts, hipStream_t s);
+size_t fill_perm_count_words(int places);  // words of `counts` per cloud
 // dst[b][j] = xyz[b][sel[b][j]] for j < S
 hipError_t launch_gather_points(const float *xyz, int B, int N, const int32_t *sel,
                                 long sel_stride, int S, float *dst, hipStream_t s);
@@ -94,12 +114,11 @@ hipError_t launch_gather_rows(const float *rows, int B, int N, int C, const int3
 // out[b][j] = prev[b][loc[b][j]] for j < S
 hipError_t launch_compose(const int32_t *prev, long prev_stride, const int32_t *loc,
                           long loc_stride, int B, int S, int32_t *out, long out_stride,
-                          hipStream_t s);
+                          const Cleared &clear, const Prefixes &stages, hipStream_t s);
 // out[b][j] = src[b][j] for j < S
 hipError_t launch_copy_prefix(const int32_t *src, long src_stride, int B, int S, int32_t *out,
                               long out_stride, hipStream_t s);
-// idx[b][at[l] + j] = idx[b][j] for j < len[l], l < n <= kMaxPrefixes; lengths do not grow
-constexpr int kMaxPrefixes = 16;
-hipError_t launch_copy_prefixes(int32_t *idx, long stride, int B, int n, const long *at, const int *len, hipStream_t s);
+// idx[b][at[l] + j] = idx[b][j] for j < len[l], l < n
+hipError_t launch_copy_prefixes(int32_t *idx, long stride, int B, const Prefixes &p, hipStream_t s);
 
 }  // namespace ffps
