@@ -36,6 +36,32 @@ __device__ __forceinline__ void tile_range(int N, int tiles, int t, int &lo, int
     hi = min(N, lo + per);
 }
 
+// Sum over the lanes up to this one, and over the waves of the block before it: an exclusive prefix; `total` receives the sum.
+template <int WAVES>
+__device__ __forceinline__ uint32_t block_before(uint32_t v, uint32_t *part, int tid, uint32_t *total) {
+    const int lane = tid & 63, wave = tid >> 6;
+    uint32_t s = v;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t u = __shfl_up(s, o);
+        s += lane >= o ? u : 0u;
+    }
+    if (lane == 63) part[wave] = s;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        const uint32_t c = part[w];
+        before += w < wave ? c : 0u;
+        all += c;
+    }
+    *total = all;
+    return before + s - v;
+}
+// Points of a thread that are on their way at once in the passes over a cloud.  One after another, five million points
+// took 20, 28 and 18 us (boxes, keys, counts); 62 and 116 us the two passes that move them.
+constexpr int kTogether = 4;
+
 struct Ext { float lo[3], hi[3]; };
 
 __device__ __forceinline__ void block_box(Ext &e, float (*sh)[6], int tid) {
@@ -78,13 +104,20 @@ __global__ __launch_bounds__(kOT) void k_order_box(const float *__restrict__ xyz
     Ext e;
 #pragma unroll
     for (int k = 0; k < 3; ++k) { e.lo[k] = __builtin_inff(); e.hi[k] = -__builtin_inff(); }
-    for (int i = lo + tid; i < hi; i += kOT) {
+    for (int i0 = lo + tid; i0 < hi; i0 += kTogether * kOT) {
+        float v[kTogether][3];
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            const float v = p[3 * (size_t)i + k];
-            e.lo[k] = fminf(e.lo[k], v);
-            e.hi[k] = fmaxf(e.hi[k], v);
+        for (int j = 0; j < kTogether; ++j) {
+            const float *q = p + 3 * (size_t)min(i0 + j * kOT, hi - 1);
+            v[j][0] = q[0]; v[j][1] = q[1]; v[j][2] = q[2];
         }
+#pragma unroll
+        for (int j = 0; j < kTogether; ++j)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                e.lo[k] = fminf(e.lo[k], v[j][k]);
+                e.hi[k] = fmaxf(e.hi[k], v[j][k]);
+            }
     }
     block_box(e, sh, tid);
     if (tid < 6) boxes[((size_t)b * tiles + t) * 6 + tid] = tid < 3 ? e.lo[tid] : e.hi[tid - 3];
@@ -172,15 +205,24 @@ __global__ __launch_bounds__(kOT) void k_order_code(const float *__restrict__ xy
         atomicAdd(&cnt[key & (kLowBins - 1)], 1u);
     };
     if (fills_box(qx, qy, qz, e.lo, side)) {
-        for (int i = lo + tid; i < hi; i += kOT) {
-            uint32_t c[3];
+        for (int i0 = lo + tid; i0 < hi; i0 += kTogether * kOT) {
+            float v[kTogether][3];
 #pragma unroll
-            for (int k = 0; k < 3; ++k) c[k] = (uint32_t)fmaxf(0.f, fminf(31.f, (p[3 * (size_t)i + k] - e.lo[k]) * scale));
-            put(i, hilbert_code<5>(c[0], c[1], c[2]));
+            for (int j = 0; j < kTogether; ++j) {
+                const float *q = p + 3 * (size_t)min(i0 + j * kOT, hi - 1);
+                v[j][0] = q[0]; v[j][1] = q[1]; v[j][2] = q[2];
+            }
+#pragma unroll
+            for (int j = 0; j < kTogether; ++j) {
+                uint32_t c[3];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) c[k] = (uint32_t)fmaxf(0.f, fminf(31.f, (v[j][k] - e.lo[k]) * scale));
+                const uint32_t key = hilbert_code<5>(c[0], c[1], c[2]);
+                if (i0 + j * kOT < hi) put(i0 + j * kOT, key);
+            }
         }
     } else {
         const Frame f = find_splitters(p, N, tid, sp);
-        constexpr int kTogether = 4;  // points of a thread whose searches do not wait for one another
         for (int i0 = lo + tid; i0 < hi; i0 += kTogether * kOT) {
             uint32_t code[kTogether], s[kTogether];
 #pragma unroll
@@ -202,106 +244,144 @@ __global__ __launch_bounds__(kOT) void k_order_code(const float *__restrict__ xy
 }
 
 // One pass of a stable radix sort: a block moves the elements of its tile behind those of
-// earlier tiles and, within the tile, behind those of earlier waves.  `digit(i)` is the digit
-// of element i, `move(i, pos)` puts it in its place.
-template <int BITS, typename D, typename MV>
+// earlier tiles and, within the tile, behind those of earlier waves.  `get(i)` is element i, `digit(e)` its digit, `fetch(e, i)` what `put(x, pos)` puts in its place.  What bounds it is latency, so elements are loaded, and moved, a
+// few rows at a time, the first rows before the counts of the tiles; these are added up by all threads, some to a digit.
+template <int BITS>
+struct PassShared {
+    uint32_t cnt[kOW][1 << BITS], before[kOT], total[kOT], part[kOW];
+};
+template <int BITS, typename G, typename D, typename F, typename PU>
 __device__ __forceinline__ void stable_pass(const uint32_t *__restrict__ hist, int tiles, int t, int lo, int hi, int tid,
-                                            uint32_t (*cnt)[1 << BITS], uint32_t *part, D digit, MV move) {
-    constexpr int NB = 1 << BITS;
-    static_assert(NB <= kOT, "a thread per digit");
+                                            PassShared<BITS> &sh, G get, D digit, F fetch, PU put) {
+    constexpr int NB = 1 << BITS, kRows = 8;
+    static_assert(NB <= kOT && kOT % NB == 0, "threads per digit");
     const int lane = tid & 63, wave = tid >> 6;
-    for (int i = tid; i < kOW * NB; i += kOT) (&cnt[0][0])[i] = 0;
+    const int rows = (hi - lo + kOT - 1) / kOT, w0 = lo + wave * rows * kWave + lane;
+    decltype(get(0)) e[kRows];
+    auto on = [&](int r) { return r < rows && w0 + r * kWave < hi; };
+    auto load = [&](int r0) {
+#pragma unroll
+        for (int k = 0; k < kRows; ++k) e[k] = get(min(w0 + (r0 + k) * kWave, hi - 1));  // others' are not used
+    };
+    load(0);
+    for (int i = tid; i < kOW * NB; i += kOT) (&sh.cnt[0][0])[i] = 0;
     // elements of each digit in earlier tiles, and in all of them
     uint32_t before = 0, total = 0;
-    if (tid < NB) {
 #pragma unroll 8
-        for (int k = 0; k < tiles; ++k) {
-            const uint32_t h = hist[(size_t)k * NB + tid];
-            before += k < t ? h : 0u;
-            total += h;
-        }
-        part[tid] = total;
+    for (int k = tid / NB; k < tiles; k += kOT / NB) {
+        const uint32_t h = hist[(size_t)k * NB + (tid & (NB - 1))];
+        before += k < t ? h : 0u;
+        total += h;
     }
+    sh.before[tid] = before;
+    sh.total[tid] = total;
     __syncthreads();
-    const int rows = (hi - lo + kOT - 1) / kOT, w0 = lo + wave * rows * kWave;
-    for (int r = 0; r < rows; ++r) {
-        const int i = w0 + r * kWave + lane;
-        if (i < hi) atomicAdd(&cnt[wave][digit(i)], 1u);
-    }
-    for (int o = 1; o < NB; o <<= 1) {
-        const uint32_t v = tid < NB && tid >= o ? part[tid - o] : 0u;
-        __syncthreads();
-        if (tid < NB) part[tid] += v;
-        __syncthreads();
-    }
     if (tid < NB) {
-        uint32_t at = part[tid] - total + before;
+#pragma unroll
+        for (int g = NB; g < kOT; g += NB) {
+            before += sh.before[g + tid];
+            total += sh.total[g + tid];
+        }
+    }
+    for (int r0 = 0;;) {
+#pragma unroll
+        for (int k = 0; k < kRows; ++k)
+            if (on(r0 + k)) atomicAdd(&sh.cnt[wave][digit(e[k])], 1u);
+        r0 += kRows;
+        if (r0 >= rows) break;
+        load(r0);
+    }
+    if (rows > kRows) load(0);
+    uint32_t all;
+    uint32_t at = block_before<kOW>(tid < NB ? total : 0u, sh.part, tid, &all) + before;
+    if (tid < NB) {
         for (int v = 0; v < kOW; ++v) {
-            const uint32_t c = cnt[v][tid];
-            cnt[v][tid] = at;
+            const uint32_t c = sh.cnt[v][tid];
+            sh.cnt[v][tid] = at;
             at += c;
         }
     }
     __syncthreads();
-    for (int r = 0; r < rows; ++r) {
-        const int i = w0 + r * kWave + lane;
-        const bool ok = i < hi;
-        const uint32_t d = ok ? digit(i) : 0u;
-        const uint64_t m = same_digit<BITS>(d, __builtin_amdgcn_ballot_w64(ok));
-        const uint32_t base = cnt[wave][d];
-        const int r_in = lanes_below(m);
-        wave_lds_order();  // all lanes have read the count
-        if (ok && r_in == 0) cnt[wave][d] = base + (uint32_t)__builtin_popcountll(m);
-        wave_lds_order();  // and it is written before the next row reads it
-        if (ok) move(i, base + r_in);
+    for (int r0 = 0;;) {
+        uint32_t pos[kRows];
+#pragma unroll
+        for (int k = 0; k < kRows; ++k) {
+            const bool ok = on(r0 + k);
+            const uint32_t d = digit(e[k]);
+            const uint64_t m = same_digit<BITS>(d, __builtin_amdgcn_ballot_w64(ok));
+            const uint32_t base = sh.cnt[wave][d];
+            const int r_in = lanes_below(m);
+            wave_lds_order();  // all lanes have read the count
+            if (ok && r_in == 0) sh.cnt[wave][d] = base + (uint32_t)__builtin_popcountll(m);
+            wave_lds_order();  // and it is written before the next row reads it
+            pos[k] = base + r_in;
+        }
+        decltype(fetch(e[0], 0)) x[kRows];
+#pragma unroll
+        for (int k = 0; k < kRows; ++k) x[k] = fetch(e[k], min(w0 + (r0 + k) * kWave, hi - 1));
+#pragma unroll
+        for (int k = 0; k < kRows; ++k)
+            if (on(r0 + k)) put(x[k], pos[k]);
+        r0 += kRows;
+        if (r0 >= rows) break;
+        load(r0);
     }
 }
 
-// An element on its way: index below, high digit above.
+// A point on its way: in its last word the index below, the high digit above.
 constexpr int kIndexBits = 25;
 
-__global__ __launch_bounds__(kOT) void k_order_low(int N, int tiles, const uint16_t *__restrict__ codes, const uint32_t *__restrict__ hist,
-                                                   uint32_t *__restrict__ elems) {
-    __shared__ uint32_t cnt[kOW][kLowBins], part[kLowBins];
+__global__ __launch_bounds__(kOT) void k_order_low(const float *__restrict__ xyz, int N, int tiles, const uint16_t *__restrict__ codes,
+                                                   const uint32_t *__restrict__ hist, u32x4 *__restrict__ elems) {
+    __shared__ PassShared<8> sh;
     const int tid = threadIdx.x, t = blockIdx.x, b = blockIdx.y;
     int lo, hi;
     tile_range(N, tiles, t, lo, hi);
     const uint16_t *c = codes + (size_t)b * N;
-    uint32_t *out = elems + (size_t)b * N;
-    stable_pass<8>(hist + (size_t)b * tiles * kLowBins, tiles, t, lo, hi, tid, cnt, part,
-                   [&](int i) { return (uint32_t)c[i] & (kLowBins - 1); },
-                   [&](int i, uint32_t pos) { out[pos] = ((uint32_t)c[i] >> 8) << kIndexBits | (uint32_t)i; });
+    const float *p = xyz + (size_t)b * N * 3;
+    u32x4 *out = elems + (size_t)b * N;
+    stable_pass<8>(hist + (size_t)b * tiles * kLowBins, tiles, t, lo, hi, tid, sh, [&](int i) { return (uint32_t)c[i]; },
+                   [&](uint32_t e) { return e & (kLowBins - 1); },
+                   [&](uint32_t e, int i) {
+                       const float *q = p + 3 * (size_t)i;
+                       return u32x4{f2u(q[0]), f2u(q[1]), f2u(q[2]), (e >> 8) << kIndexBits | (uint32_t)i};
+                   },
+                   [&](const u32x4 &x, uint32_t pos) { out[pos] = x; });
 }
 
 // How often each high digit occurs in a tile.
-__global__ __launch_bounds__(kOT) void k_order_count(int N, int tiles, const uint32_t *__restrict__ elems, uint32_t *__restrict__ hist2) {
+__global__ __launch_bounds__(kOT) void k_order_count(int N, int tiles, const u32x4 *__restrict__ elems, uint32_t *__restrict__ hist2) {
     __shared__ uint32_t cnt[kHighBins];
     const int tid = threadIdx.x, t = blockIdx.x, b = blockIdx.y;
     if (tid < kHighBins) cnt[tid] = 0;
     __syncthreads();
     int lo, hi;
     tile_range(N, tiles, t, lo, hi);
-    const uint32_t *in = elems + (size_t)b * N;
-    for (int i = lo + tid; i < hi; i += kOT) atomicAdd(&cnt[in[i] >> kIndexBits], 1u);
+    const u32x4 *in = elems + (size_t)b * N;
+    for (int i0 = lo + tid; i0 < hi; i0 += kTogether * kOT) {
+        uint32_t e[kTogether];
+#pragma unroll
+        for (int j = 0; j < kTogether; ++j) e[j] = in[min(i0 + j * kOT, hi - 1)].w;
+#pragma unroll
+        for (int j = 0; j < kTogether; ++j)
+            if (i0 + j * kOT < hi) atomicAdd(&cnt[e[j] >> kIndexBits], 1u);
+    }
     __syncthreads();
     if (tid < kHighBins) hist2[((size_t)b * tiles + t) * kHighBins + tid] = cnt[tid];
 }
 
-__global__ __launch_bounds__(kOT) void k_order_high(const float *__restrict__ xyz, int N, int tiles, const uint32_t *__restrict__ elems,
+__global__ __launch_bounds__(kOT) void k_order_high(int N, int tiles, const u32x4 *__restrict__ elems,
                                                     const uint32_t *__restrict__ hist2, u32x4 *__restrict__ pts) {
-    __shared__ uint32_t cnt[kOW][kHighBins], part[kHighBins];
+    __shared__ PassShared<7> sh;
     const int tid = threadIdx.x, t = blockIdx.x, b = blockIdx.y;
     int lo, hi;
     tile_range(N, tiles, t, lo, hi);
-    const uint32_t *in = elems + (size_t)b * N;
-    const float *p = xyz + (size_t)b * N * 3;
+    const u32x4 *in = elems + (size_t)b * N;
     u32x4 *out = pts + (size_t)b * N;
-    stable_pass<7>(hist2 + (size_t)b * tiles * kHighBins, tiles, t, lo, hi, tid, cnt, part,
-                   [&](int i) { return in[i] >> kIndexBits; },
-                   [&](int i, uint32_t pos) {
-                       const uint32_t k = in[i] & ((1u << kIndexBits) - 1u);
-                       out[pos] = u32x4{f2u(p[3 * (size_t)k]), f2u(p[3 * (size_t)k + 1]), f2u(p[3 * (size_t)k + 2]), k};
-                   });
+    stable_pass<7>(hist2 + (size_t)b * tiles * kHighBins, tiles, t, lo, hi, tid, sh, [&](int i) { return in[i]; },
+                   [&](const u32x4 &e) { return e.w >> kIndexBits; },
+                   [&](const u32x4 &e, int) { return u32x4{e.x, e.y, e.z, e.w & ((1u << kIndexBits) - 1u)}; },
+                   [&](const u32x4 &x, uint32_t pos) { out[pos] = x; });
 }
 
 // ---- the picks in their order ----------------------------------------------------
@@ -329,28 +409,6 @@ struct FinishArgs {
     int *status;
 };
 
-// Sum over the lanes up to this one, and over the waves of the block before it: an exclusive prefix; `total` receives the sum.
-template <int WAVES>
-__device__ __forceinline__ uint32_t block_before(uint32_t v, uint32_t *part, int tid, uint32_t *total) {
-    const int lane = tid & 63, wave = tid >> 6;
-    uint32_t s = v;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const uint32_t u = __shfl_up(s, o);
-        s += lane >= o ? u : 0u;
-    }
-    if (lane == 63) part[wave] = s;
-    __syncthreads();
-    uint32_t before = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < WAVES; ++w) {
-        const uint32_t c = part[w];
-        before += w < wave ? c : 0u;
-        all += c;
-    }
-    *total = all;
-    return before + s - v;
-}
 // Place of a bin in LDS, where neighbours and every 64th bin lie in different banks.
 __device__ __forceinline__ uint32_t bank_place(uint32_t bin) { return bin ^ ((bin >> 6) & 31u); }
 
@@ -592,12 +650,12 @@ hipError_t launch_order(const float *xyz, int B, int N, const LocalBuffers &l, i
     if (N > 1 << kIndexBits) return hipErrorInvalidValue;
     const int tiles = order_tiles(N);
     const dim3 grid(tiles, B);
-    uint32_t *elems = (uint32_t *)l.picks;  // the picks come later
+    u32x4 *elems = (u32x4 *)l.picks;  // the picks come later
     k_order_box<<<grid, dim3(kOT), 0, s>>>(xyz, N, tiles, l.boxes, (uint32_t *)l.zeroed, (long)(l.zero_bytes / 4), clear_status);
     k_order_code<<<grid, dim3(kOT), 0, s>>>(xyz, N, tiles, l.boxes, l.codes, l.hist1);
-    k_order_low<<<grid, dim3(kOT), 0, s>>>(N, tiles, l.codes, l.hist1, elems);
+    k_order_low<<<grid, dim3(kOT), 0, s>>>(xyz, N, tiles, l.codes, l.hist1, elems);
     k_order_count<<<grid, dim3(kOT), 0, s>>>(N, tiles, elems, l.hist2);
-    k_order_high<<<grid, dim3(kOT), 0, s>>>(xyz, N, tiles, elems, l.hist2, (u32x4 *)l.pts);
+    k_order_high<<<grid, dim3(kOT), 0, s>>>(N, tiles, elems, l.hist2, (u32x4 *)l.pts);
     return hipGetLastError();
 }
 
