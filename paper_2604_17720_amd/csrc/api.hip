@@ -244,7 +244,7 @@ int kernel_for(int B, int N, int M, int variant, const Device &dev, size_t local
     if (any_rounds(M, variant) && takes_block(B, N)) return FFPS_KERNEL_BLOCK;
     if (v == FFPS_VARIANT_WG) return FFPS_KERNEL_WG;
     if (any_rounds(M, variant) && takes_local(B, N, M, v, dev.num_cu)) {
-        const LocalPlan plan = plan_fps_local(B, N, dev.num_cu);
+        const LocalPlan plan = plan_fps_local(B, N, M, dev.num_cu);
         size_t bytes = 0;
         if (plan.wg_per_cloud > 0) {
             carve_local(nullptr, B, N, plan, &bytes);
@@ -278,7 +278,7 @@ int run_exact(const float *xyz, int B, int N, int M, int start, const int *start
         return hip_rc(launch_fps_wg(xyz, B, N, M, start, start_dev, idx, idx_stride, md, md_stride,
                                     variant_picks(variant), (int *)(ws + w.status), s));
     if (kernel == FFPS_KERNEL_LOCAL) {
-        const LocalPlan plan = plan_fps_local(B, N, dev.num_cu);
+        const LocalPlan plan = plan_fps_local(B, N, M, dev.num_cu);
         const LocalBuffers l = carve_local(ws + w.local, B, N, plan, nullptr);
         int *status = (int *)(ws + w.status);
         int rc = hip_rc(launch_order(xyz, B, N, l, clear ? status : nullptr, s));

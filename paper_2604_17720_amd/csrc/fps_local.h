@@ -15,13 +15,13 @@ constexpr int kLocalWords = kLocalBins + kLocalMaxUnits;  // picks per bin, pick
 // counting does not queue up at one memory channel.
 __host__ __device__ __forceinline__ uint32_t local_bin_place(uint32_t bin) { return ((bin & 63u) << 7) | ((bin >> 6) & 127u); }
 
-// How B clouds of N points are laid over the device.
+// How B clouds of N points, of which M are sampled, are laid over the device.
 struct LocalPlan {
     int wg_per_cloud;       // 0: the kernel does not take such clouds
     int clouds_per_launch;
     int units_per_cloud;
 };
-LocalPlan plan_fps_local(int B, int N, int num_cu);
+LocalPlan plan_fps_local(int B, int N, int M, int num_cu);
 
 struct LocalBuffers {  // device memory of one call
     void *pts;          // [B][N] 16 bytes: the points in order; later the keys of the picks

@@ -883,12 +883,21 @@ constexpr int kUnitMax = kMaxRows * kWave;
 
 }  // namespace
 
-LocalPlan plan_fps_local(int B, int N, int num_cu) {
+// Workgroups of a cloud.  A row of points per unit is where a unit costs least, but smaller ones make fewer rounds, as
+// long as there are not so many that the first rounds, in which all see all, cost more than that saves.  us with
+// 512, 256 and 171 points per workgroup: 9000 points to 4000 435, 342, 318 (128 points: 295); 16,384 to 4096 369, 333, 316;
+// 30,000 of a room to 2000 295, 288, 318; 30,000 of a LiDAR frame to 2500 465, 368, 359; 45,678 to 5001 341, 355, 364.
+// So up to 88 workgroups have down to 128 points.  With a quarter of the points as samples most rounds are late ones: 60,000
+// to 25,000 500, 462, 472; 120,000 to 30,000 591, 561, 568; 60,000 to 5000 326, 339, 351: 256 points there.
+LocalPlan plan_fps_local(int B, int N, int M, int num_cu) {
     const int maxG = num_cu < kMaxGridWG ? num_cu : kMaxGridWG;
     LocalPlan p = {0, 0, 0};
     const int need = (N + kWaves * kUnitMax - 1) / (kWaves * kUnitMax);
     if (need > maxG) return p;
-    int g = (N + kThreads - 1) / kThreads;  // a row of points per unit
+    auto per = [&](int points) { return (N + points - 1) / points; };
+    int g = per(kThreads);
+    if (g < 88) g = per(128) < 88 ? per(128) : 88;
+    if ((long)M * 4 >= N && g < per(256)) g = per(256);
     const int share = maxG / (B < maxG ? B : maxG);
     if (g > share) g = share;
     if (g < need) g = need;
@@ -930,7 +939,7 @@ int local_capacity() { return kMaxGridWG * kWaves * kUnitMax; }
 
 size_t local_workspace_bound(int B, int N) {
     // no device gives a cloud more workgroups than this, whatever it has
-    LocalPlan p = plan_fps_local(B, N, kMaxGridWG);
+    LocalPlan p = plan_fps_local(B, N, N, kMaxGridWG);  // nor has fewer samples more of them
     const int need = (N + kWaves * kUnitMax - 1) / (kWaves * kUnitMax);
     if (p.wg_per_cloud < need) p.wg_per_cloud = need;
     p.units_per_cloud = p.wg_per_cloud * kWaves;

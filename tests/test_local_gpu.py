@@ -53,6 +53,9 @@ CASES = {
     "many clouds of few samples": (lambda: np.stack([inputs.uniform_cube(4700, i) for i in range(270)]), 90, 3, "BLOCK"),
     "clusters in many clouds": (lambda: np.stack([inputs.planes_and_clusters(5003, i) for i in range(37)]), 600, 1, "GRID"),
     "equal values, bins sorted in LDS": (lambda: inputs.lattice_grid(40, 40, 8)[None], 3000, 0),
+    "as many small workgroups as there are, exactly": (lambda: inputs.room(11264, 5)[None], 3000, 7),
+    "one point more than that": (lambda: inputs.room(11265, 5)[None], 3000, 11264),
+    "half a row per unit for many samples": (lambda: inputs.planes_and_clusters(30001, 5)[None], 7501, 1),
     "equal values in sixteen rows": (lambda: inputs.lattice_grid(160, 128, 102)[None], 200, 0),
     "equal values in rows that are read again": (lambda: inputs.lattice_grid(160, 128, 108)[None], 200, 0),
     "clusters": (lambda: np.stack([inputs.planes_and_clusters(9001, 50 + i) for i in range(4)]), 4000, 1),
