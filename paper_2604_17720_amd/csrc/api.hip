@@ -35,8 +35,11 @@ struct Workspace {  // byte offsets into the caller's workspace
     }
 };
 
-// Least points x samples of k_fps_local, and its least samples (see takes_local).
+// Least points x samples of k_fps_local, in general and for small clouds that have at least so many workgroups each, and its
+// least samples (see takes_local).
 constexpr long kLocalWork = 1L << 25;
+constexpr int kLocalFew = 17, kLocalSmallMax = 8192, kLocalMediumMax = 65536;
+constexpr long local_work_small(int share) { return share >= 64 ? 3L << 20 : 5L << 20; }
 constexpr int kLocalSamples = 80;
 
 Workspace carve(int B, int N, int M) {
@@ -52,7 +55,9 @@ Workspace carve(int B, int N, int M) {
     w.spos = o;     o += align_up((size_t)B * sizeof(int));
     // Neither clouds of one workgroup nor too few samples go to the local-maximum kernel, and what a call
     // samples on the way (candidates, stages) has no more points and no more samples.
-    const bool local = N > wgm_capacity() && N <= local_capacity() && (long)N * M >= kLocalWork && M >= kLocalSamples &&
+    const int share = kMaxGridWG / B;
+    const long least = share >= kLocalFew && N <= kLocalMediumMax ? local_work_small(share) : kLocalWork;
+    const bool local = N > wgm_capacity() && N <= local_capacity() && (long)N * M >= least && M >= kLocalSamples &&
                        B <= kMaxBatchHelpers;
     w.least = w.local = o;
     w.local_bytes = local ? align_up(local_workspace_bound(B, N)) : 0;
@@ -203,6 +208,17 @@ bool takes_block(int B, int N) {
 // 200,000 normally distributed points to 2048 take 575 against 527 us (a million to 2048 748 against 891), 300,000
 // points of which five in a hundred lie around the others at up to 100 times the extent, to 16,384, 3150 against 2210.
 //
+// Those were the figures of 512 points per workgroup and of units that publish one point.  Now small clouds have more
+// and smaller units, and the lines of up to fifteen clouds below 65,536 points lie lower (k_fps_grid against k_fps_local, us,
+// a room / planes / LiDAR): 5000 points to 625 220, 248, 267 against 217, 224, 236, to 1250 298, 348, 364 against 233, 247, 245,
+// but to 312 175, 186, 201 against 197, 210, 210; 7000 to 875 262, 277 against 221, 237; eight clouds (planes, LiDAR) of 5000 to
+// 625 246, 305 against 259, 276, to 1250 340, 402 against 294, 305; 9000 to 2250 417, 429, 516 against 255, 270, 302;
+// 12,000 to 1500 352, 338 against 246, 272.  A lattice of 8000 to 1000 3111 against 475.  Clouds of tails still lose: a cube
+// with five points in a hundred at up to 100 times the extent, 6000 to 1000 315 against 350, 9000 to 1500 403 against 463,
+// 16,000 to 1500 465 against 528, but 9000 to 3000 556 against 500, so beyond 8192 points the line is 9 x 2^21.
+// With more than 4 samples of 9 points it stays at 2^25 (that would gain as well: 8192 to 4095 579 against 300; the tests of
+// k_fps_grid sample small clouds whole).
+//
 // Many clouds leave each few workgroups, and what is gained shrinks, for LiDAR stretches first: 12 clouds of
 // 30,000 to 7500 812, 890, 1591 against 1310, 1405, 1687; 16 clouds (16 workgroups each) of 16,384 to 4096 668, 717,
 // 848 against 804, 834, 967, but of 30,000 to 7500 982, 1069, 1970 against 1554, 1613, 1860; 32 of 9000 to 4500 925, 974, 1454 against 930, 999, 1071; 64 of 30,000 to 7500 3117, 3522,
@@ -211,13 +227,17 @@ bool takes_block(int B, int N) {
 // them in batches.
 constexpr long kLocalWorkLarge = 1L << 26;  // beyond 65,536 points
 constexpr long kLocalWorkMany = 3L << 27;   // many clouds
+constexpr long kLocalWorkMedium = 9L << 21; // 8193 to 65,536 points
 bool takes_local(int B, int N, int M, int v, int num_cu) {
     const long work = (long)N * M;
-    if (B > kMaxBatchHelpers || work < kLocalWork || M < kLocalSamples) return false;
-    if (v == FFPS_VARIANT_STREAM) return true;
+    if (B > kMaxBatchHelpers || M < kLocalSamples) return false;
+    if (v == FFPS_VARIANT_STREAM) return work >= kLocalWork;
     const int share = (num_cu < kMaxGridWG ? num_cu : kMaxGridWG) / B;  // workgroups of a cloud
     if (B > 1 && (share < 16 || (share == 16 && N > 1024 * share))) return work >= kLocalWorkMany;
-    return work >= (N > 65536 ? kLocalWorkLarge : kLocalWork) && M >= 96 + N / 65536;
+    if (M < 96 + N / 65536) return false;
+    if (N > kLocalMediumMax) return work >= kLocalWorkLarge;
+    if (share < kLocalFew || 9L * M > 4L * N) return work >= kLocalWork;
+    return N > kLocalSmallMax ? work >= kLocalWorkMedium : work >= local_work_small(share) && 8L * M >= N;
 }
 
 // Clouds that are rows of a larger array: point i of cloud b is row idx[b][i] of [B][points]

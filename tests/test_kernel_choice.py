@@ -71,3 +71,16 @@ def test_no_area_for_calls_that_cannot_use_it(b, n, m):
     up = lambda v: (v + 255) // 256 * 256
     assert fb.ffps_workspace_bytes(b, n, m) == 256 + 256 * 2 * 6 * 256 * 16 + up(12 * b * n) + up(4 * b * m) + \
         up(4 * b * ((n + 31) // 32)) + 2 * up(4 * b * n) + up(4 * b)
+
+
+def test_small_clouds_go_to_local_maxima_early():
+    """Up to fifteen clouds: an eighth of the points as samples where a cloud is small, a line of its own up to
+    65,536 points, and a workspace has the area wherever a call or one of its stages may use it."""
+    local, grid = fb.FFPS_KERNEL_LOCAL, fb.FFPS_KERNEL_GRID
+    assert [kernel(1, 5000, m) for m in (624, 625, 629, 630, 2222, 2223)] == [grid, grid, grid, local, local, grid]
+    assert [kernel(b, 5000, 1000) for b in (4, 5, 15, 16)] == [local, grid, grid, grid]
+    assert [kernel(b, 5000, 1049) for b in (4, 5, 15, 16)] == [local, local, local, grid]
+    assert [kernel(1, 8192, m) for m in (1023, 1024)] == [grid, local]
+    assert [kernel(15, 8193, m) for m in (2303, 2304)] == [grid, local]
+    assert [kernel(1, 65536, m) for m in (287, 288)] == [grid, local]
+    assert fb.ffps_workspace_bytes(1, 12000, 300) > fb.ffps_workspace_bytes(1, 12000, 262)

@@ -56,6 +56,13 @@ CASES = {
     "as many small workgroups as there are, exactly": (lambda: inputs.room(11264, 5)[None], 3000, 7),
     "one point more than that": (lambda: inputs.room(11265, 5)[None], 3000, 11264),
     "half a row per unit for many samples": (lambda: inputs.planes_and_clusters(30001, 5)[None], 7501, 1),
+    "smallest of all that has the work for it": (lambda: inputs.uniform_cube(4609, 1)[None], 683, 4608),
+    "small, equal values": (lambda: inputs.lattice_grid(20, 20, 20)[None], 1000, 0),
+    "small, a line": (lambda: inputs.lattice_line(5000)[None], 2000, 0),
+    "small, one place": (lambda: np.ones((1, 6000, 3), np.float32), 800, 3),
+    "small, duplicates": (lambda: _dup(6000, 8)[None], 1600, 0),
+    "fifteen small ones": (lambda: np.stack([inputs.planes_and_clusters(4999, 90 + i) for i in range(15)]), 1049, 3),
+    "an outlier, small": (lambda: _outlier(8000), 1100, 1),
     "equal values in sixteen rows": (lambda: inputs.lattice_grid(160, 128, 102)[None], 200, 0),
     "equal values in rows that are read again": (lambda: inputs.lattice_grid(160, 128, 108)[None], 200, 0),
     "clusters": (lambda: np.stack([inputs.planes_and_clusters(9001, 50 + i) for i in range(4)]), 4000, 1),
