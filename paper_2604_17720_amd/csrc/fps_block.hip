@@ -4,7 +4,7 @@
 // What bounds a cloud this small is the number of instructions of a round (with two waves on a
 // SIMD an instruction costs about eight cycles).  k_fps_wgm takes 20 to 30 picks a round but
 // needs about 12,000 cycles for it: pairwise masks of 64 candidates, one wave that settles them,
-// and every pick applied to every point.  Here a round has ten picks and takes 1.2 us (1024 points):
+// and every pick applied to every point.  Here a round has eleven picks and takes 1.3 us (1024 points):
 //   - The points are put along a space-filling curve (two stable radix passes in LDS, by cells of a
 //     grid over the cloud or, where that would not do, by splitters: fps_space.h); a UNIT
 //     is a row of 16 lanes with P points each, 32 units in eight waves, so that everything a

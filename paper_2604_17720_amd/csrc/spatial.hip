@@ -6,10 +6,11 @@
 // its box, 15-bit keys that ascend with 30-bit codes (fps_space.h: 256 splitters, 128 places between two);
 // a radix sort of 8 and 7 bits.  Both passes are stable, so the order, and with it every round of the
 // kernel, is the same in each run.  Five launches: boxes of tiles; keys and counts of the low digit; low digit;
-// counts of the high digit in tiles of that order; high digit with the gather of the coordinates.
+// counts of the high digit in tiles of that order; high digit.  The points themselves move in both passes (gathered at random
+// by the second one alone, five million took 104 us there and 34 in the first).
 // A block adds up the counts of all tiles itself instead of a scan of its own.  (The high digits
 // counted by the pass that moves the low ones, with an atomic in memory per point, took 256 us of
-// five million points; the pass and the counts by themselves take 60 and 18 us.)
+// five million points; the pass and the counts by themselves took 60 and 18 us then.)
 //
 // Picks: k_fps_local counts them in 8192 bins by value (32 bins to a factor of two), so a pick's
 // bin is known at once; bins are sorted in LDS, by 1024 sub-bins first.
@@ -59,7 +60,7 @@ __device__ __forceinline__ uint32_t block_before(uint32_t v, uint32_t *part, int
     return before + s - v;
 }
 // Points of a thread that are on their way at once in the passes over a cloud.  One after another, five million points
-// took 20, 28 and 18 us (boxes, keys, counts); 62 and 116 us the two passes that move them.
+// took 20, 28 and 18 us (boxes, keys, counts), 12, 26 and 19 now, and 62 and 116 us the two passes that move them, 44 and 41 now.
 constexpr int kTogether = 4;
 
 struct Ext { float lo[3], hi[3]; };
