@@ -214,7 +214,7 @@ bool takes_block(int B, int N) {
 // but to 312 175, 186, 201 against 197, 210, 210; 7000 to 875 262, 277 against 221, 237; eight clouds (planes, LiDAR) of 5000 to
 // 625 246, 305 against 259, 276, to 1250 340, 402 against 294, 305; 9000 to 2250 417, 429, 516 against 255, 270, 302;
 // 12,000 to 1500 352, 338 against 246, 272.  A lattice of 8000 to 1000 3111 against 475.  Clouds of tails still lose: a cube
-// with five points in a hundred at up to 100 times the extent, 6000 to 1000 315 against 350, 9000 to 1500 403 against 463,
+// with five points in a hundred at up to 100 times the extent, 6000 to 1000 315 against 350 (Cauchy distributed 283 against 354), 9000 to 1500 403 against 463,
 // 16,000 to 1500 465 against 528, but 9000 to 3000 556 against 500, so beyond 8192 points the line is 9 x 2^21.
 // With more than 4 samples of 9 points it stays at 2^25 (that would gain as well: 8192 to 4095 579 against 300; the tests of
 // k_fps_grid sample small clouds whole).

@@ -60,8 +60,12 @@ __device__ __forceinline__ uint32_t row_bits(uint64_t m, int lane) {
 }
 __device__ __forceinline__ uint64_t key_of(const u32x4 &rec) { return ((uint64_t)rec.y << 32) | rec.x; }
 
+// Waves per SIMD the registers have to leave room for.  With two points per lane six (three clouds on a CU): 80 registers,
+// five of them spilled outside the rounds.  With 86 a CU holds two clouds, and 600 of 1000 points to 300 took 115 us, 101 now.
+constexpr int waves_per_simd(int P) { return P == 2 ? 6 : 2; }
+
 template <int P>
-__global__ __launch_bounds__(kBlockThreads, 2) void k_fps_block(BlockArgs a) {
+__global__ __launch_bounds__(kBlockThreads, waves_per_simd(P)) void k_fps_block(BlockArgs a) {
     constexpr int kCap = kBlockThreads * P;
     constexpr bool kTwo = P > 1;  // units report their second points
     // coordinates by index and the order, later the keys of the picks
