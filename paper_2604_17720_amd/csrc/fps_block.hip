@@ -64,10 +64,18 @@ __device__ __forceinline__ uint64_t key_of(const u32x4 &rec) { return ((uint64_t
 // five of them spilled outside the rounds.  With 86 a CU holds two clouds, and 600 of 1000 points to 300 took 115 us, 101 now.
 constexpr int waves_per_simd(int P) { return P == 2 ? 6 : 2; }
 
-template <int P>
+// Clouds of a launch beyond which a CU holds several workgroups: FAR below.
+constexpr int kOnePerCu = 256;
+
+// FAR: a wave passes over the half of the units that is not around it where the boxes are too far apart for every lane.  With
+// one workgroup on a CU that is slower (the test comes before the loads: 1 to 3 % of 1024 and 4096 points); with several,
+// instructions count, and LiDAR stretches and clusters have such halves: 512 clouds of 3000 to 700 303 and 178 us without, 281 and
+// 167 with it, cubes and rooms the same.
+template <int P, bool FAR>
 __global__ __launch_bounds__(kBlockThreads, waves_per_simd(P)) void k_fps_block(BlockArgs a) {
     constexpr int kCap = kBlockThreads * P;
     constexpr bool kTwo = P > 1;  // units report their second points
+    constexpr bool kTwoOfTies = P <= 3;  // also where values are equal (see report)
     // coordinates by index and the order, later the keys of the picks
     __shared__ __attribute__((aligned(16))) float sx[4 * kCap];
     uint32_t *order = reinterpret_cast<uint32_t *>(sx + 3 * kCap);
@@ -256,8 +264,9 @@ __global__ __launch_bounds__(kBlockThreads, waves_per_simd(P)) void k_fps_block(
         bool win = f2u(t1) == top;
         float bx = x[0], by = y[0], bz = z[0];
         uint32_t bi = id[0];
-        if (__builtin_popcountll(__builtin_amdgcn_ballot_w64(win)) == 4 &&
-            (P == 1 || __builtin_amdgcn_ballot_w64(f2u(t2) == top) == 0)) {
+        const bool tied = __builtin_popcountll(__builtin_amdgcn_ballot_w64(win)) != 4 ||
+                          (P > 1 && __builtin_amdgcn_ballot_w64(f2u(t2) == top) != 0);
+        if (!tied) {
 #pragma unroll
             for (int j = 1; j < P; ++j) {
                 const bool e = f2u(m[j]) == top;
@@ -280,17 +289,24 @@ __global__ __launch_bounds__(kBlockThreads, waves_per_simd(P)) void k_fps_block(
         }
         const uint32_t rest = f2u(win ? t2 : t1), second = row_max_all(rest);
         if constexpr (kTwo) {
-            // Of equal seconds any will do: the third value is the same then.  So it is taken to be where a lane
-            // holds the two best: its own third value is not known.
-            const bool win2 = l16 == __builtin_ctz(row_bits(__builtin_amdgcn_ballot_w64(rest == second), lane) | 0x10000u);
-            const uint32_t third = row_max_all(win2 ? f2u(t2) : rest);
-            float cx = x[0], cy = y[0], cz = z[0];
+            if (!kTwoOfTies && tied) {
+                // The others may be as large as the second, wherever that lies.  In lattices the second points release 3 picks of
+                // a hundred, elsewhere 20 to 40: without looking for them 3000 points to 1500 take 819 us, with 855, 4096 to 1024 554 and 570.
+                // (With two or three points per lane it is the other way round: 1500 to 700 328 without, 318 with.)
+                if (l16 == 0) recC[unit] = u32x4{f2u(__builtin_inff()), f2u(__builtin_inff()), f2u(__builtin_inff()), second};
+            } else {
+                // Of equal seconds any will do: the third value is the same then.  So it is taken to be where a lane
+                // holds the two best: its own third value is not known.
+                const bool win2 = l16 == __builtin_ctz(row_bits(__builtin_amdgcn_ballot_w64(rest == second), lane) | 0x10000u);
+                const uint32_t third = row_max_all(win2 ? f2u(t2) : rest);
+                float cx = x[0], cy = y[0], cz = z[0];
 #pragma unroll
-            for (int j = 1; j < P; ++j) {
-                const bool e = f2u(m[j]) == second;
-                cx = e ? x[j] : cx; cy = e ? y[j] : cy; cz = e ? z[j] : cz;
+                for (int j = 1; j < P; ++j) {
+                    const bool e = f2u(m[j]) == second;
+                    cx = e ? x[j] : cx; cy = e ? y[j] : cy; cz = e ? z[j] : cz;
+                }
+                if (win2) recC[unit] = u32x4{f2u(cx), f2u(cy), f2u(cz), third};
             }
-            if (win2) recC[unit] = u32x4{f2u(cx), f2u(cy), f2u(cz), third};
         }
         pvb = top;
         if (win) {
@@ -303,6 +319,7 @@ __global__ __launch_bounds__(kBlockThreads, waves_per_simd(P)) void k_fps_block(
     const int base = (wave * 4 + kBlockUnits - 6) & (kBlockUnits - 1);
     const int u0 = (base + l16) & (kBlockUnits - 1), u1 = u0 ^ 16;
     const Box b0 = ubox[u0], b1 = ubox[u1];
+    const uint32_t g1 = f2u(box_box(box, b1));  // not above the distance of any two of their points
     report();
 
     // ---- rounds ----
@@ -315,8 +332,9 @@ __global__ __launch_bounds__(kBlockThreads, waves_per_simd(P)) void k_fps_block(
         ++round;
         const uint32_t par = round & 1;
         wg_barrier();  // records
-        const u32x4 rA = recA[unit], a0 = recA[u0], a1 = recA[u1], d0 = recC[u0], d1 = recC[u1];
-        const u32x2 rB = recB[unit], c0 = recB[u0], c1 = recB[u1];
+        const bool far = !FAR || __builtin_amdgcn_ballot_w64(g1 < pvb) != 0;  // a unit of the other half may matter
+        const u32x4 rA = recA[unit], a0 = recA[u0], d0 = recC[u0];
+        const u32x2 rB = recB[unit], c0 = recB[u0];
         const float pv = u2f(pvb), px = u2f(rA.w), py = u2f(rB.x), pz = u2f(rB.y);
         const uint64_t kp = key_of(rA);
         auto holds = [&](const u32x4 &A, const u32x2 &B, const u32x4 &C, const Box &b) {
@@ -327,7 +345,14 @@ __global__ __launch_bounds__(kBlockThreads, waves_per_simd(P)) void k_fps_block(
             else
                 return (key_of(A) > kp) & (first | ((A.z >= pvb) & near));
         };
-        const bool held = holds(a0, c0, d0, b0) | holds(a1, c1, d1, b1);
+        bool held;
+        if (far) {
+            const u32x4 a1 = recA[u1], d1 = recC[u1];
+            const u32x2 c1 = recB[u1];
+            held = holds(a0, c0, d0, b0) | holds(a1, c1, d1, b1);
+        } else {
+            held = holds(a0, c0, d0, b0);
+        }
         const bool pick = (pvb != 0u) & (n_list < n_mine) & (row_bits(__builtin_amdgcn_ballot_w64(held), lane) == 0u);
         if (l16 == 0) {
             pick_of[unit] = u32x4{f2u(px), f2u(py), f2u(pz), pick ? pvb : 0u};
@@ -365,7 +390,7 @@ __global__ __launch_bounds__(kBlockThreads, waves_per_simd(P)) void k_fps_block(
             return box_dist(box, u2f(q.x), u2f(q.y), u2f(q.z)) < u2f(umin(pvb, q.w));
         };
         uint32_t hits = row_bits(__builtin_amdgcn_ballot_w64(reaches(q0)), lane);
-        hits |= row_bits(__builtin_amdgcn_ballot_w64(reaches(q1)), lane) << 16;
+        if (far) hits |= row_bits(__builtin_amdgcn_ballot_w64(reaches(q1)), lane) << 16;
         if (__builtin_amdgcn_ballot_w64(hits != 0) == 0) continue;
         do {
             const int h0 = hits ? (base + __builtin_ctz(hits)) & (kBlockUnits - 1) : kBlockUnits;
@@ -492,7 +517,12 @@ __global__ __launch_bounds__(kBlockThreads, waves_per_simd(P)) void k_fps_block(
 
 template <int P>
 hipError_t launch_t(const BlockArgs &a, int B, hipStream_t s) {
-    k_fps_block<P><<<dim3(B), dim3(kBlockThreads), 0, s>>>(a);
+    // more points per lane fill a CU's LDS; fewer gain nothing (one) or spill (two: 768 clouds of 700 3 % slower)
+    constexpr bool kSeveral = P >= 3 && P <= 8;
+    if (kSeveral && B > kOnePerCu)
+        k_fps_block<P, kSeveral><<<dim3(B), dim3(kBlockThreads), 0, s>>>(a);
+    else
+        k_fps_block<P, false><<<dim3(B), dim3(kBlockThreads), 0, s>>>(a);
     return hipGetLastError();
 }
 

@@ -13,6 +13,13 @@ def _shape(b, n):
     return np.stack([inputs.shape_cloud(n, 61000 + 5 * n + i) for i in range(b)])
 
 
+def _far_clusters(b, n):
+    """Eight clusters far apart in each cloud: most units are out of one another's reach, all of a half at times."""
+    r = np.random.default_rng(n)
+    c = r.uniform(-1, 1, (b, 8, 3)) * 100
+    return (np.take_along_axis(c, r.integers(0, 8, (b, n))[..., None], 1) + r.uniform(-.5, .5, (b, n, 3))).astype(np.float32)
+
+
 CASES = {
     # name: (clouds, M, start); a row of 16 lanes holds 16 points per step, 32 rows make the cloud
     "smallest": (lambda: _shape(3, 257), 257, 256),
@@ -29,6 +36,12 @@ CASES = {
     "many clouds, twelve per lane": (lambda: _shape(80, 4609), 300, 4608),
     "many clouds, sixteen per lane": (lambda: _shape(81, 8192), 400, 8191),
     "more clouds than CUs": (lambda: _shape(300, 700), 90, 2),
+    "more clouds than CUs, three per lane": (lambda: _far_clusters(257, 1537), 300, 2),
+    "more clouds than CUs, four per lane": (lambda: np.concatenate([_shape(30, 1800), _far_clusters(240, 1800)]), 200, 2),
+    "more clouds than CUs, six per lane": (lambda: _far_clusters(257, 3072), 150, 2),
+    "more clouds than CUs, eight per lane": (lambda: np.concatenate([_shape(30, 4096), _far_clusters(230, 4096)]), 100, 2),
+    "more clouds than CUs, equal values": (lambda: np.repeat(inputs.lattice_grid(16, 16, 12)[None], 258, 0), 300, 5),
+    "equal values, four per lane": (lambda: inputs.lattice_grid(16, 16, 8)[None], 2048, 1),
     "planes": (lambda: np.stack([inputs.planes_and_clusters(4001, i) for i in range(5)]), 1500, 1),
     "lattice, many equal values": (lambda: inputs.lattice_grid(16, 16, 12)[None], 2000, 0),
     "a line": (lambda: inputs.lattice_line(1500)[None], 1500, 0),
