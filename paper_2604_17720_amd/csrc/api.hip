@@ -40,6 +40,7 @@ struct Workspace {  // byte offsets into the caller's workspace
 constexpr long kLocalWork = 1L << 25;
 constexpr int kLocalFew = 17, kLocalSmallMax = 8192, kLocalMediumMax = 65536;
 constexpr long local_work_small(int share) { return share >= 64 ? 3L << 20 : 5L << 20; }
+constexpr long kLocalWorkMedium = 9L << 21;  // 8193 to 65,536 points
 constexpr int kLocalSamples = 80;
 
 Workspace carve(int B, int N, int M) {
@@ -53,12 +54,14 @@ Workspace carve(int B, int N, int M) {
     w.mind = o;     o += align_up((size_t)B * N * sizeof(float));
     w.cand = o;     o += align_up((size_t)B * N * sizeof(int32_t));
     w.spos = o;     o += align_up((size_t)B * sizeof(int));
-    // Neither clouds of one workgroup nor too few samples go to the local-maximum kernel, and what a call
-    // samples on the way (candidates, stages) has no more points and no more samples.
+    // Neither clouds of one workgroup nor too few samples go to the local-maximum kernel.  What a call samples on the
+    // way (candidates, stages) has no more points and no more samples, but small clouds have lower lines: the work of
+    // as many of the points as are a small cloud decides, too.
     const int share = kMaxGridWG / B;
-    const long least = share >= kLocalFew && N <= kLocalMediumMax ? local_work_small(share) : kLocalWork;
-    const bool local = N > wgm_capacity() && N <= local_capacity() && (long)N * M >= least && M >= kLocalSamples &&
-                       B <= kMaxBatchHelpers;
+    auto work = [&](int points) { return (long)(N < points ? N : points) * M; };
+    const bool enough = work(N) >= kLocalWork || (share >= kLocalFew && (work(kLocalSmallMax) >= local_work_small(share) ||
+                                                                         work(kLocalMediumMax) >= kLocalWorkMedium));
+    const bool local = N > wgm_capacity() && N <= local_capacity() && enough && M >= kLocalSamples && B <= kMaxBatchHelpers;
     w.least = w.local = o;
     w.local_bytes = local ? align_up(local_workspace_bound(B, N)) : 0;
     w.total = o + w.local_bytes;
@@ -227,7 +230,6 @@ bool takes_block(int B, int N) {
 // them in batches.
 constexpr long kLocalWorkLarge = 1L << 26;  // beyond 65,536 points
 constexpr long kLocalWorkMany = 3L << 27;   // many clouds
-constexpr long kLocalWorkMedium = 9L << 21; // 8193 to 65,536 points
 bool takes_local(int B, int N, int M, int v, int num_cu) {
     const long work = (long)N * M;
     if (B > kMaxBatchHelpers || M < kLocalSamples) return false;

@@ -68,14 +68,18 @@ def test_a_workspace_sized_for_other_clouds():
 @pytest.mark.parametrize("b,n,m", [(4096, 4700, 90), (1, 200000, 167), (1, 1000000, 33), (1, 5000000, 6), (70000, 9000, 4000)])
 def test_no_area_for_calls_that_cannot_use_it(b, n, m):
     assert kernel(b, n, m) != fb.FFPS_KERNEL_LOCAL
+    assert fb.ffps_workspace_bytes(b, n, m) == _least(b, n, m)
+
+
+def _least(b, n, m):
+    """What a workspace needs without the area of the local-maximum kernel."""
     up = lambda v: (v + 255) // 256 * 256
-    assert fb.ffps_workspace_bytes(b, n, m) == 256 + 256 * 2 * 6 * 256 * 16 + up(12 * b * n) + up(4 * b * m) + \
-        up(4 * b * ((n + 31) // 32)) + 2 * up(4 * b * n) + up(4 * b)
+    return 256 + 256 * 2 * 6 * 256 * 16 + up(12 * b * n) + up(4 * b * m) + up(4 * b * ((n + 31) // 32)) + 2 * up(4 * b * n) + up(4 * b)
 
 
 def test_small_clouds_go_to_local_maxima_early():
     """Up to fifteen clouds: an eighth of the points as samples where a cloud is small, a line of its own up to
-    65,536 points, and a workspace has the area wherever a call or one of its stages may use it."""
+    65,536 points."""
     local, grid = fb.FFPS_KERNEL_LOCAL, fb.FFPS_KERNEL_GRID
     assert [kernel(1, 5000, m) for m in (624, 625, 629, 630, 2222, 2223)] == [grid, grid, grid, local, local, grid]
     assert [kernel(b, 5000, 1000) for b in (4, 5, 15, 16)] == [local, grid, grid, grid]
@@ -83,4 +87,22 @@ def test_small_clouds_go_to_local_maxima_early():
     assert [kernel(1, 8192, m) for m in (1023, 1024)] == [grid, local]
     assert [kernel(15, 8193, m) for m in (2303, 2304)] == [grid, local]
     assert [kernel(1, 65536, m) for m in (287, 288)] == [grid, local]
-    assert fb.ffps_workspace_bytes(1, 12000, 300) > fb.ffps_workspace_bytes(1, 12000, 262)
+
+
+def test_candidates_and_stages_have_the_area():
+    """What a call samples on the way has no more points and no more samples than the call; where that is a case for
+    local maxima, the workspace of the call holds its area."""
+    sizes = (4609, 4700, 6000, 8192, 8193, 9500, 12953, 20000, 52500, 65536, 65537, 70000, 100000, 400000, 3000000)
+    samples = (96, 300, 470, 512, 700, 921, 922, 1200, 1536, 1537, 1667, 2098, 3000, 6000, 40000)
+    used = 0
+    for b in (1, 4, 5, 15, 16, 17):
+        for n in sizes:
+            for m in [s for s in samples if s <= n]:
+                area = fb.ffps_workspace_bytes(b, n, m) - _least(b, n, m)
+                for n1 in [s for s in sizes if s <= n]:
+                    for m1 in [s for s in samples if s <= min(m, n1)]:
+                        if kernel(b, n1, m1) == fb.FFPS_KERNEL_LOCAL:
+                            used += 1
+                            assert kernel(b, n1, m1, ws_bytes=_least(b, n1, m1) + area) == fb.FFPS_KERNEL_LOCAL, (b, n, m, n1, m1)
+    assert used > 1000
+    assert fb.ffps_workspace_bytes(1, 12000, 300) == _least(1, 12000, 300)  # and none that nothing can use
