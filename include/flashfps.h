@@ -99,9 +99,8 @@ int ffps_prune_sizes(int N, int M, int keep_num, int keep_den, unsigned flags, i
  * for B clouds of N points and at most M samples per cloud.  Host only.
  * The workspace needs 256-byte alignment and no initialisation.
  * 20 to 24 bytes per point and 12 MiB are needed by every call; clouds of 4609
- * to 5,242,880 points with points x samples >= 2^25 and 80 samples or more, and up
- * to fifteen clouds out of which a call may sample a small one that needs less work,
- * have 34 bytes per point (and 140 to 900 KB per cloud) on top for the local-maximum
+ * to 5,242,880 points with points x samples >= 2^25 and 80 samples or more, up to four
+ * clouds from 922 samples on and up to fifteen from 1537 on, have 34 bytes per point (and 140 to 900 KB per cloud) on top for the local-maximum
  * kernel.  A workspace that lacks only that area, one sized for other clouds for
  * instance, is accepted: AUTO then takes the kernels that do without it, with the
  * same results (ffps_describe_kernel tells).  Clouds of more points have no such area, also

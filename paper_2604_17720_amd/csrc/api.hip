@@ -35,13 +35,11 @@ struct Workspace {  // byte offsets into the caller's workspace
     }
 };
 
-// Least points x samples of k_fps_local, in general and for small clouds that have at least so many workgroups each, and its
-// least samples (see takes_local).
+// Least points x samples of k_fps_local, and its least samples; and the most points per sample of clouds that go there
+// with less work, 0 where there are too many of them, by the workgroups each has (see takes_local).
 constexpr long kLocalWork = 1L << 25;
-constexpr int kLocalFew = 17, kLocalSmallMax = 8192, kLocalMediumMax = 65536;
-constexpr long local_work_small(int share) { return share >= 64 ? 3L << 20 : 5L << 20; }
-constexpr long kLocalWorkMedium = 9L << 21;  // 8193 to 65,536 points
 constexpr int kLocalSamples = 80;
+constexpr int local_points_per_sample(int share) { return share >= 64 ? 5 : share >= 17 ? 3 : 0; }
 
 Workspace carve(int B, int N, int M) {
     Workspace w;
@@ -55,12 +53,9 @@ Workspace carve(int B, int N, int M) {
     w.cand = o;     o += align_up((size_t)B * N * sizeof(int32_t));
     w.spos = o;     o += align_up((size_t)B * sizeof(int));
     // Neither clouds of one workgroup nor too few samples go to the local-maximum kernel.  What a call samples on the
-    // way (candidates, stages) has no more points and no more samples, but small clouds have lower lines: the work of
-    // as many of the points as are a small cloud decides, too.
-    const int share = kMaxGridWG / B;
-    auto work = [&](int points) { return (long)(N < points ? N : points) * M; };
-    const bool enough = work(N) >= kLocalWork || (share >= kLocalFew && (work(kLocalSmallMax) >= local_work_small(share) ||
-                                                                         work(kLocalMediumMax) >= kLocalWorkMedium));
+    // way (candidates, stages) has no more points and no more samples: never more work, but maybe fewer points per
+    // sample, so that as few points as are not one workgroup's decide.
+    const bool enough = (long)N * M >= kLocalWork || (long)M * local_points_per_sample(kMaxGridWG / B) > wgm_capacity();
     const bool local = N > wgm_capacity() && N <= local_capacity() && enough && M >= kLocalSamples && B <= kMaxBatchHelpers;
     w.least = w.local = o;
     w.local_bytes = local ? align_up(local_workspace_bound(B, N)) : 0;
@@ -185,51 +180,56 @@ int resolve_variant(int B, int N, int variant, const Device &dev) {
 
 // Which kernel AUTO takes (clouds of at most 256 points: one wave, one pick per pass).
 //
-// k_fps_block against k_fps_wgm, one cloud, uniform / planes / a stretch of a LiDAR frame: 1024 points
-// to 512 in 79, 70 against 121, 119 us; 4096 to 1024 in 198, 230 against 336, 364; 4608 to 2304 in
-// 379, 400, 705 against 639, 646, 705 us.  Beyond 4608 points it needs 12 or 16 points per lane and a cloud
-// is faster on many CUs, unless there are many, which then wait for one another: 8192 points to 4096,
-// 64 clouds 853, 963, 1667 against 1346, 1376, 1479 us of k_fps_grid, 80 clouds 850, 963, 1672 against 1717, 1850, 1974.
+// k_fps_block against k_fps_wgm, one cloud, uniform / planes / a stretch of a LiDAR frame: 1024 points to 512 71, 72, 106
+// against 121, 120, 153 us; 4096 to 1024 187, 232, 364 against 336, 364, 407; 4608 to 2304 333, 368, 760 against 639, 645,
+// 705. Beyond 4608 points it needs 12 or 16 points per lane and a cloud is faster on many CUs unless its samples are few
+// (5500 to 1375 283, 308, 516 against 236, 244, 232 of k_fps_local; to 343 133, 139, 183 against 161, 199, 249 of k_fps_grid,
+// but 376 against 188 for a cube with tails), or unless there are many clouds, which then wait for one another: 8192 points
+// to 4096, 64 clouds 761, 882, 1704 against 1332, 1327, 1474 us of k_fps_grid, 80 clouds 756, 885, 1701 against 1711, 1767,
+// 1913.
 constexpr int kOneWaveMax = kWaveCapacity;
 constexpr int kBlockMax = 4608;
 constexpr int kBlockManyClouds = 80;
 bool takes_block(int B, int N) {
     return N > kOneWaveMax && (N <= kBlockMax || (N <= block_capacity() && B >= kBlockManyClouds));
 }
-// k_fps_local against k_fps_grid: it has a dearer start (two sorts, 50 us in all at 45,678 points, 95 at 200,000) and
-// more rounds as long as the samples are few; its rounds do not grow with the points.  One to
-// eight clouds, uniform / planes / LiDAR, in us: 8192 points to 4096 548, 579, 640 against 584, 642, 677;
-// 12,000 to 1500 359, 366, 399 against 333, 362, 441, to 2800 423, 443, 499 against 458, 506, 581; 24,000 to
-// 1400 351, 369, 396 against 371, 411, 494; 60,000 to 560 334, 342, 308 against 340, 451, 525: points x samples = 2^25.
-// The sorts grow with the points, and uniform clouds gain least: 100,000 to 336 361 against 308, to
-// 800 404 against 406; 200,000 to 168 348 against 289, to 512 408 against 396; a million to 300 490 against 470.
-// Rooms and LiDAR frames gain half as much again there (100,000 to 600: 326 and 340 against 460 and 610), so the line
-// beyond 65,536 points is 2^26.  Beyond the registers' 3.1 million points, where k_fps_grid gives way to
-// k_fps_stream, the two meet near 80 samples (four million uniform points to 80: 673 against 738 us, five million to
-// 64: 886 against 769, to 128: 972 against 1086; a room of five million to 64: 747 against 1168).
-// Clouds of long tails are the ones that lose, whose far points are most of the samples and lie in few units:
-// 200,000 normally distributed points to 2048 take 575 against 527 us (a million to 2048 748 against 891), 300,000
-// points of which five in a hundred lie around the others at up to 100 times the extent, to 16,384, 3150 against 2210.
+// k_fps_local has a dearer start than k_fps_grid (two sorts, 45 us in all at 45,678 points, 60 at 200,000) and more rounds as
+// long as the samples are few; its rounds do not grow with the points.  In us, k_fps_grid first, uniform / a room / planes /
+// a LiDAR stretch: at points x samples = 2^25 8190 points to 4095 577:286, 594:267, 638:294, 667:262; 12,000 to 3000 462:277,
+// 492:266, 521:295, 583:274; 24,000 to 1500 379:277, 396:266, 415:311, 501:280.
 //
-// Those were the figures of 512 points per workgroup and of units that publish one point.  Now small clouds have more
-// and smaller units, and the lines of up to fifteen clouds below 65,536 points lie lower (k_fps_grid against k_fps_local, us,
-// a room / planes / LiDAR): 5000 points to 625 220, 248, 267 against 217, 224, 236, to 1250 298, 348, 364 against 233, 247, 245,
-// but to 312 175, 186, 201 against 197, 210, 210; 7000 to 875 262, 277 against 221, 237; eight clouds (planes, LiDAR) of 5000 to
-// 625 246, 305 against 259, 276, to 1250 340, 402 against 294, 305; 9000 to 2250 417, 429, 516 against 255, 270, 302;
-// 12,000 to 1500 352, 338 against 246, 272.  A lattice of 8000 to 1000 3111 against 475.  Clouds of tails still lose: a cube
-// with five points in a hundred at up to 100 times the extent, 6000 to 1000 315 against 350 (Cauchy distributed 283 against 354), 9000 to 1500 403 against 463,
-// 16,000 to 1500 465 against 528, but 9000 to 3000 556 against 500, so beyond 8192 points the line is 9 x 2^21.
-// With more than 4 samples of 9 points it stays at 2^25 (that would gain as well: 8192 to 4095 579 against 300; the tests of
-// k_fps_grid sample small clouds whole).
+// Few clouds have many and small units (plan_fps_local) and go with less.  Ordinary clouds gain from a tenth of the points as
+// samples on: 6000 to 1000 274:234, 268:208, 281:244, 360:214, to 1200 297:235, 302:220, 308:254, 378:217, to 3000 498:273,
+// 493:244, 526:304, 581:246; eight clouds of 8000 to 2666 455:320, 502:320, 511:348, 631:333.  Clouds whose points share
+// distances gain most, for k_fps_grid makes few picks a round there: a lattice of 5000 to 1250 4550:268, points on a raster
+// (planes, 1/32) 493:258, to 2500 3918:286.  What the line waits for are clouds of tails, whose far points are most of the
+// samples and lie in few units.  A cube with five points in a hundred at up to 100 times the extent / Cauchy distributed:
+// 6000 to 1000 342:335, 298:348, to 1200 366:346, 336:373, to 1500 394:348, 376:392 (but 7000 to 1750 432:523, 409:410); 9000
+// to 1500 401:480, 386:433, to 2250 485:499, 474:474; 16,000 to 1333 396:496, 374:487; eight clouds of 5000 to 1250 382:455,
+// 346:412, to 1666 436:528, 416:443.  From a fifth of up to four clouds' points, a third of up to fifteen's, and beyond 8192
+// points with 9 x 2^21, they lose a tenth at most times and a fifth at worst, where ordinary clouds gain a quarter to one
+// half and more samples turn the order for all.
 //
-// Many clouds leave each few workgroups, and what is gained shrinks, for LiDAR stretches first: 12 clouds of
-// 30,000 to 7500 812, 890, 1591 against 1310, 1405, 1687; 16 clouds (16 workgroups each) of 16,384 to 4096 668, 717,
-// 848 against 804, 834, 967, but of 30,000 to 7500 982, 1069, 1970 against 1554, 1613, 1860; 32 of 9000 to 4500 925, 974, 1454 against 930, 999, 1071; 64 of 30,000 to 7500 3117, 3522,
-// 6051 against 4625, 4732, 5154, to 15,000 5283, 5955, 9111 against 8798, 8940, 9377: from 12 x 2^25 on.
+// The sorts grow with the points, and uniform clouds gain least: 100,000 to 340 312:332 (a room 386:273, LiDAR 525:287), to
+// 700 386:364; 200,000 to 170 300:303 (383:251), to 340 361:346; a million to 100 356:338 (480:280).  Normally distributed
+// ones lose up to a third (200,000 to 340 293:380, 100,000 to 700 343:365), tails more (224:384; with more samples the order
+// turns: 300,000 to 16,384 normally distributed 2019:852, Cauchy 2015:2077, the cube with tails 2181:2549).  So the line
+// beyond 65,536 points is 2^26.  Beyond the registers' 3.1 million points k_fps_grid gives way to k_fps_stream, which is the
+// slower one with fewer samples already (64 of four million uniform points 685:504, of a room 995:440): 2^25 and 80 samples
+// are a cautious line there.
+//
+// Many clouds leave each few workgroups, and what is gained shrinks, for LiDAR stretches first (uniform / a room / planes /
+// LiDAR): 16 clouds (16 workgroups each) of 16,384 to 4096 804:526, 857:492, 857:556, 962:807; of 30,000 to 7500 1534:741,
+// 1641:714, 1641:849, 1841:1665; 20 of 30,000 to 7500 1785:967, 1855:931, 1823:1115, 2032:2182, with tails 1898:2401, to
+// 15,000 3248:1511, 3310:1411, 3308:1696, 3583:3004, tails 3409:3318; 32 of 9000 to 4500 928:691, 984:670, 1016:810,
+// 1081:1114, tails 1002:1429; 64 of 30,000 to 7500 4600:2456, 4788:2430, 4772:2922, 5244:5638, tails 4864:6587.  From 12 x
+// 2^25 on LiDAR stretches gain and tails break even; ordinary clouds would from a quarter of that.
+//
 // The sorts put the cloud number in gridDim.y: more clouds than that stay with k_fps_grid, which takes
 // them in batches.
 constexpr long kLocalWorkLarge = 1L << 26;  // beyond 65,536 points
 constexpr long kLocalWorkMany = 3L << 27;   // many clouds
+constexpr long kLocalWorkMedium = 9L << 21; // 8193 points and more, few per sample
 bool takes_local(int B, int N, int M, int v, int num_cu) {
     const long work = (long)N * M;
     if (B > kMaxBatchHelpers || M < kLocalSamples) return false;
@@ -237,9 +237,8 @@ bool takes_local(int B, int N, int M, int v, int num_cu) {
     const int share = (num_cu < kMaxGridWG ? num_cu : kMaxGridWG) / B;  // workgroups of a cloud
     if (B > 1 && (share < 16 || (share == 16 && N > 1024 * share))) return work >= kLocalWorkMany;
     if (M < 96 + N / 65536) return false;
-    if (N > kLocalMediumMax) return work >= kLocalWorkLarge;
-    if (share < kLocalFew || 9L * M > 4L * N) return work >= kLocalWork;
-    return N > kLocalSmallMax ? work >= kLocalWorkMedium : work >= local_work_small(share) && 8L * M >= N;
+    if (N > 65536) return work >= kLocalWorkLarge;
+    return work >= kLocalWork || ((long)M * local_points_per_sample(share) >= N && (N <= 8192 || work >= kLocalWorkMedium));
 }
 
 // Clouds that are rows of a larger array: point i of cloud b is row idx[b][i] of [B][points]

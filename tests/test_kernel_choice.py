@@ -78,15 +78,26 @@ def _least(b, n, m):
 
 
 def test_small_clouds_go_to_local_maxima_early():
-    """Up to fifteen clouds: an eighth of the points as samples where a cloud is small, a line of its own up to
-    65,536 points."""
+    """Up to four clouds of up to 8192 points from a fifth of the points as samples on, up to fifteen from a third,
+    beyond that size with a line of its own as well."""
     local, grid = fb.FFPS_KERNEL_LOCAL, fb.FFPS_KERNEL_GRID
-    assert [kernel(1, 5000, m) for m in (624, 625, 629, 630, 2222, 2223)] == [grid, grid, grid, local, local, grid]
-    assert [kernel(b, 5000, 1000) for b in (4, 5, 15, 16)] == [local, grid, grid, grid]
-    assert [kernel(b, 5000, 1049) for b in (4, 5, 15, 16)] == [local, local, local, grid]
-    assert [kernel(1, 8192, m) for m in (1023, 1024)] == [grid, local]
-    assert [kernel(15, 8193, m) for m in (2303, 2304)] == [grid, local]
-    assert [kernel(1, 65536, m) for m in (287, 288)] == [grid, local]
+    assert [kernel(1, 5000, m) for m in (999, 1000, 2223, 2500, 5000)] == [grid, local, local, local, local]
+    assert [kernel(b, 5000, 1000) for b in (4, 5)] == [local, grid]
+    assert [kernel(b, 5000, 1667) for b in (5, 15, 16)] == [local, local, grid]
+    assert kernel(5, 5000, 1666) == grid
+    assert [kernel(1, n, n // 2) for n in (4610, 6500, 8000, 8191)] == [local] * 4
+    assert [kernel(15, 8193, m) for m in (2730, 2731)] == [grid, local]
+    assert [kernel(1, 9000, m) for m in (1500, 2097, 2098)] == [grid, grid, local]
+    assert [kernel(1, 16000, m) for m in (1500, 2097, 2098)] == [grid, grid, local]
+    assert [kernel(1, 65536, m) for m in (511, 512)] == [grid, local]
+
+
+@pytest.mark.parametrize("b", [1, 4, 5, 15, 16, 17, 64])
+def test_more_samples_never_lead_back(b):
+    """Once a cloud has the samples for local maxima, more of them do not make it another kernel's."""
+    for n in (4609, 5000, 6999, 8192, 8193, 11000, 30000, 65536, 65537, 200000):
+        ks = [kernel(b, n, m) for m in sorted({min(n, int(80 * 1.03 ** i)) for i in range(400)})]
+        assert ks == sorted(ks), (b, n)
 
 
 def test_candidates_and_stages_have_the_area():

@@ -27,10 +27,11 @@ def _denser(n, seed):
 CASES = {
     # name: (clouds, M, start[, kernel, where it is another one]); a workgroup holds 512 points per row,
     # 256 workgroups are the most; points x samples of 2^25 (2^26 beyond 65,536 points, 12 x 2^25 with many
-    # clouds) and about a hundred samples are the least
-    "smallest": (lambda: inputs.uniform_cube(4609, 1)[None], 4609, 4608, "GRID"),
+    # clouds) and about a hundred samples are the least, or a fifth (a third) of up to 8192 points
+    "smallest": (lambda: inputs.uniform_cube(4609, 1)[None], 4609, 4608),
     "smallest with the work for it": (lambda: inputs.uniform_cube(5793, 1)[None], 5793, 5792),
-    "just short of it": (lambda: inputs.uniform_cube(8192, 1)[None], 4095, 0, "GRID"),
+    "half of a small cloud": (lambda: inputs.uniform_cube(8192, 1)[None], 4095, 0),
+    "just short of it": (lambda: inputs.uniform_cube(30000, 1)[None], 1118, 0, "GRID"),
     "few samples, still enough": (lambda: inputs.uniform_cube(2097152, 5)[None], 128, 9),
     "too few samples": (lambda: inputs.uniform_cube(2097152, 5)[None], 127, 9, "GRID"),
     "twenty-four rows, exactly": (lambda: inputs.uniform_cube(3145728, 6)[None], 150, 3145727),
@@ -56,19 +57,19 @@ CASES = {
     "as many small workgroups as there are, exactly": (lambda: inputs.room(11264, 5)[None], 3000, 7),
     "one point more than that": (lambda: inputs.room(11265, 5)[None], 3000, 11264),
     "half a row per unit for many samples": (lambda: inputs.planes_and_clusters(30001, 5)[None], 7501, 1),
-    "smallest of all that has the work for it": (lambda: inputs.uniform_cube(4609, 1)[None], 683, 4608),
-    "small, equal values": (lambda: inputs.lattice_grid(20, 20, 20)[None], 1000, 0),
+    "a fifth of the smallest": (lambda: inputs.uniform_cube(4609, 1)[None], 922, 4608),
+    "small, equal values": (lambda: inputs.lattice_grid(20, 20, 20)[None], 1600, 0),
     "small, a line": (lambda: inputs.lattice_line(5000)[None], 2000, 0),
-    "small, one place": (lambda: np.ones((1, 6000, 3), np.float32), 800, 3),
+    "small, one place": (lambda: np.ones((1, 6000, 3), np.float32), 1200, 3),
     "small, duplicates": (lambda: _dup(6000, 8)[None], 1600, 0),
-    "fifteen small ones": (lambda: np.stack([inputs.planes_and_clusters(4999, 90 + i) for i in range(15)]), 1049, 3),
-    "an outlier, small": (lambda: _outlier(8000), 1100, 1),
+    "fifteen small ones": (lambda: np.stack([inputs.planes_and_clusters(4999, 90 + i) for i in range(15)]), 1667, 3),
+    "an outlier, small": (lambda: _outlier(8000), 1700, 1),
     "equal values in sixteen rows": (lambda: inputs.lattice_grid(160, 128, 102)[None], 200, 0),
     "equal values in rows that are read again": (lambda: inputs.lattice_grid(160, 128, 108)[None], 200, 0),
     "clusters": (lambda: np.stack([inputs.planes_and_clusters(9001, 50 + i) for i in range(4)]), 4000, 1),
     "one pick": (lambda: inputs.uniform_cube(5000, 6)[None], 2, 0, "GRID"),
     "equal values, bins too large for one sort in LDS": (lambda: inputs.lattice_grid(60, 60, 12)[None], 20000, 0),
-    "a line": (lambda: inputs.lattice_line(5000)[None], 5000, 0, "GRID"),
+    "a line": (lambda: inputs.lattice_line(5000)[None], 5000, 0),
     "duplicates, fewer points than samples": (lambda: _dup(24000, 8)[None], 7000, 0),
     "one place, few samples": (lambda: np.ones((1, 6000, 3), np.float32), 100, 3, "GRID"),
     "one place": (lambda: np.ones((1, 6000, 3), np.float32), 5700, 3),
