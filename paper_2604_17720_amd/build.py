@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libflashfps.so")
 LIB_PROFILE = os.path.join(HERE, "libflashfps_prof.so")
 SOURCES = ["api.hip", "fps_wg.hip", "fps_grid.hip", "fps_stream.hip", "fps_local.hip", "fps_block.hip", "spatial.hip", "aux.hip"]
-HEADERS = ["fps_device.h", "fps_launch.h", "fps_exchange.h", "fps_local.h", "fps_block.h", "fps_space.h"]
+HEADERS = ["fps_device.h", "fps_launch.h", "fps_exchange.h", "fps_local.h", "fps_record.h", "fps_block.h", "fps_space.h"]
 
 # -ffp-contract=off: a fused multiply-add would change the low bits of the
 # squared distance and therefore the picks.

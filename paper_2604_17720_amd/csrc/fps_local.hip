@@ -50,6 +50,7 @@
 // status now and then and leave, too.
 #include "fps_exchange.h"
 #include "fps_local.h"
+#include "fps_record.h"
 #include "fps_space.h"
 
 namespace ffps {
@@ -58,19 +59,11 @@ namespace {
 
 constexpr int kWaves = 8;  // units of a workgroup, two waves per SIMD
 constexpr int kThreads = kWaves * kWave;
-// A 16-byte chunk is three words and the exclusive or of them with a constant of its kind and
-// the round: cleared memory stands for no round, and a chunk two rounds old (the buffer
-// alternates) is told from a new one.
-constexpr uint32_t kTagA = 0x9E3779B1u, kTagB = 0x85EBCA6Bu, kTagBox = 0x5F356495u;
 constexpr uint32_t kTagWindow = 1u << 20;  // "this round or a later one"
 constexpr int kPollsPerLook = 1024;        // at records that are missing, between two looks at the status
 
-// The third chunk has a byte for that: the rest of the word is a bound, rounded up.  (Half a word, and a bound of 16 bits,
-// made more rounds: 2 % of the time.)
-constexpr uint32_t kTagC = 0x27D4EB2Fu, kCheckC = 0xffu;
-__device__ __forceinline__ uint32_t bound_up(float v) { return (f2u(v) + kCheckC) & ~kCheckC; }
-
-__device__ __forceinline__ uint32_t chunk_round(const u32x4 &c, uint32_t which) { return c.x ^ c.y ^ c.z ^ c.w ^ which; }
+// The round a chunk is of, if it is whole.
+__device__ __forceinline__ uint32_t chunk_round(const u32x4 &c, uint32_t which) { return record_check(c.x, c.y, c.z, which, c.w); }
 
 // 16 bytes of every unit, side by side: the boxes, then the records of even and of odd rounds.
 constexpr int kBoxPlanes = 4, kRecordPlanes = 3;
@@ -393,13 +386,13 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
             char *buf = ex + plane * (kBoxPlanes + kRecordPlanes * (round & 1)) + (size_t)unit * 16;
             u32x4 A, B, C;
             A.x = f2u(best.v) | (stopped ? 0x80000000u : 0u);
-            A.y = best.i | (picked ? 0x80000000u : 0u);
+            A.y = index_word(best.i, f2u(best.v2), f2u(best.v3), picked);
             A.z = f2u(best.v2);
-            A.w = A.x ^ A.y ^ A.z ^ kTagA ^ round;
+            A.w = record_check(A.x, A.y, A.z, kTagA, round);
             B.x = f2u(best.x); B.y = f2u(best.y); B.z = f2u(best.z);
-            B.w = B.x ^ B.y ^ B.z ^ kTagB ^ round;
+            B.w = record_check(B.x, B.y, B.z, kTagB, round);
             C.x = f2u(best.x2); C.y = f2u(best.y2); C.z = f2u(best.z2);
-            C.w = bound_up(best.v3) | ((C.x ^ C.y ^ C.z ^ kTagC ^ round) & kCheckC);
+            C.w = record_check(C.x, C.y, C.z, kTagC, round);
             store_chunk(buf, A);
             store_chunk(buf + plane, B);
             store_chunk(buf + 2 * plane, C);
@@ -411,7 +404,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
     if (lane == 0) {
         auto put = [&](int k, float c0, float c1, float c2) {
             u32x4 A = {f2u(c0), f2u(c1), f2u(c2), 0u};
-            A.w = A.x ^ A.y ^ A.z ^ kTagBox ^ (uint32_t)(k + 1);
+            A.w = record_check(A.x, A.y, A.z, kTagBox, (uint32_t)(k + 1));
             store_chunk(ex + plane * k + (size_t)unit * 16, A);
         };
         put(0, ba.lx, ba.ly, ba.lz); put(1, ba.hx, ba.hy, ba.hz);
@@ -512,7 +505,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
         auto missing = [&](int q) {
             const uint32_t da = chunk_round(ra[q], kTagA) - round;
             uint32_t d = da | (chunk_round(rb[q], kTagB) - round);
-            if constexpr (TWO) d |= (chunk_round(rc[q], kTagC) ^ round) & kCheckC;
+            if constexpr (TWO) d |= chunk_round(rc[q], kTagC) - round;
             return (__builtin_amdgcn_ballot_w64(d != 0u) & want[Q0 + q]) |
                    (__builtin_amdgcn_ballot_w64(da >= kTagWindow) & wait[Q0 + q] & ~want[Q0 + q]);
         };
@@ -568,7 +561,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
                 if (__builtin_amdgcn_inverse_ballot_w64(pm[q])) plist[pbase + lanes_below(pm[q])] = pe[q];
                 if (__builtin_amdgcn_inverse_ballot_w64(rm[q])) {
                     u32x4 *e = rlist + (TWO ? 3 : 2) * (rbase + lanes_below(rm[q]));
-                    e[0] = u32x4{f2u(sv[s]), ra[q].y & 0x7fffffffu, ra[q].z, TWO ? rc[q].w & ~kCheckC : 0u};
+                    e[0] = u32x4{f2u(sv[s]), ra[q].y & kRecordIndex, ra[q].z, TWO ? bound_of_others(ra[q].z, ra[q].y) : 0u};
                     e[1] = u32x4{f2u(sx[s]), f2u(sy[s]), f2u(sz[s]), off[s] >> 4};
                     if constexpr (TWO) e[2] = rc[q];
                 }
@@ -880,6 +873,7 @@ hipError_t launch_t(LocalArgs &a, int clouds, hipStream_t s) {
 #define FFPS_LOCAL_ROWS(X) X(1) X(2) X(3) X(4) X(6) X(8) X(12) X(16) X(24) X(32) X(40)
 constexpr int kMaxRows = 40;
 constexpr int kUnitMax = kMaxRows * kWave;
+static_assert(kMaxGridWG * kWaves * kUnitMax <= (1 << kIndexBitsOfRecord), "an index and the bound of a record are one word");
 
 }  // namespace
 
