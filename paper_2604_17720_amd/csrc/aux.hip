@@ -110,7 +110,7 @@ __device__ __forceinline__ int block_prefix(int cnt, int *part, int tid, int *to
 // First tile of a block.
 __device__ __forceinline__ int first_tile(int tiles, int block, int blocks) { return (int)((long)tiles * block / blocks); }
 
-// Fill of FPS-Prune, a tile of the bitmap per block (beyond 8.4 million points several, so that the
+// Fill of FPS-Prune, a tile of the bitmap per block (beyond 2.1 million points several, so that the
 // counting does not grow with the square of the points): ranks of the free indices by popcount
 // (a block counts the words of the tiles before its own again: 25 KB for 200,000 points) and
 // scan, then every free index decides on its own whether

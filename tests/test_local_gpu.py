@@ -64,6 +64,13 @@ CASES = {
     "small, duplicates": (lambda: _dup(6000, 8)[None], 1600, 0),
     "fifteen small ones": (lambda: np.stack([inputs.planes_and_clusters(4999, 90 + i) for i in range(15)]), 1667, 3),
     "an outlier, small": (lambda: _outlier(8000), 1700, 1),
+    "six rows, exactly": (lambda: inputs.uniform_cube(786432, 7)[None], 130, 786431),
+    "eight rows": (lambda: inputs.room(786433, 7)[None], 131, 5),
+    "twelve rows": (lambda: inputs.uniform_cube(1048577, 7)[None], 130, 0),
+    "twelve rows, exactly": (lambda: inputs.room(1572864, 7)[None], 129, 9),
+    "equal values in six rows": (lambda: inputs.lattice_grid(88, 88, 88)[None], 150, 0),
+    "equal values in eight rows": (lambda: inputs.lattice_grid(100, 100, 100)[None], 150, 7),
+    "equal values in twelve rows": (lambda: inputs.lattice_grid(112, 112, 112)[None], 150, 0),
     "equal values in sixteen rows": (lambda: inputs.lattice_grid(160, 128, 102)[None], 200, 0),
     "equal values in rows that are read again": (lambda: inputs.lattice_grid(160, 128, 108)[None], 200, 0),
     "clusters": (lambda: np.stack([inputs.planes_and_clusters(9001, 50 + i) for i in range(4)]), 4000, 1),
