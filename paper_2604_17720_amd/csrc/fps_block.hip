@@ -2,7 +2,8 @@
 // (the rule, and why picks may be made and applied out of order, stands in fps_local.hip).
 //
 // What bounds a cloud this small is the number of instructions of a round (with two waves on a
-// SIMD an instruction costs about eight cycles).  k_fps_wgm takes 20 to 30 picks a round but
+// SIMD an instruction costs about eight cycles): nine tenths of its 3300 cycles with 1024 points, five sixths of 4900 with
+// 4096, where the waves wait for the one that has most picks to apply (seven tenths in LiDAR stretches).  k_fps_wgm takes 20 to 30 picks a round but
 // needs about 12,000 cycles for it: pairwise masks of 64 candidates, one wave that settles them,
 // and every pick applied to every point.  Here a round has eleven picks and takes 1.3 us (1024 points):
 //   - The points are put along a space-filling curve (two stable radix passes in LDS, by cells of a

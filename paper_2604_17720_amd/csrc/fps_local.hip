@@ -40,8 +40,8 @@
 //     room, 45 % more than 5001 of 45,678, 37 % more than 16,384 of a LiDAR frame.
 //
 // Measured, exact FPS of a room of 200,000 points to 50,000 samples, sorts included:
-// 0.67 ms against 4.44 ms with k_fps_grid; 45,678 points to 5,001: 0.35 against 0.84 ms;
-// five million to 1024: 1.09 ms against 4.7 ms with k_fps_stream.
+// 0.63 ms against 4.44 ms with k_fps_grid; 45,678 points to 5,001: 0.34 against 0.84 ms;
+// five million to 1024: 0.92 ms against 4.7 ms with k_fps_stream.
 // Before the second points, loops by the number of slots, lanes' states as masks in scalar registers and a unit's own pick
 // applied beside the others': 0.84, 0.43 and 1.2 ms.
 //
@@ -298,6 +298,9 @@ __device__ __forceinline__ Best unit_best(const Points<P> &p, const float (&m)[P
 // takes are dearer than a second wait (at 24 to 40 rows; 12 and 16 rows were not tried).
 constexpr int kGatherRows = 16;
 
+// What scalar registers do not hold (54 to 82 of them up to 12 rows, 108, 138, 211 and 313 from 16 to 40) is kept in lanes of one or two
+// vector registers.  Up to 12 rows half of that is read in the rounds: 38 to 46 instructions of 2500 to 3600 in the loop with
+// four slots, 7 to 15 of 1200 to 2700 in the others; at 16 rows 60, 37 and 27, at 24 80, 67 and 45, at 40 204, 164 and 152 of 5600 to 7000.
 template <int P>
 __global__ __launch_bounds__(kThreads, 2) void k_fps_local(LocalArgs a) {
     constexpr int kSlots = 4;
@@ -881,7 +884,11 @@ static_assert(kMaxGridWG * kWaves * kUnitMax <= (1 << kIndexBitsOfRecord), "an i
 // long as there are not so many that the first rounds, in which all see all, cost more than that saves.  us with
 // 512, 256 and 171 points per workgroup: 9000 points to 4000 435, 342, 318 (128 points: 295); 16,384 to 4096 369, 333, 316;
 // 30,000 of a room to 2000 295, 288, 318; 30,000 of a LiDAR frame to 2500 465, 368, 359; 45,678 to 5001 341, 355, 364.
-// So up to 88 workgroups have down to 128 points.  With a quarter of the points as samples most rounds are late ones: 60,000
+// So up to 88 workgroups have down to 128 points; the line is where 88 of them have 512 points each, 45,056.  With 512 points, 88
+// workgroups and 256 points, a cube / a room / planes / LiDAR: 34,000 to 3777 356, 344, 385 / 324, 319, 319 / 363, 352, 377 / 388, 351,
+// 357; 42,000 to 4666 377, 365, 414 / 341, 333, 347 / 388, 382, 395 / 368, 370, 355; 45,678 to 5075 381, 394, 402 / 345, 358, 351 / 382,
+// 398, 389 / 388, 424, 375; 64,000 to 7111 401, 418, 441 / 368, 393, 400 / 417, 439, 439 / 448, 479, 450.
+// With a quarter of the points as samples most rounds are late ones: 60,000
 // to 25,000 500, 462, 472; 120,000 to 30,000 591, 561, 568; 60,000 to 5000 326, 339, 351: 256 points there.
 LocalPlan plan_fps_local(int B, int N, int M, int num_cu) {
     const int maxG = num_cu < kMaxGridWG ? num_cu : kMaxGridWG;
